@@ -497,8 +497,8 @@ hipError_t launch_export_keys(hipStream_t s, int n, const Rec *rec, const int *k
                               double *tmin_out);
 hipError_t launch_step_backward(hipStream_t s, const Particles &P, const Grid &G, double dt,
                                 double e, const int *partner, const double *tcoll,
-                                const StateGrad &gout, const StateGrad &gin, double *ebuf,
-                                double *ge);
+                                const StateGrad &gout, const StateGrad &gin, double *epart,
+                                double *ge);  // epart: (n + 255) / 256 sums
 // Deposition of per-sphere sources onto the corner nodes of a periodic
 // Cartesian grid: positions x, y, z (n), sources a[q * n + i] (comp <= 8),
 // nc cells of side h = L / nc per axis, out[node * comp + q] (nnode nodes,

@@ -136,3 +136,40 @@ def test_checkpoint_recompute_and_determinism():
         assert torch.equal(a, b)
     for a, b in zip(grads[0], grads[2]):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 257, 70_001])
+def test_restitution_gradient_sums_every_pair(n):
+    """The e-gradient over one sphere, less and more than a workgroup and many of them: pairs
+    (0, 1), (2, 3), ... at given times against the pair formula m_r g (bvin.n/m_i - bvjn.n/m_j)
+    summed in extended precision; a pair's value carries under 64 roundings and the fixed tree
+    under 64 additions per value."""
+    rng = np.random.default_rng(n)
+    x, v, gx, gv = (rng.normal(size=(3, n)) for _ in range(4))
+    x = x + 50.0
+    r, m = rng.uniform(0.5, 1.0, n), rng.uniform(0.5, 2.0, n)
+    dt, e, L = 0.4, 0.8, (100.0,) * 3
+    i = np.arange(0, n - 1, 2)
+    j = i + 1
+    partner = np.full(n, -1, dtype=np.int32)
+    partner[i], partner[j] = j, i
+    t = np.full(n, np.nan)
+    t[i] = t[j] = rng.uniform(0.0, dt, len(i))
+    X, V, GX, GV, R, M, T = (q.astype(np.longdouble) for q in (x, v, gx, gv, r, m, t))
+    d, u = X[:, j] - X[:, i], V[:, j] - V[:, i]
+    nn = (d + T[i] * u) / (R[i] + R[j])
+    g = (u * nn).sum(0)
+    terms = [(GV + (dt - T) * GX)[:, k] * nn / M[k] for k in (i, j)]
+    scale = M[i] * M[j] / (M[i] + M[j]) * g
+    want = (scale * (terms[0] - terms[1]).sum(0)).sum()
+    umag = (np.abs(V[:, i]) + np.abs(V[:, j]))
+    nmag = (np.abs(X[:, i]) + np.abs(X[:, j]) + T[i] * umag) / (R[i] + R[j])
+    bmag = [(np.abs(GV) + dt * np.abs(GX))[:, k] * nmag / M[k] for k in (i, j)]
+    mag = (M[i] * M[j] / (M[i] + M[j]) * (umag * nmag).sum(0) * (bmag[0] + bmag[1]).sum(0)).sum()
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+    p = pc.Particles(*dev(np.concatenate([x, v])), dev(r), dev(m))
+    gin = torch.empty((6, n), dtype=torch.float64, device="cuda")
+    ge = torch.full((), 3.0, dtype=torch.float64, device="cuda")
+    pc.pcol_step_backward(pc.Context(n), p, L, dt, e, dev(partner), dev(t),
+                          list(dev(np.concatenate([gx, gv]))), list(gin), ge)
+    assert abs(ge.item() - 3.0 - float(want)) <= 128 * 2.0 ** -53 * (float(mag) + 3.0)
