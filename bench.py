@@ -760,7 +760,7 @@ def main():
                      # WRITE_SIZE, copy-calibrated) and algorithmic bytes
                      "hbm_frac_counted": (traffic / det_med / PEAK_HBM) if traffic else None,
                      "hbm_frac_algorithmic": phase_bytes["detect"] / det_med / PEAK_HBM,
-                     "kernel": "k_detect_half64g",
+                     "kernel": "k_detect_half64",
                      "note": f"FP64 vector operations (an FMA counts one): {OPS_PER_PAIR_TEST} per "
                              f"unordered pair test; as flops ({FLOPS_PER_PAIR_TEST} per test) "
                              f"{flops / 1e12:.2f} of 78.6 TFLOP/s"},

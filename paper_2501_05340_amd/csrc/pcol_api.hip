@@ -713,33 +713,41 @@ static double fp32_band(const pcol_ctx *ctx, double dt) {  // returns the band
 }
 
 // Tolerance of the binary64 Gram filter (filter 0).  The filter evaluates
-// G = alpha_i + <P_j, Q_i> (seven FMAs from alpha_i) from coordinates relative
-// to the home cell centre and passes the pair when G <= fl(tol - beta_j); in
-// real numbers that is F = G + beta_j <= tol.  For a pair the rule keeps, the
-// real F is at most E0 = 3 eps ((reach^2 + (2 r_max)^2) + reach 2 v_max dt2)
-// (the binary64 argument: the kept root c / (-b + sqrt D) <= dt gives
-// c <= 2 |b| dt (1 + 6 eps) < |b| dt2).  The evaluation differs from the real F by
-//  * the relative coordinates: each is one or two roundings of values below
-//    L + h, so the separation d is off by at most delta = eps (2 (Lmax + h) + X_i +
-//    X_j), which moves F by at most delta (2 reach + 2 v_max dt2) + delta^2;
-//  * alpha, beta, Q, P (a few roundings each, <= 6 eps relative) and the seven
+// g = beta_i + <P_i, Q_j> (seven FMAs from beta_i) and passes the pair when
+// g <= fl(tol - beta_j); in real numbers that is F = g + beta_j <= tol.  For a
+// pair the rule keeps, the real F is at most
+// E0 = 3 eps ((reach^2 + (2 r_max)^2) + reach 2 v_max dt2) (the binary64 argument:
+// the kept root c / (-b + sqrt D) <= dt gives c <= 2 |b| dt (1 + 6 eps) < |b| dt2).
+// The evaluation differs from the real F by
+//  * the image shift of the candidate: one rounding per axis of a value below
+//    L + h, so the separation d is off by at most delta = 2 eps (Lmax + h), which
+//    moves F by at most delta (2 reach + 2 v_max dt2) + delta^2;
+//  * beta_i, beta_j, Q, (a few roundings each, <= 6 eps relative) and the seven
 //    FMAs of the sum (<= 7 eps of the sum of magnitudes): at most
-//    16 eps (A_ + B_ + S) with A_, B_, S the bounds of |alpha|, |beta| and
-//    sum_k |P_k Q_k| for |x_i| <= X_i = (sqrt 3 / 2) h, |x_j| <= X_i + reach;
-//  * the threshold's one rounding, at most eps (tol + |beta|): the eps tol part
-//    is covered by the factor two below, the eps B_ part by a 17th eps.
+//    16 eps (2 B + S) with B, S the bounds of |beta| and sum_k |P_k Q_k| for
+//    |x| <= X, the norm of the box sides each lengthened by a cell;
+//  * the threshold's one rounding, at most eps (tol + |beta_j|): the eps tol part
+//    is covered by the factor two below, the eps B part by a 17th eps.
 // The tolerance is twice the sum.
-static double gram64_tolerance(double h, double R, double V, double r, double Lmax,
+static double gram64_tolerance(double X, double h, double R, double V, double r, double Lmax,
                                double dt2) {
-  const double s3 = sqrt(3.0), eps = 0x1.0p-53;
-  const double Xi = 0.5 * s3 * h * (1.0 + 1e-6), Xj = Xi + R;
-  const double Ab = Xi * Xi + dt2 * Xi * V + r * r, Bb = Xj * Xj + dt2 * Xj * V + r * r;
-  const double S = Xj * (2.0 * Xi + dt2 * V) + V * dt2 * Xi + 2.0 * r * r;
+  const double eps = 0x1.0p-53;
+  X *= 1.0 + 1e-6;
+  const double B = X * X + dt2 * X * V + r * r;
+  const double S = X * (2.0 * X + dt2 * V) + V * dt2 * X + 2.0 * r * r;
   const double E0 = 3.0 * eps * ((R * R + 4.0 * r * r) + R * 2.0 * V * dt2);
-  const double delta = eps * (2.0 * (Lmax + h) + Xi + Xj);
+  const double delta = 2.0 * eps * (Lmax + h);
   const double Epos = delta * (2.0 * R + 2.0 * V * dt2) + delta * delta;
-  const double E = 17.0 * eps * (Ab + Bb + S);
+  const double E = 17.0 * eps * (2.0 * B + S);
   return 2.0 * (E0 + Epos + E);
+}
+
+// Norm of the box sides, each lengthened by a cell: bounds every position and
+// periodic image that the pair tests meet.
+static double grid_norm(const Grid &G) {
+  double q = 0.0;
+  for (int a = 0; a < 3; ++a) q += (G.L[a] + G.h[a]) * (G.L[a] + G.h[a]);
+  return sqrt(q);
 }
 
 // sweep 1: keys of all spheres (all active) into ctx->key_j / key_t (sorted
@@ -784,7 +792,7 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
         h = ctx->h[a] > h ? ctx->h[a] : h;
         Lmax = ctx->G.L[a] > Lmax ? ctx->G.L[a] : Lmax;
       }
-      A.tol64 = gram64_tolerance(h, R, ctx->vmax_pass, ctx->rmax_pass, Lmax, A.dt2);
+      A.tol64 = gram64_tolerance(grid_norm(ctx->G), h, R, ctx->vmax_pass, ctx->rmax_pass, Lmax, A.dt2);
       // pairs with a sphere above the split extent: |d| up to the full reach
       const double Rw = ctx->reach, sw = 2.0 * ctx->rmax;
       A.tol_wide = 16.0 * 0x1.0p-53 * (Rw * Rw + sw * sw + Rw * 2.0 * ctx->vmax * A.dt2);
@@ -1413,10 +1421,12 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   A.tol = 16.0 * 0x1.0p-53 * hmax * hmax * (2.0 + A.dt2 / dt);
   {
     // reach <= hmax, 2 r_max <= hmax and 2 v_max dt <= hmax in every box (see above)
-    double Lmax = 0.0;
-    for (const Grid &G : bp->gtab_h)
+    double Lmax = 0.0, X = 0.0;
+    for (const Grid &G : bp->gtab_h) {
+      X = std::max(X, grid_norm(G));
       for (int a = 0; a < 3; ++a) Lmax = G.L[a] > Lmax ? G.L[a] : Lmax;
-    A.tol64 = gram64_tolerance(hmax, hmax, hmax / (2.0 * dt), 0.5 * hmax, Lmax, A.dt2);
+    }
+    A.tol64 = gram64_tolerance(X, hmax, hmax, hmax / (2.0 * dt), 0.5 * hmax, Lmax, A.dt2);
   }
   A.K = ctx->K;
   A.fp32 = 0;

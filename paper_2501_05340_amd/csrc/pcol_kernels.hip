@@ -544,9 +544,9 @@ __device__ __forceinline__ void record_contact(const DetectArgs &A, int i, int g
 // sphere); deciding it at once would run the square root, the division and
 // two atomics for one live lane while the other 63 idle, so survivors are
 // queued and decided 64 at a time at the end of the home cell, where few
-// registers are live.  A survivor that finds the queue full is decided at
-// once.
-constexpr int QCAP = 256;
+// registers are live, or sooner when the queue has no room for another step's.
+constexpr int QCAP = 256;    // binary32 filter: two homes appended per step
+constexpr int QCAP64 = 512;  // binary64 filter: four homes
 
 struct SurvivorQueue {
   int2 *q;              // cap entries in LDS, private to the wave
@@ -571,22 +571,6 @@ __device__ __forceinline__ void flush_survivors(const DetectArgs &A, const Grid 
     }
   }
   Q.n = 0;
-}
-
-// Queue this lane's survivor (i, g) if `pass`; returns false if the queue had
-// no room for the wave's survivors, which the caller then decides at once.
-__device__ __forceinline__ bool push_survivor(bool pass, int i, int g, SurvivorQueue &Q) {
-  const unsigned long long m = __ballot(pass);
-  if (!m) return true;
-  const int c = __popcll(m);
-  Q.pushed += c;
-  if (Q.n + c > Q.cap) return false;
-  if (pass) {
-    const unsigned int lane = __lane_id();
-    Q.q[Q.n + __popcll(m & ((1ull << lane) - 1ull))] = make_int2(i, g);
-  }
-  Q.n += c;
-  return true;
 }
 
 // Append the survivors of two home spheres i0 and i1 against the lane's
@@ -818,201 +802,227 @@ __device__ __forceinline__ void detect_cell32(const DetectArgs &A, const Grid &G
 
 // ---------------------------------------------------------------- a5, binary64 Gram filter
 
-// The binary64 filter in Gram form.  With positions relative to the home cell
-// centre o, F = |d|^2 - s^2 + dt2 (d . u) = alpha_i + beta_j + <P_j, Q_i> where
-//   P_j = (x_j, v_j, r_j),  Q_i = (-2 x_i - dt2 v_i, -dt2 x_i, -2 r_i),
-//   alpha_i = |x_i|^2 + dt2 x_i.v_i - r_i^2,  beta_j = |x_j|^2 + dt2 x_j.v_j - r_j^2
-// (d = x_j - x_i, u = v_j - v_i, s = r_i + r_j).  Q_i and alpha_i are formed once
-// per home sphere into LDS, P_j and the candidate's threshold tol64 - beta_j
-// once per candidate and chunk (the run's periodic shift applied), so a pair
-// costs seven FMAs (alpha_i + <P_j, Q_i>, alpha_i the first addend) and one
-// compare.  A pair passes iff alpha_i + <P_j, Q_i> <= tol64 - beta_j as
-// evaluated, tol64 a bound on the rounding of this evaluation, of the
-// threshold and of the relative coordinates for pairs the rule can keep (host,
-// gram64_tolerance); survivors are decided by the rule (flush_survivors), so
-// the result is exactly the rule's.
-struct alignas(16) HomeQ {
-  double q[7];
-  double alpha;
-};
+// The binary64 filter in Gram form.  F = |d|^2 - s^2 + dt2 (d . u)
+// = beta_i + beta_j + <P_i, Q_j> where
+//   P_i = (x_i, r_i, v_i),  Q_j = (-2 x_j - dt2 v_j, -2 r_j, -dt2 x_j),
+//   beta = |x|^2 + dt2 x.v - r^2
+// (d = x_j - x_i, u = v_j - v_i, s = r_i + r_j).  A pair passes iff
+// beta_i + <P_i, Q_j> <= tol64 - beta_j as evaluated (beta_i the first addend
+// of seven FMAs), tol64 a bound on the rounding of this evaluation and of the
+// threshold for pairs the rule can keep (host, gram64_tolerance); survivors are
+// decided by the rule (flush_survivors), so the result is exactly the rule's.
+//
+// The home sphere i is uniform across the wave and P_i is its record as it
+// stands, so the records of the homes are read through the scalar cache
+// straight into scalar registers, the operands of the FMAs (one each): no
+// home terms are formed, staged or read back.  Lanes hold Q_j and the threshold
+// of their candidate, formed once per chunk; of the home only beta_i goes
+// through LDS.  A pair costs seven FMAs and one compare of vector issue, which
+// bounds the kernel.  Coordinates are the caller's, not relative to the cell:
+// the tolerance then grows with the box, as 1e-13 L^2, which admits pairs up to
+// 4e-7 L apart, and saves the subtraction on both sides.
+typedef double d8 __attribute__((ext_vector_type(8)));
+typedef const d8 __attribute__((address_space(4))) *ScalarRec;
 
-// Pair tests of one candidate chunk against a batch of homes, two homes per
-// step; a survivor that finds the queue full is decided at once.
-template <bool MASK>
-__device__ __forceinline__ void detect_chunk64(const DetectArgs &A, const Grid &G, const HomeQ *hq,
-                                               int nb, int i0, int g, int thr, const double P[7],
-                                               double fthr, SurvivorQueue &Q) {
-  int k = 0;
-  for (; k + 1 < nb; k += 2) {
-    const HomeQ a = hq[k], b = hq[k + 1];
-    double t0 = a.alpha, t1 = b.alpha;
+__device__ __forceinline__ double gram_beta(double x, double y, double z, double vx, double vy,
+                                            double vz, double r, double dt2) {
+  const double xx = __builtin_fma(z, z, __builtin_fma(y, y, x * x));
+  const double xv = __builtin_fma(z, vz, __builtin_fma(y, vy, x * vx));
+  return __builtin_fma(-r, r, __builtin_fma(dt2, xv, xx));
+}
+
+// Queue the survivors of home i (the lanes of m) against the lane's candidate
+// g, but for own-cell candidates that do not come after i (g < last holds the
+// pair to j after i; last is INT_MAX outside the own cell).  The queue has room
+// for a wave's worth.
+__device__ __forceinline__ void push_home(unsigned long long m, int i, int g, int last,
+                                          SurvivorQueue &Q) {
+  if (!m) return;
+  m &= __builtin_amdgcn_ballot_w64(i < last);
+  if (!m) return;
+  const int at = __builtin_amdgcn_mbcnt_hi(
+      (unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, (unsigned int)Q.n));
+  if (__builtin_amdgcn_inverse_ballot_w64(m)) Q.q[at] = make_int2(i, g);
+  // kept in a scalar register: the loops that test it stay uniform, and the
+  // home records they index stay scalar loads
+  Q.n = __builtin_amdgcn_readfirstlane(Q.n + __popcll(m));
+}
+
+// NC chunks of a home cell's candidate list, from slot base on, against its
+// homes [i0 + k, i0 + nb), two homes a step; the records of the next two are
+// fetched while two are tested.  Returns nb, or the home to go on from when the
+// queue has no room for another step's survivors.  Each scalar record serves NC wave-wide tests:
+// with one chunk a pass the waves stood waiting for scalar loads (the homes of
+// the waves on two CUs exceed their 16 KB scalar cache), 2.65 ms at 16M.
+template <int NC>
+__device__ __forceinline__ int detect_chunks(const DetectArgs &A, const CellSet &S, int base,
+                                             int i0, int k, int nb, const double *hbeta,
+                                             const RunT *rt, SurvivorQueue &Q) {
+  const int *pre = S.pre;
+  const double dt2 = A.dt2;
+  double q[NC][7], thr[NC];
+  int g[NC], last[NC];
 #pragma unroll
-    for (int c = 0; c < 7; ++c) {
-      t0 = __builtin_fma(P[c], a.q[c], t0);
-      t1 = __builtin_fma(P[c], b.q[c], t1);
-    }
-    const int i = i0 + k;
-    const bool p0 = t0 <= fthr && (!MASK || i < thr);
-    const bool p1 = t1 <= fthr && (!MASK || i + 1 < thr);
-    if (!push_survivor(p0, i, g, Q) && p0) {
-      double t;
-      if (pair_time(A.rec[i], A.rec[g], G, A.dt, t)) record_contact(A, i, g, t);
-    }
-    if (!push_survivor(p1, i + 1, g, Q) && p1) {
-      double t;
-      if (pair_time(A.rec[i + 1], A.rec[g], G, A.dt, t)) record_contact(A, i + 1, g, t);
-    }
-  }
-  if (k < nb) {
-    const HomeQ a = hq[k];
-    double t0 = a.alpha;
+  for (int c = 0; c < NC; ++c) {
+    const int v = base + c * WAVE + (int)__lane_id();
+    // the run of list slot v: the last run whose first slot is at most v.  The
+    // first slots are non-decreasing, so it is the number of runs after the
+    // first that start at or before v (an empty run starts where the next
+    // does, so it is never the one counted last for a slot inside the list)
+    int r = 0;
 #pragma unroll
-    for (int c = 0; c < 7; ++c) t0 = __builtin_fma(P[c], a.q[c], t0);
-    const int i = i0 + k;
-    const bool p0 = t0 <= fthr && (!MASK || i < thr);
-    if (!push_survivor(p0, i, g, Q) && p0) {
-      double t;
-      if (pair_time(A.rec[i], A.rec[g], G, A.dt, t)) record_contact(A, i, g, t);
-    }
+    for (int k = 1; k < MAXRUN; ++k) r += v >= pre[k] ? 1 : 0;
+    asm volatile("" : "+v"(r));  // the count apart from the table address
+    const RunT run = rt[r];
+    const bool ok = v < S.total;
+    // past the end of the list: some record, and a threshold nothing meets
+    g[c] = ok ? run.off + v : i0;
+    last[c] = ((run.code >> 6) & 1) ? g[c] : 0x7fffffff;
+    const Rec b = A.rec[g[c]];
+    const double x = b.x + run.sx, y = b.y + run.sy, z = b.z + run.sz;
+    q[c][0] = __builtin_fma(-2.0, x, -dt2 * b.vx);
+    q[c][1] = __builtin_fma(-2.0, y, -dt2 * b.vy);
+    q[c][2] = __builtin_fma(-2.0, z, -dt2 * b.vz);
+    q[c][3] = -2.0 * b.r;
+    q[c][4] = -dt2 * x;
+    q[c][5] = -dt2 * y;
+    q[c][6] = -dt2 * z;
+    const double th = A.tol64 - gram_beta(x, y, z, b.vx, b.vy, b.vz, b.r, dt2);
+    thr[c] = ok ? th : -INFINITY;
   }
+  const auto test = [&](d8 p, double beta, int c) {
+    double t = __builtin_fma(p[0], q[c][0], beta);
+#pragma unroll
+    for (int k = 1; k < 7; ++k) t = __builtin_fma(p[k], q[c][k], t);
+    return (unsigned long long)__builtin_amdgcn_ballot_w64(t <= thr[c]);
+  };
+  const ScalarRec homes = (ScalarRec)(uintptr_t)(A.rec + i0);
+  const int top = nb - 1;
+  d8 a = homes[k], b = homes[k < top ? k + 1 : top];
+  double ba = hbeta[k], bb = hbeta[k < top ? k + 1 : top];
+  for (; k < nb && Q.n <= Q.cap - 2 * NC * WAVE; k += 2) {
+    const int ka = k + 2 < top ? k + 2 : top, kb = k + 3 < top ? k + 3 : top;
+    const d8 na = homes[ka], nbr = homes[kb];
+    const double nba = hbeta[ka], nbb = hbeta[kb];
+    unsigned long long m0[NC], m1[NC], any = 0ull;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      m0[c] = test(a, ba, c);
+      any |= m0[c];
+    }
+    if (k < top) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        m1[c] = test(b, bb, c);
+        any |= m1[c];
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) m1[c] = 0ull;
+    }
+    if (any) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        push_home(m0[c], i0 + k, g[c], last[c], Q);
+        push_home(m1[c], i0 + k + 1, g[c], last[c], Q);
+      }
+    }
+    a = na;
+    b = nbr;
+    ba = nba;
+    bb = nbb;
+  }
+  return k < nb ? k : nb;
 }
 
 // Pair tests of one home cell with the binary64 Gram filter; homes in batches
-// of 64 (hq holds one batch), candidates in chunks of 64 lanes.
+// of 64 (hbeta holds one batch's beta), candidates in chunks of 64 lanes, three
+// chunks a pass (a cell of 13 has about 180 candidates).
 // vs, code: the cell's 20 starts and run codes (cell_starts), loaded ahead by
 // the caller; rt: the wave's room in LDS for the cell's run table (MAXRUN
 // entries).
 __device__ __forceinline__ void detect_cell64(const DetectArgs &A, const Grid &G, int vs,
-                                              int code, int cell, SurvivorQueue &Q, HomeQ *hq,
+                                              int code, SurvivorQueue &Q, double *hbeta,
                                               RunT *rt) {
   CellSet S;
   if (!cell_setup(G, vs, code, rt, S)) return;
-  const int h0 = S.h0, h1 = S.h1, nh = h1 - h0, total = S.total;
-  const int *pre = S.pre;
-  Q.tests += (unsigned long long)nh * (unsigned long long)(total - nh) +
+  const int h0 = S.h0, nh = S.h1 - S.h0;
+  Q.tests += (unsigned long long)nh * (unsigned long long)(S.total - nh) +
              (unsigned long long)nh * (unsigned long long)(nh - 1) / 2ull;
-  const int lane = __lane_id();
-  int cx, cy, cz;
-  cell_xyz(G, cell, cx, cy, cz);
-  const double ox = (cx + 0.5) * G.h[0], oy = (cy + 0.5) * G.h[1], oz = (cz + 0.5) * G.h[2];
-  const double dt2 = A.dt2;
   for (int hb = 0; hb < nh; hb += WAVE) {
     const int nb = nh - hb < WAVE ? nh - hb : WAVE;
-    if (lane < nb) {  // this batch's home terms (one wave owns hq: in-order LDS)
-      const Rec a = A.rec[h0 + hb + lane];
-      const double xh = a.x - ox, yh = a.y - oy, zh = a.z - oz;
-      HomeQ h;
-      h.q[0] = -2.0 * xh - dt2 * a.vx;
-      h.q[1] = -2.0 * yh - dt2 * a.vy;
-      h.q[2] = -2.0 * zh - dt2 * a.vz;
-      h.q[3] = -dt2 * xh;
-      h.q[4] = -dt2 * yh;
-      h.q[5] = -dt2 * zh;
-      h.q[6] = -2.0 * a.r;
-      h.alpha = ((xh * xh + yh * yh) + zh * zh) + dt2 * ((xh * a.vx + yh * a.vy) + zh * a.vz) -
-                a.r * a.r;
-      hq[lane] = h;
+    const int i0 = h0 + hb;
+    if ((int)__lane_id() < nb) {  // one wave owns hbeta: its LDS operations stay in order
+      const Rec a = A.rec[i0 + (int)__lane_id()];
+      hbeta[__lane_id()] = gram_beta(a.x, a.y, a.z, a.vx, a.vy, a.vz, a.r, A.dt2);
     }
-    for (int base = 0; base < total; base += WAVE) {
-      const int v = base + lane;
-      // the run of list slot v: the last run whose first slot is at most v.  The
-      // first slots are non-decreasing, so it is the number of runs after the
-      // first that start at or before v (an empty run starts where the next
-      // does, so it is never the one counted last for a slot inside the list)
-      int r = 0;
-#pragma unroll
-      for (int k = 1; k < MAXRUN; ++k) r += v >= pre[k] ? 1 : 0;
-      asm volatile("" : "+v"(r));  // the count apart from the table address
-      const RunT run = rt[r];
-      const int g = run.off + v;
-      const bool ok = v < total;
-      const bool own = (run.code >> 6) & 1;
-      const int thr = !ok ? -1 : (own ? g : 0x7fffffff);
-      double P[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      double beta = 1e300;  // no candidate: its threshold -1e300 is never met
-      if (thr >= 0) {
-        const Rec b = A.rec[g];
-        const double xj = (b.x + run.sx) - ox;
-        const double yj = (b.y + run.sy) - oy;
-        const double zj = (b.z + run.sz) - oz;
-        P[0] = xj;
-        P[1] = yj;
-        P[2] = zj;
-        P[3] = b.vx;
-        P[4] = b.vy;
-        P[5] = b.vz;
-        P[6] = b.r;
-        beta = ((xj * xj + yj * yj) + zj * zj) + dt2 * ((xj * b.vx + yj * b.vy) + zj * b.vz) -
-               b.r * b.r;
+    for (int base = 0, k = 0; base < S.total;) {
+      const int left = S.total - base;
+      int step = 3 * WAVE;
+      if (left > 2 * WAVE) {
+        k = detect_chunks<3>(A, S, base, i0, k, nb, hbeta, rt, Q);
+      } else if (left > WAVE) {
+        k = detect_chunks<2>(A, S, base, i0, k, nb, hbeta, rt, Q);
+      } else {
+        k = detect_chunks<1>(A, S, base, i0, k, nb, hbeta, rt, Q);
       }
-      // own-cell candidates (the first rl[0] of the list): only j after i
-      if (base < nh)
-        detect_chunk64<true>(A, G, hq, nb, h0 + hb, g, thr, P, A.tol64 - beta, Q);
-      else
-        detect_chunk64<false>(A, G, hq, nb, h0 + hb, g, thr, P, A.tol64 - beta, Q);
+      if (k < nb) {  // the queue is full (rare): decide it, then the rest of these homes
+        flush_survivors(A, G, Q);
+        step = 0;
+      } else {
+        k = 0;
+      }
+      base += step;
     }
   }
   // the survivors left in Q are the caller's to decide (flush_survivors), now
   // or after later cells of the same grid
 }
 
-template <bool FP32>
-__global__ __launch_bounds__(WAVE) void k_detect_half(DetectArgs A) {
+// The binary32 filter over A.cpw consecutive cells per workgroup (see
+// k_detect_half64).
+__global__ __launch_bounds__(WAVE) void k_detect_half32(DetectArgs A) {
   __shared__ int2 survq[QCAP];
   SurvivorQueue Q{survq, 0, 0u, QCAP, 0ull};
-  if (FP32) {  // A.cpw consecutive cells per workgroup (see k_detect_half64g)
-    __shared__ Rec32 hl[HB32];
-    __shared__ RunT rt[MAXRUN];
-    const int c0 = xcd_remap(blockIdx.x, gridDim.x) * A.cpw;
-    const int c1 = c0 + A.cpw < A.G.ncell ? c0 + A.cpw : A.G.ncell;
-    for (int cell = c0; cell < c1; ++cell) {
-      detect_cell32(A, A.G, A.start, cell, Q, hl, rt);
-      if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, A.G, Q);
-    }
-  } else {
-    __shared__ HomeQ hq[WAVE];
-    __shared__ RunT rt[MAXRUN];
-    const int cell = xcd_remap(blockIdx.x, gridDim.x);
-    int code;
-    const int vs = cell_starts(A.G, A.start, cell, code);
-    detect_cell64(A, A.G, vs, code, cell, Q, hq, rt);
-    flush_survivors(A, A.G, Q);
+  __shared__ Rec32 hl[HB32];
+  __shared__ RunT rt[MAXRUN];
+  const int c0 = xcd_remap(blockIdx.x, gridDim.x) * A.cpw;
+  const int c1 = c0 + A.cpw < A.G.ncell ? c0 + A.cpw : A.G.ncell;
+  for (int cell = c0; cell < c1; ++cell) {
+    detect_cell32(A, A.G, A.start, cell, Q, hl, rt);
+    if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, A.G, Q);
   }
-  // this cell's counts, summed by launch_cell_counts (a counter atomic per
+  // the workgroup's counts, summed by launch_cell_counts (a counter atomic per
   // wave would serialise over the million cells)
-  if (__lane_id() == 0) A.cellc[blockIdx.x] = CellCount{Q.tests, FP32 ? Q.pushed : 0ull};
+  if (__lane_id() == 0) A.cellc[blockIdx.x] = CellCount{Q.tests, Q.pushed};
 }
 
-// The binary64 filter over A.cpw consecutive cells per workgroup, for sparse
-// cells: the survivor queue carries over between them and is decided a wave at
-// a time (a cell of 13 spheres leaves about 13 survivors, so deciding them
-// per cell runs the rule's square root and division on a fifth of the lanes).
-// Register-limited to 5 waves per SIMD (96 registers, no spills).
-__global__ __launch_bounds__(WAVE, 5) void k_detect_half64g(DetectArgs A) {
-  __shared__ int2 survq[QCAP];
-  __shared__ HomeQ hq[WAVE];
+// The binary64 filter over A.cpw consecutive cells per workgroup: the survivor
+// queue carries over between them and is decided a wave at a time (a cell of
+// 13 spheres leaves about 13 survivors, so deciding them per cell runs the
+// rule's square root and division on a fifth of the lanes).
+__global__ __launch_bounds__(WAVE, 5) void k_detect_half64(DetectArgs A) {
+  __shared__ int2 survq[QCAP64];
+  __shared__ double hbeta[WAVE];
   __shared__ RunT rt[MAXRUN];
-  SurvivorQueue Q{survq, 0, 0u, QCAP, 0ull};
+  SurvivorQueue Q{survq, 0, 0u, QCAP64, 0ull};
   const int c0 = xcd_remap(blockIdx.x, gridDim.x) * A.cpw;
   const int c1 = c0 + A.cpw < A.G.ncell ? c0 + A.cpw : A.G.ncell;
   // the next cell's starts are loaded while this cell is tested
   int code = 0;
   int v = c0 < c1 ? cell_starts(A.G, A.start, c0, code) : 0;
-  for (int cell = c0; cell < c1; ++cell) {  // one flush site (register pressure)
+  for (int cell = c0; cell < c1; ++cell) {
     const int vc = v;
     const int cc = code;
     if (cell + 1 < c1) v = cell_starts(A.G, A.start, cell + 1, code);
-    detect_cell64(A, A.G, vc, cc, cell, Q, hq, rt);
+    detect_cell64(A, A.G, vc, cc, Q, hbeta, rt);
     if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, A.G, Q);
   }
   if (__lane_id() == 0) A.cellc[blockIdx.x] = CellCount{Q.tests, 0ull};
 }
 
-// Workgroups of launch_detect_half (one wave each): one per cell, but for the
-// persistent binary64 kernel a multiple of 8 (the XCDs) near the waves the
-// chip holds at once.  Also the number of per-workgroup counts it writes.
+// Workgroups of launch_detect_half (one wave each), each writing one CellCount.
 int detect_half_blocks(const DetectArgs &A) {
-  if (A.cpw <= 1) return A.G.ncell;
   return (A.G.ncell + A.cpw - 1) / A.cpw;
 }
 
@@ -1031,17 +1041,17 @@ __device__ __forceinline__ int box_of_cell(const int *cell_base, int nbox, int c
 
 // Batched form: the cells of all boxes are numbered consecutively, box after
 // box, and each workgroup (one wave) takes cpw consecutive global cells, as
-// k_detect_half64g does in one box: the box of each cell comes from the
+// k_detect_half64 does in one box: the box of each cell comes from the
 // first-cell table, the pair tests run with that box's grid, and the survivor
 // queue carries over the cells, decided with the grid of the box its survivors
 // came from whenever the next cell lies in another box, when it holds a wave's
 // worth, and at the end.
 __global__ __launch_bounds__(WAVE) void k_detect_batched(DetectArgs A, BatchDev B, int cpw) {
   if (B.flags[FLAG_ERR]) return;
-  __shared__ int2 survq[QCAP];
-  __shared__ HomeQ hq[WAVE];
+  __shared__ int2 survq[QCAP64];
+  __shared__ double hbeta[WAVE];
   __shared__ RunT rt[MAXRUN];
-  SurvivorQueue Q{survq, 0, 0u, QCAP, 0ull};
+  SurvivorQueue Q{survq, 0, 0u, QCAP64, 0ull};
   const int total = B.cell_base[B.nbox];
   const int c0 = xcd_remap(blockIdx.x, gridDim.x) * cpw;
   const int c1 = c0 + cpw < total ? c0 + cpw : total;
@@ -1058,7 +1068,7 @@ __global__ __launch_bounds__(WAVE) void k_detect_batched(DetectArgs A, BatchDev 
     const int base = B.cell_base[b];
     int code;
     const int vs = cell_starts(G, A.start + base, item - base, code);
-    detect_cell64(A, G, vs, code, item - base, Q, hq, rt);
+    detect_cell64(A, G, vs, code, Q, hbeta, rt);
     if (item + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
   }
 }
@@ -1088,11 +1098,9 @@ hipError_t launch_cell_counts(hipStream_t s, const CellCount *c, int n, SweepCou
 hipError_t launch_detect_half(hipStream_t s, const DetectArgs &A) {
   if (A.G.ncell <= 0) return hipSuccess;
   if (A.fp32)
-    hipLaunchKernelGGL(k_detect_half<true>, dim3(detect_half_blocks(A)), dim3(WAVE), 0, s, A);
-  else if (A.cpw > 1)
-    hipLaunchKernelGGL(k_detect_half64g, dim3(detect_half_blocks(A)), dim3(WAVE), 0, s, A);
+    hipLaunchKernelGGL(k_detect_half32, dim3(detect_half_blocks(A)), dim3(WAVE), 0, s, A);
   else
-    hipLaunchKernelGGL(k_detect_half<false>, dim3(A.G.ncell), dim3(WAVE), 0, s, A);
+    hipLaunchKernelGGL(k_detect_half64, dim3(detect_half_blocks(A)), dim3(WAVE), 0, s, A);
   return hipGetLastError();
 }
 
