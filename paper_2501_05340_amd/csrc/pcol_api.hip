@@ -44,10 +44,8 @@ struct pcol_ctx {
   int *key_j = nullptr;
   double *key_t = nullptr;
   uint8_t *status = nullptr;
-  int *ovf = nullptr;
+  int *ovf = nullptr;  // spheres with more contacts than slots, then the sweeps' second keys
   int *list_a = nullptr;  // spheres still to act after sweep 1
-  int *keep_cnt = nullptr, *keep_off = nullptr, *keep_bs = nullptr;  // its construction
-  int *nlist_h = nullptr;  // pinned read-back of its length
   OutRec *out = nullptr;
   int *partner_tmp = nullptr;
   double *tcoll_tmp = nullptr;
@@ -56,11 +54,9 @@ struct pcol_ctx {
   unsigned int *reach_phist = nullptr;  // REACH_BLOCKS partial extent histograms
   SweepCounters *ctr_d = nullptr;
   ReachOut *reach_h = nullptr;
-  SweepCounters *ctr_h = nullptr;
-  // sweeps 2 on run on the device in groups: FLAG_* words and totals (pairs,
-  // contacts, overflow) with their pinned read-back
-  unsigned int *sflags = nullptr, *sflags_h = nullptr;
-  unsigned long long *stotals = nullptr, *stotals_h = nullptr;
+  StepReport *rep = nullptr;  // page-locked host memory that the step's last kernel writes
+  int exact_sweeps = 0;       // some step's contacts overflowed the slots: sweeps that can search
+  int sweep_guess = 5;        // sweeps the last step took: so many are queued, and one more
   hipEvent_t ev[8] = {};
 
   bool binned = false;
@@ -124,10 +120,9 @@ struct BatchPlan {
   std::vector<int> chunk_box_h;
   std::vector<int64_t> chunk_lo_h;
   unsigned int *flags = nullptr;          // FLAG_* words
-  unsigned long long *totals = nullptr;   // pairs, contacts, overflow
   int cap_box = 0;
   int64_t cap_n = 0;
-  unsigned int *flags_h = nullptr;        // pinned: 4 flags + padding, then 3 totals
+  unsigned int *flags_h = nullptr;        // pinned read-back of the flags
   std::vector<double> breach_h;
   std::vector<Grid> gtab_h;
   std::vector<int> cell_base_h;
@@ -142,6 +137,7 @@ struct BatchPlan {
   hipStream_t gstream = nullptr;
   hipGraphExec_t exec = nullptr;
   bool captured = false;
+  int cap_exact = 0;  // its sweeps can search
   const void *cap_ptr[8] = {};
   const void *cap_part = nullptr, *cap_tc = nullptr;
   double cap_dt = 0.0, cap_e = 0.0;
@@ -378,24 +374,20 @@ void pcol_destroy(pcol_ctx *ctx) {
   void *dev[] = {ctx->rec,    ctx->rank,   ctx->cid,         ctx->slot,
                  ctx->count,  ctx->start,  ctx->blocksum, ctx->cnt,      ctx->slot_t,
                  ctx->slot_j, ctx->key_j,  ctx->key_t,  ctx->status,      ctx->out,
-                 ctx->ovf,    ctx->partner_tmp, ctx->tcoll_tmp, ctx->list_a, ctx->keep_cnt, ctx->keep_off, ctx->keep_bs,
-                 ctx->reach_d, ctx->cellc, ctx->ctr_d, ctx->sflags, ctx->stotals, ctx->dep_buf,
+                 ctx->ovf,    ctx->partner_tmp, ctx->tcoll_tmp, ctx->list_a,
+                 ctx->reach_d, ctx->cellc, ctx->ctr_d, ctx->dep_buf,
                  ctx->crank, ctx->reach_parts, ctx->reach_phist};
   for (void *p : dev)
     if (p) (void)hipFree(p);
   if (ctx->reach_h) (void)hipHostFree(ctx->reach_h);
-  if (ctx->ctr_h) (void)hipHostFree(ctx->ctr_h);
+  if (ctx->rep) (void)hipHostFree(ctx->rep);
   if (ctx->wide_h) (void)hipHostFree(ctx->wide_h);
-  if (ctx->sflags_h) (void)hipHostFree(ctx->sflags_h);
-  if (ctx->stotals_h) (void)hipHostFree(ctx->stotals_h);
-  if (ctx->nlist_h) (void)hipHostFree(ctx->nlist_h);
   if (ctx->dep_flag_h) (void)hipHostFree(ctx->dep_flag_h);
   for (hipEvent_t &e : ctx->ev)
     if (e) (void)hipEventDestroy(e);
   if (BatchPlan *bp = ctx->bp) {
     void *bd[] = {bp->gtab,    bp->cell_base, bp->box_of, bp->box_off_d, bp->breach,
-                  bp->chunk_box, bp->chunk_lo, bp->bmax,  bp->flags,     bp->totals,
-                  bp->tune_buf};
+                  bp->chunk_box, bp->chunk_lo, bp->bmax,  bp->flags,     bp->tune_buf};
     for (void *q : bd)
       if (q) (void)hipFree(q);
     if (bp->flags_h) (void)hipHostFree(bp->flags_h);
@@ -432,9 +424,10 @@ pcol_status pcol_create(pcol_ctx **out, int64_t n_max, void *hip_stream, const p
   auto A = [&](hipError_t r) {
     if (e == hipSuccess && r != hipSuccess) e = r;
   };
+  const size_t lists = n + (size_t)(NSHARD + 1) * 256;  // every shard has whole workgroups
   A(dalloc(&ctx->rec, n));
   A(dalloc(&ctx->rank, n));
-  A(dalloc(&ctx->cid, n));
+  A(dalloc(&ctx->cid, lists));
   A(dalloc(&ctx->slot, n));
   A(dalloc(&ctx->cnt, n));
   A(dalloc(&ctx->slot_t, n * (size_t)ctx->K));
@@ -444,10 +437,7 @@ pcol_status pcol_create(pcol_ctx **out, int64_t n_max, void *hip_stream, const p
   A(dalloc(&ctx->status, n));
   A(dalloc(&ctx->out, n));
   A(dalloc(&ctx->ovf, n));
-  A(dalloc(&ctx->list_a, n));
-  A(dalloc(&ctx->keep_cnt, n / 256 + 2));
-  A(dalloc(&ctx->keep_off, n / 256 + 3));
-  A(dalloc(&ctx->keep_bs, n / 256 / 4096 + 2));
+  A(dalloc(&ctx->list_a, lists));
   A(dalloc(&ctx->partner_tmp, n));
   A(dalloc(&ctx->tcoll_tmp, n));
   if (ctx->opts.order == 1) A(dalloc(&ctx->crank, n));
@@ -455,14 +445,9 @@ pcol_status pcol_create(pcol_ctx **out, int64_t n_max, void *hip_stream, const p
   A(dalloc(&ctx->reach_parts, REACH_BLOCKS));
   A(dalloc(&ctx->reach_phist, (int64_t)REACH_BLOCKS * RHO_BINS));
   A(dalloc(&ctx->ctr_d, 1));
-  A(dalloc(&ctx->sflags, 16));
-  A(dalloc(&ctx->stotals, 4));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->sflags_h, 16 * sizeof(unsigned int));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->stotals_h, 4 * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->reach_h, sizeof(ReachOut));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->ctr_h, sizeof(SweepCounters));
+  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->rep, sizeof(StepReport));
   if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->wide_h, 2 * sizeof(int));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->nlist_h, sizeof(int));
   for (hipEvent_t &ev : ctx->ev)
     if (e == hipSuccess) e = hipEventCreate(&ev);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -814,27 +799,18 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     if (ctx->split) PCOL_HIP(launch_detect_wide(s, A, ctx->start + ctx->G.layer2, n));
     if (ctx->opts.timing) PCOL_HIP(hipEventRecord(ctx->ev[6], s));
     ctx->detect_timed = true;
-    PCOL_HIP(launch_slot_min(s, n, 1, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->status,
-                             ctx->rec, ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d,
-                             nullptr, nullptr, 0, &ctx->G, crank));
-    PCOL_HIP(launch_gather_exact(s, ctx->ovf, 0, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
-                                 ctx->G, dt, ctx->status, ctx->key_j, ctx->key_t, nullptr, crank));
+    PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
+                             ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, nullptr, &ctx->G,
+                             crank));
+    PCOL_HIP(launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
+                                 ctx->G, dt, nullptr, ctx->key_j, ctx->key_t, nullptr, crank));
   } else {
     // fewer than 3 cells on some axis: exact search for every sphere
     ctx->cpw_used = 0;
     PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, -1, ctx->rec, ctx->start, ctx->G, dt,
-                                 ctx->status, ctx->key_j, ctx->key_t, nullptr, crank));
+                                 nullptr, ctx->key_j, ctx->key_t, nullptr, crank));
   }
   return PCOL_OK;
-}
-
-static void sum_counters(const SweepCounters &c, unsigned long long &pairs,
-                         unsigned long long &contacts) {
-  pairs = contacts = 0ull;
-  for (int k = 0; k < NSHARD; ++k) {
-    pairs += c.shard[k].pairs;
-    contacts += c.shard[k].contacts;
-  }
 }
 
 pcol_status pcol_detect(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box, double dt,
@@ -848,7 +824,6 @@ pcol_status pcol_detect(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *
   if (n == 0) return PCOL_OK;
   PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
   if (!active) {
-    PCOL_HIP(launch_fill_u8(s, ctx->status, ST_ACTIVE, n));
     if ((st = detect_all(ctx, dt, nullptr)) != PCOL_OK) return st;
   } else {
     PCOL_HIP(launch_status_from_active(s, active, ctx->rec, n, ctx->status));
@@ -856,8 +831,8 @@ pcol_status pcol_detect(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *
     PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, ST_ACTIVE, ctx->rec, ctx->start, ctx->G,
                                  dt, ctx->status, ctx->key_j, ctx->key_t, nullptr));
   }
-  PCOL_HIP(launch_export_keys(s, n, ctx->rec, ctx->key_j, ctx->key_t, ctx->status, key_out,
-                              tmin_out));
+  PCOL_HIP(launch_export_keys(s, n, ctx->rec, ctx->key_j, ctx->key_t,
+                              active ? ctx->status : nullptr, key_out, tmin_out));
   return PCOL_OK;
 }
 
@@ -885,6 +860,56 @@ pcol_status pcol_advance(pcol_ctx *ctx, pcol_particles *p, const pcol_box *box, 
 
 }  // extern "C"
 
+// What the sweeps of a step need from the context.
+static SweepArgs sweep_args(const pcol_ctx *ctx, const Particles &P, double dt, double e) {
+  SweepArgs W{};
+  W.n = (int)P.n;
+  W.K = ctx->K;
+  W.small = ctx->small;
+  W.exact = ctx->small || ctx->exact_sweeps;
+  W.rec = ctx->rec;
+  W.start = ctx->start;
+  W.G = ctx->G;
+  W.dt = dt;
+  W.e = e;
+  W.mass = P.m;
+  W.cnt = ctx->cnt;
+  W.slot_j = ctx->slot_j;
+  W.slot_t = ctx->slot_t;
+  W.key_t = ctx->key_t;
+  W.status = ctx->status;
+  W.out = ctx->out;
+  W.list[0] = ctx->list_a;
+  W.list[1] = ctx->cid;  // the cell numbers are done with once the spheres are sorted
+  W.ctr = ctx->ctr_d;
+  sweep_shards(W);
+  return W;
+}
+
+// Queue the sweeps before place `end` of the counters on s.  first: from the
+// first sweep on (place 0), keys in ctx->key_j, and the list is made; else more
+// of them, from place 1.  The keys alternate between ctx->key_j and ctx->ovf; W
+// counts the turns from one group to the next.
+static hipError_t queue_sweeps(pcol_ctx *ctx, SweepArgs &W, hipStream_t s, int end, bool first) {
+  hipError_t e = hipSuccess;
+  if (first) {
+    if ((e = launch_sweep_first(s, W, ctx->key_j)) != hipSuccess) return e;
+    W.turn = 0;
+    // a first group of one: the next one starts with the rekey
+    W.rekeyed = end > 1;
+    if (end > 1 && (e = launch_rekey(s, W, ctx->key_j)) != hipSuccess) return e;
+  } else if (!W.rekeyed) {
+    if ((e = launch_rekey(s, W, ctx->key_j)) != hipSuccess) return e;
+    W.rekeyed = 1;
+  }
+  for (int k = 1; k < end; ++k) {
+    int *in = W.turn & 1 ? ctx->ovf : ctx->key_j, *out = W.turn & 1 ? ctx->key_j : ctx->ovf;
+    if ((e = launch_sweep(s, W, in, out, k, k == 1, W.turn)) != hipSuccess) return e;
+    ++W.turn;
+  }
+  return e;
+}
+
 // The whole step of pcol_step and pcol_step_spin (spin: nullptr for none).
 static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *box, double dt,
                              double e, int32_t *partner, double *tcoll, pcol_stats *stats,
@@ -909,133 +934,54 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
   unsigned long long contacts = 0ull, recheck = 0ull, tests = 0ull;
   double ms_detect = 0.0;
   if (n > 0) {
-    PCOL_HIP(launch_fill_u8(s, ctx->status, ST_ACTIVE, n));
     PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
     // sweep 1: every contact within dt, then the earliest partner of each sphere
     ctx->detect_timed = false;
     if ((st = detect_all(ctx, dt, crank)) != PCOL_OK) return st;
     if (timing) PCOL_HIP(hipEventRecord(ctx->ev[2], s));
-    // sweep 1 over every sphere; later sweeps over the list of the spheres it
-    // left ACTIVE or DIRTY (the others are done for the step; entries that
-    // finish later are skipped by their status)
-    PCOL_HIP(launch_resolve_sweep(s, n, ctx->rec, ctx->G, dt, e, P.m, ctx->key_j, ctx->key_t,
-                                  ctx->status, ctx->out, ctx->ctr_d, nullptr,
-                                  nullptr, 0, spin));
-    PCOL_HIP(launch_keep_list(s, ctx->status, n, ctx->keep_cnt, ctx->keep_off, ctx->keep_bs,
-                              ctx->reach_d, ctx->list_a));
-    PCOL_HIP(hipMemcpyAsync(ctx->nlist_h, ctx->keep_off + (n + 255) / 256, sizeof(int),
-                            hipMemcpyDeviceToHost, s));
-    PCOL_HIP(hipMemcpyAsync(ctx->ctr_h, ctx->ctr_d, sizeof(SweepCounters), hipMemcpyDeviceToHost,
-                            s));
-    PCOL_HIP(hipStreamSynchronize(s));
+    SweepArgs W = sweep_args(ctx, P, dt, e);
+    W.crank = crank;
+    if (spin) W.spin = *spin;
+    // All the sweeps that the step is likely to take, and the free flight behind
+    // them, are queued at once: a sweep runs if the one before it resolved a pair,
+    // the free flight if the last one resolved none.  Steps that need more are
+    // continued below, one wait for each group.
+    const int cap = ctx->opts.max_sweeps;
+    int group = ctx->sweep_guess + 1;
+    if (group < 4) group = 4;
+    bool first = true;
+    for (;;) {
+      if (group > MAX_QUEUE - 1) group = MAX_QUEUE - 1;
+      if (cap > 0 && group > cap - (int)sweeps) group = cap - (int)sweeps;
+      if (!first) PCOL_HIP(hipMemsetAsync(ctx->ctr_d->pairs, 0, sizeof(ctx->ctr_d->pairs), s));
+      const int begin = first ? 0 : 1, end = begin + group;
+      PCOL_HIP(queue_sweeps(ctx, W, s, end, first));
+      if (timing) PCOL_HIP(hipEventRecord(ctx->ev[3], s));
+      PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G, nullptr,
+                             ctx->ctr_d, end, W.exact != 0, ctx->rep));
+      PCOL_HIP(hipStreamSynchronize(s));
+      if (!W.exact && ctx->rep->n_overflow) {  // nothing ran: again, with the exact search
+        W.exact = ctx->exact_sweeps = 1;
+        continue;
+      }
+      bool done = false;
+      for (int k = begin; k < end && !done; ++k) {
+        ++sweeps;
+        pairs += (int64_t)ctx->rep->pairs[k];
+        done = ctx->rep->pairs[k] == 0ull;
+      }
+      if (done) break;
+      if (cap > 0 && sweeps >= cap)
+        return fail(ctx, PCOL_E_SWEEPS, "sweep cap reached with pairs still resolving");
+      group = first ? 4 : 2 * group;
+      first = false;
+    }
+    ctx->sweep_guess = (int)std::min(sweeps, (int64_t)MAX_QUEUE);
     bin_readback(ctx);
-    {
-      unsigned long long sp, sc;
-      sum_counters(*ctx->ctr_h, sp, sc);
-      contacts = sc / 2ull;
-      for (int k = 0; k < NSHARD; ++k) {
-        recheck += ctx->ctr_h->shard[k].recheck;
-        tests += ctx->ctr_h->shard[k].tests;
-      }
-      ovf_total = ctx->ctr_h->n_overflow;
-      sweeps = 1;
-      pairs = (int64_t)sp;
-    }
-    const int *lin = ctx->list_a;
-    const int nlist = *ctx->nlist_h;
-    // Later sweeps over a long list run on the device in groups without a host
-    // round trip per sweep: each ends with k_sweep_check, which totals its pairs
-    // and, at zero, raises FLAG_DONE, turning every later kernel into an early
-    // exit.  The group's last check raises FLAG_UNFINISHED if that sweep still
-    // paired, so the free flight queued behind the group only runs once the step
-    // is done.  A short list (small boxes, where launches cost more than the
-    // kernels) takes one sweep per round trip, with no launches to spare.
-    BatchDev Bf{};
-    Bf.flags = ctx->sflags;
-    const bool more = pairs > 0;
-    const bool groups = nlist >= (1 << 16);
-    if (more && ctx->opts.max_sweeps == 1)
-      return fail(ctx, PCOL_E_SWEEPS, "sweep cap reached with pairs still resolving");
-    while (more && !groups) {
-      PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
-      if (!ctx->small) {
-        PCOL_HIP(launch_slot_min(s, n, 0, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K,
-                                 ctx->status, ctx->rec, ctx->key_j, ctx->key_t, ctx->ovf,
-                                 ctx->ctr_d, nullptr, lin, nlist, &ctx->G, crank));
-        PCOL_HIP(launch_gather_exact(s, ctx->ovf, 0, &ctx->ctr_d->n_overflow, -1, ctx->rec,
-                                     ctx->start, ctx->G, dt, ctx->status, ctx->key_j,
-                                     ctx->key_t, nullptr, crank));
-      } else {
-        PCOL_HIP(launch_gather_exact(s, lin, nlist, nullptr, ST_DIRTY, ctx->rec, ctx->start,
-                                     ctx->G, dt, ctx->status, ctx->key_j, ctx->key_t, nullptr,
-                                     crank));
-      }
-      PCOL_HIP(launch_resolve_sweep(s, n, ctx->rec, ctx->G, dt, e, P.m, ctx->key_j, ctx->key_t,
-                                    ctx->status, ctx->out, ctx->ctr_d, nullptr,
-                                    lin, nlist, spin));
-      PCOL_HIP(hipMemcpyAsync(ctx->ctr_h, ctx->ctr_d, sizeof(SweepCounters),
-                              hipMemcpyDeviceToHost, s));
-      PCOL_HIP(hipStreamSynchronize(s));
-      unsigned long long sp, sc;
-      sum_counters(*ctx->ctr_h, sp, sc);
-      ovf_total += ctx->ctr_h->n_overflow;
-      ++sweeps;
-      pairs += (int64_t)sp;
-      if (sp == 0ull) break;
-      if (ctx->opts.max_sweeps > 0 && sweeps >= ctx->opts.max_sweeps)
-        return fail(ctx, PCOL_E_SWEEPS, "sweep cap reached with pairs still resolving");
-    }
-    if (more && groups) {
-      PCOL_HIP(launch_fill_u32(s, ctx->sflags, 0u, 16));
-      PCOL_HIP(launch_fill_u32(s, (unsigned int *)ctx->stotals, 0u, 8));
-      PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
-    }
-    for (int group = 0; more && groups; ++group) {
-      int S = group == 0 ? 5 : 2;  // a step takes about six sweeps at 16M
-      if (ctx->opts.max_sweeps > 0 && S > ctx->opts.max_sweeps - (int)sweeps)
-        S = ctx->opts.max_sweeps - (int)sweeps;
-      for (int k = 0; k < S; ++k) {
-        // new partners for DIRTY spheres (partner collided elsewhere), then the resolve
-        if (!ctx->small) {
-          PCOL_HIP(launch_slot_min(s, n, 0, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K,
-                                   ctx->status, ctx->rec, ctx->key_j, ctx->key_t, ctx->ovf,
-                                   ctx->ctr_d, ctx->sflags, lin, nlist, &ctx->G, crank));
-          PCOL_HIP(launch_gather_exact(s, ctx->ovf, 0, &ctx->ctr_d->n_overflow, -1, ctx->rec,
-                                       ctx->start, ctx->G, dt, ctx->status, ctx->key_j,
-                                       ctx->key_t, &Bf, crank));
-        } else {
-          PCOL_HIP(launch_gather_exact(s, lin, nlist, nullptr, ST_DIRTY, ctx->rec, ctx->start,
-                                       ctx->G, dt, ctx->status, ctx->key_j, ctx->key_t, &Bf,
-                                       crank));
-        }
-        PCOL_HIP(launch_resolve_sweep(s, n, ctx->rec, ctx->G, dt, e, P.m, ctx->key_j,
-                                      ctx->key_t, ctx->status, ctx->out, ctx->ctr_d, &Bf,
-                                      lin, nlist, spin));
-        PCOL_HIP(launch_sweep_check(s, ctx->ctr_d, ctx->sflags, ctx->stotals, k == S - 1));
-      }
-      if (timing) PCOL_HIP(hipEventRecord(ctx->ev[3], s));
-      PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G,
-                             &Bf));
-      PCOL_HIP(hipMemcpyAsync(ctx->sflags_h, ctx->sflags, 4 * sizeof(unsigned int),
-                              hipMemcpyDeviceToHost, s));
-      PCOL_HIP(hipMemcpyAsync(ctx->stotals_h, ctx->stotals, 3 * sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, s));
-      PCOL_HIP(hipStreamSynchronize(s));
-      if (ctx->sflags_h[FLAG_DONE]) break;
-      if (ctx->opts.max_sweeps > 0 && 1 + (int)ctx->sflags_h[FLAG_SWEEPS] >= ctx->opts.max_sweeps)
-        return fail(ctx, PCOL_E_SWEEPS, "sweep cap reached with pairs still resolving");
-      sweeps = 1 + ctx->sflags_h[FLAG_SWEEPS];
-      PCOL_HIP(launch_fill_u32(s, ctx->sflags + FLAG_UNFINISHED, 0u, 1));
-    }
-    if (more && groups) {
-      sweeps = 1 + ctx->sflags_h[FLAG_SWEEPS];
-      pairs += (int64_t)ctx->stotals_h[0];
-      ovf_total += (int64_t)ctx->stotals_h[2];
-    } else {
-      if (timing) PCOL_HIP(hipEventRecord(ctx->ev[3], s));
-      PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G,
-                             nullptr));
-    }
+    contacts = ctx->rep->contacts / 2ull;
+    recheck = ctx->rep->recheck;
+    tests = ctx->rep->tests;
+    ovf_total = ctx->rep->n_overflow;
     if (timing) {
       PCOL_HIP(hipEventRecord(ctx->ev[4], s));
       PCOL_HIP(hipEventSynchronize(ctx->ev[4]));
@@ -1255,21 +1201,12 @@ hipError_t regrow(T **p, int64_t want) {
   return hipMalloc((void **)p, (size_t)(want > 0 ? want : 1) * sizeof(T));
 }
 
-// read back the flags and totals of the last batched run
+// read back the flags of the last batched run (its report is there with them)
 hipError_t batch_readback(pcol_ctx *ctx, BatchPlan *bp) {
-  hipError_t e = hipMemcpyAsync(bp->flags_h, bp->flags, 16 * sizeof(unsigned int),
+  hipError_t e = hipMemcpyAsync(bp->flags_h, bp->flags, 4 * sizeof(unsigned int),
                                 hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(bp->flags_h + 16, bp->totals, 3 * sizeof(unsigned long long),
-                       hipMemcpyDeviceToHost, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   return e;
-}
-
-unsigned long long batch_total(const BatchPlan *bp, int k) {
-  unsigned long long v;
-  memcpy(&v, (const char *)(bp->flags_h + 16) + 8 * k, 8);
-  return v;
 }
 
 }  // namespace
@@ -1321,8 +1258,7 @@ static pcol_status batch_plan(pcol_ctx *ctx, int nbox, const int64_t *box_off,
   }
   if (!bp->flags) {
     if (hipMalloc((void **)&bp->flags, 16 * sizeof(unsigned int)) != hipSuccess ||
-        hipMalloc((void **)&bp->totals, 4 * sizeof(unsigned long long)) != hipSuccess ||
-        hipHostMalloc((void **)&bp->flags_h, 16 * sizeof(unsigned int) + 4 * 8) != hipSuccess)
+        hipHostMalloc((void **)&bp->flags_h, 16 * sizeof(unsigned int)) != hipSuccess)
       return fail(ctx, PCOL_E_NOMEM, "batched flags");
   }
   bp->nbox = nbox;
@@ -1383,6 +1319,16 @@ static pcol_status batch_plan(pcol_ctx *ctx, int nbox, const int64_t *box_off,
   return PCOL_OK;
 }
 
+static SweepArgs batch_sweep_args(const pcol_ctx *ctx, const Particles &P, double dt, double e) {
+  SweepArgs W = sweep_args(ctx, P, dt, e);
+  W.small = 0;
+  W.exact = ctx->exact_sweeps;
+  W.G = Grid{};  // periodic boxes; each sphere's grid is its box's
+  W.B = batch_dev(ctx->bp);
+  W.err = ctx->bp->flags + FLAG_ERR;
+  return W;
+}
+
 // Enqueue the whole batched step on stream s (captured into a graph).
 static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &P, int32_t *part,
                                  double *tc, double dt, double e, int kmax, int cpw) {
@@ -1391,7 +1337,6 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   const int n = (int)P.n;
   const int ncell = bp->total_cells;
   PCOL_HIP(launch_fill_u32(s, bp->flags, 0u, 16));
-  PCOL_HIP(launch_fill_u32(s, (unsigned int *)bp->totals, 0u, 8));
   PCOL_HIP(launch_fill_u32(s, (unsigned int *)ctx->ctr_d, 0u, sizeof(SweepCounters) / 4));
   // reach check and cell ids in one pass over the spheres (the counts are
   // discarded with everything else if the check fails)
@@ -1399,7 +1344,6 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   PCOL_HIP(launch_breach(s, P, B, dt, 1, ctx->cid, ctx->slot, ctx->count));
   PCOL_HIP(launch_scan(s, ctx->count, ncell, ctx->start, ctx->blocksum, ctx->reach_d));
   PCOL_HIP(launch_scatter(s, P, ctx->cid, ctx->slot, ctx->start, ctx->rec, ctx->rank, &B));
-  PCOL_HIP(launch_fill_u8(s, ctx->status, ST_ACTIVE, n));
   PCOL_HIP(launch_fill_i32(s, ctx->cnt, 0, n));
   DetectArgs A{};
   A.rec = ctx->rec;
@@ -1431,22 +1375,14 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   A.K = ctx->K;
   A.fp32 = 0;
   PCOL_HIP(launch_detect_batched(s, A, B, bp->total_cells, cpw));
-  PCOL_HIP(launch_slot_min(s, n, 1, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->status,
-                           ctx->rec, ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, bp->flags));
-  PCOL_HIP(launch_gather_exact(s, ctx->ovf, 0, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
-                               ctx->G, dt, ctx->status, ctx->key_j, ctx->key_t, &B));
-  for (int k = 0; k < kmax; ++k) {
-    PCOL_HIP(launch_resolve_sweep(s, n, ctx->rec, ctx->G, dt, e, P.m, ctx->key_j, ctx->key_t,
-                                  ctx->status, ctx->out, ctx->ctr_d, &B));
-    PCOL_HIP(launch_sweep_check(s, ctx->ctr_d, bp->flags, bp->totals, k == kmax - 1));
-    PCOL_HIP(launch_slot_min(s, n, 0, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->status,
-                             ctx->rec, ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, bp->flags));
-    PCOL_HIP(launch_gather_exact(s, ctx->ovf, 0, &ctx->ctr_d->n_overflow, -1, ctx->rec,
-                                 ctx->start, ctx->G, dt, ctx->status, ctx->key_j,
-                                 ctx->key_t, &B));
-  }
-  PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G,
-                         &B));
+  PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec, ctx->key_j,
+                           ctx->key_t, ctx->ovf, ctx->ctr_d, bp->flags + FLAG_ERR));
+  PCOL_HIP(launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
+                               ctx->G, dt, nullptr, ctx->key_j, ctx->key_t, &B));
+  SweepArgs W = batch_sweep_args(ctx, P, dt, e);
+  PCOL_HIP(queue_sweeps(ctx, W, s, kmax, true));
+  PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G, &B,
+                         ctx->ctr_d, kmax, W.exact != 0, ctx->rep));
   return PCOL_OK;
 }
 
@@ -1469,36 +1405,28 @@ static pcol_status batch_capture(pcol_ctx *ctx, const Particles &P, int32_t *par
   return PCOL_OK;
 }
 
-// Finish a step whose captured sweeps ran out: remaining sweeps on the host
-// loop, then free flight and the copy back (the graph skipped both).
+// Continue a step whose captured sweeps ran out (the graph then skipped the free
+// flight and the copy back): more sweeps, a wait for each group.
 static pcol_status batch_finish(pcol_ctx *ctx, const Particles &P, int32_t *part, double *tc,
                                 double dt, double e, int64_t &pairs, int64_t &sweeps) {
   BatchPlan *bp = ctx->bp;
   const BatchDev B = batch_dev(bp);
   hipStream_t s = ctx->stream;
-  const int n = (int)P.n;
-  for (;;) {
-    PCOL_HIP(launch_fill_u32(s, (unsigned int *)ctx->ctr_d, 0u, sizeof(SweepCounters) / 4));
-    PCOL_HIP(launch_resolve_sweep(s, n, ctx->rec, ctx->G, dt, e, P.m, ctx->key_j, ctx->key_t,
-                                  ctx->status, ctx->out, ctx->ctr_d, &B));
-    PCOL_HIP(hipMemcpyAsync(ctx->ctr_h, ctx->ctr_d, sizeof(SweepCounters), hipMemcpyDeviceToHost, s));
+  SweepArgs W = batch_sweep_args(ctx, P, dt, e);
+  W.rekeyed = bp->kmax > 1;
+  W.turn = bp->kmax - 1;
+  for (int end = 5;; end = std::min(2 * end, MAX_QUEUE)) {
+    PCOL_HIP(hipMemsetAsync(ctx->ctr_d->pairs, 0, sizeof(ctx->ctr_d->pairs), s));
+    PCOL_HIP(queue_sweeps(ctx, W, s, end, false));
+    PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G, &B,
+                           ctx->ctr_d, end, W.exact != 0, ctx->rep));
     PCOL_HIP(hipStreamSynchronize(s));
-    unsigned long long sp, sc;
-    sum_counters(*ctx->ctr_h, sp, sc);
-    ++sweeps;
-    pairs += (int64_t)sp;
-    if (sp == 0ull) break;
-    PCOL_HIP(launch_fill_u32(s, (unsigned int *)ctx->ctr_d, 0u, sizeof(SweepCounters) / 4));
-    PCOL_HIP(launch_slot_min(s, n, 0, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->status,
-                             ctx->rec, ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, bp->flags));
-    PCOL_HIP(launch_gather_exact(s, ctx->ovf, 0, &ctx->ctr_d->n_overflow, -1, ctx->rec,
-                                 ctx->start, ctx->G, dt, ctx->status, ctx->key_j,
-                                 ctx->key_t, &B));
+    for (int k = 1; k < end; ++k) {
+      ++sweeps;
+      pairs += (int64_t)ctx->rep->pairs[k];
+      if (ctx->rep->pairs[k] == 0ull) return PCOL_OK;
+    }
   }
-  PCOL_HIP(launch_fill_u32(s, bp->flags + FLAG_UNFINISHED, 0u, 1));
-  PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G,
-                         &B));
-  return PCOL_OK;
 }
 
 static std::string tune_key(int nbox, int64_t n, const int64_t *box_off, const pcol_box *boxes,
@@ -1634,7 +1562,7 @@ extern "C" pcol_status pcol_step_batched(pcol_ctx *ctx, int32_t nbox, const int6
   if (!ctx->bp) {
     ctx->bp = new (std::nothrow) BatchPlan();
     if (!ctx->bp) return PCOL_E_NOMEM;
-    if (ctx->opts.max_sweeps > 0) ctx->bp->kmax = ctx->opts.max_sweeps;
+    if (ctx->opts.max_sweeps > 0) ctx->bp->kmax = std::min(ctx->opts.max_sweeps, MAX_QUEUE);
   }
   BatchPlan *bp = ctx->bp;
   const Particles P = to_dev(p);
@@ -1681,6 +1609,7 @@ extern "C" pcol_status pcol_step_batched(pcol_ctx *ctx, int32_t nbox, const int6
       if ((st = batch_capture(ctx, P, part, tc, dt, e, bp->kmax, bp->cpw, &bp->exec)) != PCOL_OK)
         return st;
       bp->captured = true;
+      bp->cap_exact = ctx->exact_sweeps;
       bp->cap_dt = dt;
       bp->cap_e = e;
       bp->cap_part = part;
@@ -1700,20 +1629,35 @@ extern "C" pcol_status pcol_step_batched(pcol_ctx *ctx, int32_t nbox, const int6
     }
     break;
   }
-  int64_t pairs = (int64_t)batch_total(bp, 0);
-  int64_t sweeps = bp->flags_h[FLAG_SWEEPS];
-  if (bp->flags_h[FLAG_UNFINISHED]) {
-    if ((st = batch_finish(ctx, P, part, tc, dt, e, pairs, sweeps)) != PCOL_OK) return st;
+  if (!bp->cap_exact && ctx->rep->n_overflow) {
+    // no sweep ran: queue them here with the exact search, and capture it next time
+    ctx->exact_sweeps = 1;
+    bp->captured = false;
+    SweepArgs W = batch_sweep_args(ctx, P, dt, e);
+    const BatchDev B = batch_dev(bp);
+    PCOL_HIP(queue_sweeps(ctx, W, ctx->stream, bp->kmax, true));
+    PCOL_HIP(launch_finish(ctx->stream, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G,
+                           &B, ctx->ctr_d, bp->kmax, true, ctx->rep));
     PCOL_HIP(hipStreamSynchronize(ctx->stream));
+  }
+  int64_t pairs = 0, sweeps = 0;
+  bool done = false;
+  for (int k = 0; k < bp->kmax && !done; ++k) {
+    ++sweeps;
+    pairs += (int64_t)ctx->rep->pairs[k];
+    done = ctx->rep->pairs[k] == 0ull;
+  }
+  if (!done) {
+    if ((st = batch_finish(ctx, P, part, tc, dt, e, pairs, sweeps)) != PCOL_OK) return st;
     host_finish = 1;
     if (ctx->opts.max_sweeps == 0) {  // capture enough sweeps next time
-      bp->kmax = (int)sweeps + 4;
+      bp->kmax = (int)std::min(sweeps + 4, (int64_t)MAX_QUEUE);
       bp->captured = false;
     }
   } else if (ctx->opts.max_sweeps == 0 && bp->kmax > (int)sweeps + 4) {
     // far more sweep slots than the step used: each empty slot still launches
-    // its kernels (early exits, about 25 us a slot), so capture fewer next time,
-    // keeping room for two more sweeps than this step took
+    // its kernel (an early exit), so capture fewer next time, keeping room for
+    // two more sweeps than this step took
     bp->kmax = (int)sweeps + 2;
     bp->captured = false;
   }
@@ -1721,8 +1665,8 @@ extern "C" pcol_status pcol_step_batched(pcol_ctx *ctx, int32_t nbox, const int6
     memset(stats, 0, sizeof(*stats));
     stats->n_pairs = pairs;
     stats->n_sweeps = sweeps;
-    stats->contacts = (int64_t)(batch_total(bp, 1) / 2ull);
-    stats->n_overflow = (int64_t)batch_total(bp, 2);
+    stats->contacts = (int64_t)(ctx->rep->contacts / 2ull);
+    stats->n_overflow = (int64_t)ctx->rep->n_overflow;
     stats->total_cells = bp->total_cells;
     stats->replanned = replanned;
     stats->finished_on_host = host_finish;

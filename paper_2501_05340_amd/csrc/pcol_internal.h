@@ -125,21 +125,37 @@ struct CurveGrid {
   double h[3];
 };
 
-// Per-sweep counters the host reads back.  Sums are spread over NSHARD
-// counters on separate 128-B lines (one atomic per workgroup on shard
-// blockIdx % NSHARD), so no single address takes an atomic per wave.
+// Counters of a step, zero at its start.  Sums are spread over NSHARD counters on
+// separate 128-B lines (one atomic per workgroup on shard blockIdx % NSHARD), so
+// no single address takes an atomic per wave; the pairs of a sweep over four.
 constexpr int NSHARD = 64;
+constexpr int PAIR_SHARDS = 4;
+constexpr int MAX_QUEUE = 256;  // sweeps queued without the host looking at them
 struct alignas(128) CounterShard {
-  unsigned long long pairs;     // pairs resolved this sweep
   unsigned long long contacts;  // contacts found (each counted from both spheres)
   unsigned long long recheck;   // FP32 filter survivors rechecked in FP64 (counted per wave)
-  unsigned long long tests;     // pair tests of the large-extent search
+  unsigned long long tests;     // pair tests
+  unsigned long long pairs;     // pairs resolved by the first sweep
   unsigned long long pad[12];
+};
+struct alignas(128) ListShard {
+  int n[3];  // spheres in this shard of the list of the later sweeps, three sweeps in turn
+  int pad[29];
 };
 struct SweepCounters {
   CounterShard shard[NSHARD];
+  ListShard list[NSHARD];
   unsigned int n_overflow;  // spheres with more contacts than slots (list length)
-  unsigned int pad[31];
+  unsigned int ovf_later;   // the same among those that took a new partner later
+  unsigned int pad[30];
+  unsigned long long pairs[MAX_QUEUE][PAIR_SHARDS];  // pairs resolved by each later sweep
+};
+
+// What the host reads of a step (page-locked host memory, written by k_finish).
+struct StepReport {
+  unsigned long long contacts, recheck, tests;
+  unsigned int n_overflow, pad;
+  unsigned long long pairs[MAX_QUEUE];
 };
 
 // ---------------------------------------------------------------- the rule
@@ -366,7 +382,7 @@ struct StateGrad {
 // Device tables of the batched form: one grid per box, boxes' cells numbered
 // consecutively (cell_base), the box of every sphere, and status flags that
 // let every kernel of a captured step skip its work.
-enum { FLAG_DONE = 0, FLAG_ERR = 1, FLAG_SWEEPS = 2, FLAG_UNFINISHED = 3 };
+enum { FLAG_ERR = 0 };
 enum : unsigned int { ERR_INVALID = 1u, ERR_REPLAN = 2u, ERR_BOX = 4u };
 // A box's maxima during the batched reach pass (bits of non-negative doubles)
 // and its validity bits; zero between passes.
@@ -389,6 +405,31 @@ struct BatchDev {
   const int *chunk_box;
   const int64_t *chunk_lo;
   BoxMax *bmax;           // [nbox]
+};
+
+// Everything the sweeps need.
+struct SweepArgs {
+  int n, K;
+  int small;         // no contact slots: every search is exact
+  int exact;         // the later sweeps can search (else a step with overflowing slots stops)
+  int shards, shard_blocks;  // shards of the list, each with room for so many workgroups
+  const Rec *rec;
+  const int *start;
+  Grid G;
+  BatchDev B;        // tables of the batched form (gtab null: one box)
+  double dt, e;
+  const double *mass;
+  const int *cnt, *slot_j;
+  const double *slot_t;
+  double *key_t;
+  uint8_t *status;
+  OutRec *out;
+  int *list[2];      // n entries each and one workgroup more for each shard
+  SweepCounters *ctr;
+  const unsigned long long *crank;
+  const unsigned int *err;  // nullable; nonzero: the step does nothing
+  Spin spin;         // wx null: none
+  int turn = 0, rekeyed = 0;  // host: sweeps over the list queued so far, and sweep 1's DIRTY done
 };
 
 // Pair tests and filter survivors of one workgroup of the k_detect_half kernels.
@@ -447,35 +488,31 @@ hipError_t launch_detect_half(hipStream_t s, const DetectArgs &A);
 int detect_half_blocks(const DetectArgs &A);
 // adds the per-cell counts of launch_detect_half to the counter shards of ctr
 hipError_t launch_cell_counts(hipStream_t s, const CellCount *c, int n, SweepCounters *ctr);
-hipError_t launch_slot_min(hipStream_t s, int n, int first, const int *cnt, const double *slot_t,
-                           const int *slot_j, int K, uint8_t *status, const Rec *rec, int *key_j,
-                           double *key_t, int *ovf_list, SweepCounters *ctr,
-                           const unsigned int *flags, const int *list = nullptr, int nlist = 0,
-                           const Grid *G = nullptr,  // G: walls of the single box (none: periodic)
+hipError_t launch_slot_min(hipStream_t s, int n, const int *cnt, const double *slot_t,
+                           const int *slot_j, int K, const Rec *rec, int *key_j, double *key_t,
+                           int *ovf_list, SweepCounters *ctr, const unsigned int *err,
+                           const Grid *G = nullptr,  // walls of the single box (none: periodic)
                            const unsigned long long *crank = nullptr);  // literal order's ranks
 hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const unsigned int *nlist_dev,
                                int select, const Rec *rec, const int *start, const Grid &G,
-                               double dt, uint8_t *status, int *key_j, double *key_t,
+                               double dt, const uint8_t *status, int *key_j, double *key_t,
                                const BatchDev *B, const unsigned long long *crank = nullptr);
 hipError_t launch_curve_rank(hipStream_t s, const Rec *rec, int n, const CurveGrid &C,
                              unsigned long long *crank);
-// spin (nullable): friction and spins (the pair's sphere of smaller sorted index
-// resolves both sides and writes both spins in place)
-hipError_t launch_resolve_sweep(hipStream_t s, int n, const Rec *rec, const Grid &G, double dt,
-                                double e, const double *mass, const int *key_j,
-                                const double *key_t, uint8_t *status, OutRec *out,
-                                SweepCounters *ctr,
-                                const BatchDev *B,
-                                const int *list = nullptr, int nlist = 0,
-                                const Spin *spin = nullptr);
-// list (read back from off[(n + 255) / 256] entries) of the ACTIVE or
-// DIRTY spheres; count and off need (n + 255) / 256 + 1 entries, blocksum
-// ((n + 255) / 256) / 4096 + 2
-hipError_t launch_keep_list(hipStream_t s, const uint8_t *status, int n, int *count, int *off,
-                            int *blocksum, ReachOut *scratch_out, int *list);
+// The sweeps of a step (sweep_shards sets the list's shards).  first: every sphere;
+// rekey: new partners for those it left DIRTY; sweep k >= 1: the list, keys in
+// `in`, the next sweep's into `out`, the turn-th such sweep of the step.
+void sweep_shards(SweepArgs &A);
+hipError_t launch_sweep_first(hipStream_t s, const SweepArgs &A, const int *key);
+hipError_t launch_rekey(hipStream_t s, const SweepArgs &A, int *key);
+hipError_t launch_sweep(hipStream_t s, const SweepArgs &A, const int *in, int *out, int k,
+                        bool first, int turn);
+// the last nsweep sweeps have been queued: report, and the end-of-step state if the
+// last of them resolved nothing
 hipError_t launch_finish(hipStream_t s, const Particles &P, const int *rank, const OutRec *out,
                          const uint8_t *status, int *partner, double *tcoll, double dt,
-                         const Grid &G, const BatchDev *B);
+                         const Grid &G, const BatchDev *B, const SweepCounters *ctr, int nsweep,
+                         bool exact, StepReport *rep);
 hipError_t launch_fill_box_of(hipStream_t s, int nbox, const int64_t *box_off, int *box_of);
 // count given (zero on entry): the pass also takes every sphere's global cell
 // (box's first cell + local cell on its planned grid) and its slot in that cell
@@ -486,8 +523,6 @@ hipError_t launch_breach(hipStream_t s, const Particles &P, const BatchDev &B, d
 // cpw consecutive global cells per workgroup (one wave) over total_cells
 hipError_t launch_detect_batched(hipStream_t s, const DetectArgs &A, const BatchDev &B,
                                  int total_cells, int cpw);
-hipError_t launch_sweep_check(hipStream_t s, SweepCounters *ctr, unsigned int *flags,
-                              unsigned long long *totals, int last);
 hipError_t launch_advance(hipStream_t s, const Particles &P, const int *partner, double dt,
                           const double L[3]);
 hipError_t launch_status_from_active(hipStream_t s, const uint8_t *active, const Rec *rec, int n,

@@ -1107,89 +1107,98 @@ hipError_t launch_detect_half(hipStream_t s, const DetectArgs &A) {
 
 // ---------------------------------------------------------------- a5/a7: partner from contact slots
 
-// Earliest partner (rule 2: exact binary64 t, ties to the smaller caller index)
-// of each sphere among its recorded contacts whose partner has not collided;
-// with crank given (the literal order), the contact of smallest curve rank
-// instead (see k_curve_rank).  The contact set of a sphere only shrinks over
-// the sweeps of a step, so the slots written by the sweep-1 detect are
-// complete for every later sweep.
-// first = 1: every sphere (sweep 1); first = 0: only DIRTY spheres, which
-// become ACTIVE again.  Spheres with more contacts than slots are queued for
-// the exact search (rare; one atomic per wave that has one).  Slots are
-// k-major, so the reads of a wave are coalesced.
-__global__ __launch_bounds__(256) void k_slot_min(int n, int first, const int *cnt,
-                                                  const double *slot_t, const int *slot_j, int K,
-                                                  uint8_t *status, const Rec *rec, int *key_j,
-                                                  double *key_t, int *ovf_list,
-                                                  SweepCounters *ctr, const unsigned int *flags,
-                                                  const int *list, int nlist, Grid G,
-                                                  const unsigned long long *crank) {
-  if (flags && (flags[FLAG_ERR] || flags[FLAG_DONE])) return;
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  const int i = list && t < nlist ? list[t] : t;
+// Partner of sphere i among its c <= K recorded contacts, gone(j, out) telling
+// which of four spheres are no longer eligible: the earliest one (rule 2: exact binary64 t, ties
+// to the smaller caller index); with crank given (the literal order) the
+// contact of smallest curve rank instead (see k_curve_rank).  The contact set of
+// a sphere only shrinks over the sweeps of a step, so the slots written by the
+// sweep-1 detect are complete for every later sweep.  Slots are k-major, so the
+// reads of a wave are coalesced.  Four slots at a time: what the choice waits for is the chain of
+// reads behind each contact, and four chains run side by side.
+template <typename Gone>
+__device__ __forceinline__ void slot_choice(int i, int c, size_t n, const double *slot_t,
+                                            const int *slot_j, const Rec *rec, const Grid &G,
+                                            const unsigned long long *crank, Gone gone, int &bj,
+                                            double &bt) {
+  bt = INFINITY;
+  bj = -1;
+  unsigned long long br = ~0ull;  // literal order: curve rank of the best contact
+  // between walls a contact counts only before both centres reach a wall
+  double ti = INFINITY;
+  if (G.walls) {
+    const Rec a = rec[i];
+    ti = time_to_wall(a.x, a.y, a.z, a.vx, a.vy, a.vz, G);
+  }
+  for (int k0 = 0; k0 < c; k0 += 4) {
+    int j4[4];
+    double t4[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const size_t at = (size_t)(k0 + u < c ? k0 + u : k0) * n + i;
+      j4[u] = slot_j[at];
+      t4[u] = slot_t[at];
+    }
+    bool g4[4];
+    gone(j4, g4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = j4[u];
+      const double t = t4[u];
+      if (k0 + u >= c || g4[u]) continue;
+      if (G.walls) {
+        const Rec b = rec[j];
+        if (!(t <= ti) || !(t <= time_to_wall(b.x, b.y, b.z, b.vx, b.vy, b.vz, G))) continue;
+      }
+      if (crank) {
+        const unsigned long long rj = crank[j];
+        if (rj < br) {
+          br = rj;
+          bt = t;
+          bj = j;
+        }
+      } else if (t < bt || (bj >= 0 && t == bt && rec[j].o < rec[bj].o)) {
+        bt = t;
+        bj = j;
+      }
+    }
+  }
+}
+
+// Sweep 1's partner of every sphere.  Spheres with more contacts than slots are
+// queued for the exact search (rare; one atomic per wave that has one).
+__global__ __launch_bounds__(256) void k_slot_min(int n, const int *cnt, const double *slot_t,
+                                                  const int *slot_j, int K, const Rec *rec,
+                                                  int *key_j, double *key_t, int *ovf_list,
+                                                  SweepCounters *ctr, const unsigned int *err,
+                                                  Grid G, const unsigned long long *crank) {
+  if (err && *err) return;
+  const int i = blockIdx.x * 256 + threadIdx.x;
   bool ovf = false;
   unsigned long long nc = 0ull;
-  if (list ? t < nlist : i < n) {
-    const uint8_t st = status[i];
-    if (first ? st == ST_ACTIVE : st == ST_DIRTY) {
-      const int c = cnt[i];
-      nc = (unsigned long long)c;
-      if (c > K) {
-        ovf = true;
-        key_j[i] = -1;
-        key_t[i] = INFINITY;
-      } else {
-        double bt = INFINITY;
-        int bj = -1;
-        unsigned long long br = ~0ull;  // literal order: curve rank of the best contact
-        // between walls a contact counts only before both centres reach a wall
-        double ti = INFINITY;
-        if (G.walls) {
-          const Rec a = rec[i];
-          ti = time_to_wall(a.x, a.y, a.z, a.vx, a.vy, a.vz, G);
-        }
-        for (int k = 0; k < c; ++k) {
-          const int j = slot_j[(size_t)k * n + i];
-          if (!first && status[j] == ST_COLLIDED) continue;
-          const double t = slot_t[(size_t)k * n + i];
-          if (G.walls) {
-            const Rec b = rec[j];
-            if (!(t <= ti) || !(t <= time_to_wall(b.x, b.y, b.z, b.vx, b.vy, b.vz, G))) continue;
-          }
-          if (crank) {
-            const unsigned long long rj = crank[j];
-            if (rj < br) {
-              br = rj;
-              bt = t;
-              bj = j;
-            }
-          } else if (t < bt || (bj >= 0 && t == bt && rec[j].o < rec[bj].o)) {
-            bt = t;
-            bj = j;
-          }
-        }
-        key_j[i] = bj;
-        key_t[i] = bt;
-      }
-      if (!first) status[i] = ST_ACTIVE;
-    }
+  if (i < n) {
+    const int c = cnt[i];
+    nc = (unsigned long long)c;
+    ovf = c > K;
+    int bj;
+    double bt;
+    slot_choice(i, ovf ? 0 : c, (size_t)n, slot_t, slot_j, rec, G, crank,
+                [](const int(&)[4], bool(&g)[4]) { g[0] = g[1] = g[2] = g[3] = false; }, bj, bt);
+    key_j[i] = bj;
+    key_t[i] = bt;
   }
   const unsigned int k = wave_append(ovf, &ctr->n_overflow);
   if (ovf) ovf_list[k] = i;
-  if (first) block_add(nc, &my_shard(ctr).contacts);
+  block_add(nc, &my_shard(ctr).contacts);
 }
 
-hipError_t launch_slot_min(hipStream_t s, int n, int first, const int *cnt, const double *slot_t,
-                           const int *slot_j, int K, uint8_t *status, const Rec *rec, int *key_j,
-                           double *key_t, int *ovf_list, SweepCounters *ctr,
-                           const unsigned int *flags, const int *list, int nlist,
+hipError_t launch_slot_min(hipStream_t s, int n, const int *cnt, const double *slot_t,
+                           const int *slot_j, int K, const Rec *rec, int *key_j, double *key_t,
+                           int *ovf_list, SweepCounters *ctr, const unsigned int *err,
                            const Grid *G, const unsigned long long *crank) {
-  const int items = list ? nlist : n;
-  if (items <= 0) return hipSuccess;
+  if (n <= 0) return hipSuccess;
   const Grid none{};  // walls = 0: periodic
-  hipLaunchKernelGGL(k_slot_min, dim3((items + 255) / 256), dim3(256), 0, s, n, first, cnt, slot_t,
-                     slot_j, K, status, rec, key_j, key_t, ovf_list, ctr, flags, list, nlist,
-                     G ? *G : none, crank);
+  hipLaunchKernelGGL(k_slot_min, dim3((n + 255) / 256), dim3(256), 0, s, n, cnt, slot_t, slot_j, K,
+                     rec, key_j, key_t, ovf_list, ctr, err, G ? *G : none, crank);
   return hipGetLastError();
 }
 
@@ -1450,25 +1459,78 @@ hipError_t launch_detect_wide(hipStream_t s, const DetectArgs &A, const int *fir
   return hipGetLastError();
 }
 
-// Earliest partner (rule 2: exact binary64 t, ties to the smaller caller index;
-// with crank given, the contact of smallest curve rank) by an exact search of
-// the sphere's search box (the 27 surrounding cells, or the wider box of a
-// split grid, in both layers), minimum image by rule 1.
-// One wave per sphere; lanes over candidates; the wave reduces (t, caller
-// index) exactly.  Spheres come from `list` (length nlist, or *nlist_dev when
-// given) or, with list NULL, are all i < nlist whose status is `select`
-// (select < 0: all); selected DIRTY spheres become ACTIVE.  Collided spheres
-// are never candidates.  Used for spheres whose contacts overflowed the slots,
-// for pcol_detect with an active mask, and for grids with fewer than 3 cells
-// along some axis.
+// Partner of sphere i (record a, grid G, cell starts `start`) by an exact search
+// of its search box (the 27 surrounding cells, or the wider box of a split grid,
+// in both layers), minimum image by rule 1: the earliest (rule 2: exact binary64
+// t, ties to the smaller caller index) or, with crank given, the contact of
+// smallest curve rank, among the spheres that are not `gone`.  The whole wave
+// works on one sphere, lanes over candidates, and every lane gets the result.
+template <typename Gone>
+__device__ __forceinline__ void exact_partner(int i, const Rec &a, const Grid &G, const int *start,
+                                              const Rec *rec, double dt,
+                                              const unsigned long long *crank, Gone gone, int &bj,
+                                              double &bt) {
+  const int lane = __lane_id();
+  int k[3];
+  search_radius(G, a, dt, k);
+  const int cx = cell_coord(a.x, G.inv_h[0], G.nc[0]);
+  const int cy = cell_coord(a.y, G.inv_h[1], G.nc[1]);
+  const int cz = cell_coord(a.z, G.inv_h[2], G.nc[2]);
+  bt = INFINITY;
+  bj = -1;
+  int bo = 0x7fffffff;
+  unsigned long long br = ~0ull;  // literal order: curve rank of the best contact
+  for (int layer = 0; layer < (G.layer2 ? 2 : 1); ++layer) {
+    search_box_runs(G, start, layer ? G.layer2 : 0, cx, cy, cz, k, [&](int s0, int s1) {
+      for (int j = s0 + lane; j < s1; j += WAVE) {
+        if (j == i || gone(j)) continue;
+        const Rec b = rec[j];
+        double t;
+        if (pair_time_walls(a, b, G, dt, t)) {
+          const int o = b.o;
+          if (crank) {
+            const unsigned long long rj = crank[j];
+            if (rj < br) {
+              br = rj;
+              bt = t;
+              bj = j;
+            }
+          } else if (t < bt || (t == bt && o < bo)) {
+            bt = t;
+            bo = o;
+            bj = j;
+          }
+        }
+      }
+    });
+  }
+  for (int o = WAVE / 2; o > 0; o >>= 1) {
+    const double t2 = __shfl_xor(bt, o);
+    const int o2 = __shfl_xor(bo, o);
+    const int j2 = __shfl_xor(bj, o);
+    const unsigned long long r2 = __shfl_xor(br, o);
+    if (crank ? r2 < br : (t2 < bt || (t2 == bt && o2 < bo))) {
+      bt = t2;
+      bo = o2;
+      bj = j2;
+      br = r2;
+    }
+  }
+}
+
+// Exact partners of a list of spheres, one wave per sphere (exact_partner):
+// `list` of length nlist, or *nlist_dev when given, or, with list NULL, all
+// i < nlist whose status is `select` (select < 0: all).  status (nullable: none
+// has) tells the collided spheres, never candidates.  Used for spheres whose
+// contacts overflowed the slots, for pcol_detect with an active mask, and for
+// grids with fewer than 3 cells along some axis.
 __global__ __launch_bounds__(256) void k_gather_exact(const int *list, int nlist,
                                                       const unsigned int *nlist_dev, int select,
                                                       const Rec *rec, const int *start, Grid G0,
-                                                      double dt, uint8_t *status, int *key_j,
+                                                      double dt, const uint8_t *status, int *key_j,
                                                       double *key_t, BatchDev B,
                                                       const unsigned long long *crank) {
-  if (B.flags && (B.flags[FLAG_ERR] || B.flags[FLAG_DONE])) return;
-  const int lane = __lane_id();
+  if (B.flags && B.flags[FLAG_ERR]) return;
   const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
   const int nw = (gridDim.x * blockDim.x) / WAVE;
   const int count = nlist_dev ? (int)*nlist_dev : nlist;
@@ -1480,65 +1542,25 @@ __global__ __launch_bounds__(256) void k_gather_exact(const int *list, int nlist
     const int bx = B.gtab ? a.box : 0;
     const Grid G = B.gtab ? B.gtab[bx] : G0;
     const int *st = B.gtab ? start + B.cell_base[bx] : start;
-    int k[3];
-    search_radius(G, a, dt, k);
-    const int cx = cell_coord(a.x, G.inv_h[0], G.nc[0]);
-    const int cy = cell_coord(a.y, G.inv_h[1], G.nc[1]);
-    const int cz = cell_coord(a.z, G.inv_h[2], G.nc[2]);
-    double bt = INFINITY;
-    int bo = 0x7fffffff, bj = -1;
-    unsigned long long br = ~0ull;  // literal order: curve rank of the best contact
-    for (int layer = 0; layer < (G.layer2 ? 2 : 1); ++layer) {
-      search_box_runs(G, st, layer ? G.layer2 : 0, cx, cy, cz, k, [&](int s0, int s1) {
-        for (int j = s0 + lane; j < s1; j += WAVE) {
-          if (j == i) continue;
-          if (status[j] == ST_COLLIDED) continue;
-          const Rec b = rec[j];
-          double t;
-          if (pair_time_walls(a, b, G, dt, t)) {
-            const int o = b.o;
-            if (crank) {
-              const unsigned long long rj = crank[j];
-              if (rj < br) {
-                br = rj;
-                bt = t;
-                bj = j;
-              }
-            } else if (t < bt || (t == bt && o < bo)) {
-              bt = t;
-              bo = o;
-              bj = j;
-            }
-          }
-        }
-      });
-    }
-    for (int o = WAVE / 2; o > 0; o >>= 1) {
-      const double t2 = __shfl_xor(bt, o);
-      const int o2 = __shfl_xor(bo, o);
-      const int j2 = __shfl_xor(bj, o);
-      const unsigned long long r2 = __shfl_xor(br, o);
-      if (crank ? r2 < br : (t2 < bt || (t2 == bt && o2 < bo))) {
-        bt = t2;
-        bo = o2;
-        bj = j2;
-        br = r2;
-      }
-    }
-    if (lane == 0) {
+    int bj;
+    double bt;
+    exact_partner(i, a, G, st, rec, dt, crank,
+                  [&](int j) { return status && status[j] == ST_COLLIDED; }, bj, bt);
+    if (__lane_id() == 0) {
       key_j[i] = bj;
       key_t[i] = bt;
-      if (status[i] == ST_DIRTY) status[i] = ST_ACTIVE;
     }
   }
 }
 
 hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const unsigned int *nlist_dev,
                                int select, const Rec *rec, const int *start, const Grid &G,
-                               double dt, uint8_t *status, int *key_j, double *key_t,
+                               double dt, const uint8_t *status, int *key_j, double *key_t,
                                const BatchDev *B, const unsigned long long *crank) {
-  int64_t waves = nlist_dev ? 8192 : nlist;
-  if (waves <= 0) return hipSuccess;
+  // a list whose length is on the device is short: a wave for 64 of the nlist
+  // spheres it could name at most, in 16 to 2048 workgroups
+  int64_t waves = nlist_dev ? std::max((int64_t)64, (int64_t)nlist / 64) : nlist;
+  if (nlist <= 0) return hipSuccess;
   if (waves > 8192) waves = 8192;
   const int blocks = (int)((waves + 3) / 4);
   BatchDev none{};
@@ -1549,163 +1571,370 @@ hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const 
 
 // ---------------------------------------------------------------- a6: mutual resolve
 
-// One sweep of rule 3-4 over every ACTIVE sphere (cell-sorted order).  A sphere
-// whose partner has it as partner resolves its own side of the pair from the
-// start-of-step records and writes its end-of-step state to its output record
-// (Sec. "Inter-Particle Collisions"; eq. update_vel, update_rho).  A sphere
-// whose partner pairs with a third sphere this sweep becomes DIRTY (new partner
-// search next sweep); one without a partner becomes FREE for the step.  Each
-// thread writes only its own status, and reads only keys, so the sweep is a
-// pure function of the keys.  Partners are spatial neighbours, so the partner
-// reads stay within a few cells of the sorted order.
-// SPIN: the friction-and-spin resolve (S given); the plain kernel leaves it out
-// and needs half the registers, which the sweeps' random reads repay in waves.
+// Rule 4 for sphere i and its mutual partner p: i's end-of-step state into its
+// output record (Sec. "Inter-Particle Collisions"; eq. update_vel, update_rho)
+// and its status.  Returns 1 for one of the two spheres of the pair.
+// SPIN: the friction-and-spin resolve.  The thread of the smaller sorted index
+// resolves both sides and writes both spins in place (the partner's thread
+// writes nothing, so no thread reads a spin another one has already changed).
 template <bool SPIN>
-__global__ __launch_bounds__(256) void k_resolve_sweep(int n, const Rec *rec, Grid G0, double dt,
-                                                       double e, const double *mass,
-                                                       const int *key_j, const double *key_t,
-                                                       uint8_t *status, OutRec *out,
-                                                       SweepCounters *ctr, BatchDev B,
-                                                       const int *list,
-                                                       int nlist, Spin S) {
-  if (B.flags && (B.flags[FLAG_ERR] || B.flags[FLAG_DONE])) return;
-  const int ti = blockIdx.x * 256 + threadIdx.x;
-  const bool valid = list ? ti < nlist : ti < n;
-  const int i = list && valid ? list[ti] : ti;
-  unsigned long long npair = 0ull;
-  if (valid && status[i] == ST_ACTIVE) {
-    const int p = key_j[i];
-    if (p < 0) {
-      status[i] = ST_FREE;
-    } else {
-      const int q = key_j[p];
-      if (SPIN && q == i) {
-        // with spins, the thread of the smaller sorted index resolves both sides
-        // and writes both spins in place (the partner's thread writes nothing,
-        // so no thread reads a spin another one has already changed)
-        if (i < p) {
-          const Rec a = rec[i], b = rec[p];
-          const double t = key_t[i];
-          const double ma = mass[a.o], mb = mass[b.o];
-          const double wa[3] = {S.wx[a.o], S.wy[a.o], S.wz[a.o]};
-          const double wb[3] = {S.wx[b.o], S.wy[b.o], S.wz[b.o]};
-          double xo[3], vo[3], wo[3];
-          resolve_one_spin(a, b, ma, mb, wa, wb, G0, t, dt, e, S.mu, xo, vo, wo);
-          out[i] = OutRec{xo[0], xo[1], xo[2], vo[0], vo[1], vo[2], t, b.o, 0u};
-          S.wx[a.o] = wo[0];
-          S.wy[a.o] = wo[1];
-          S.wz[a.o] = wo[2];
-          resolve_one_spin(b, a, mb, ma, wb, wa, G0, t, dt, e, S.mu, xo, vo, wo);
-          out[p] = OutRec{xo[0], xo[1], xo[2], vo[0], vo[1], vo[2], t, a.o, 0u};
-          S.wx[b.o] = wo[0];
-          S.wy[b.o] = wo[1];
-          S.wz[b.o] = wo[2];
-          status[i] = ST_COLLIDED;
-          status[p] = ST_COLLIDED;
-          npair = 1ull;
-        }
-      } else if (q == i) {
-        const Rec a = rec[i], b = rec[p];
-        const double t = key_t[i];
-        const double ma = mass[a.o], mb = mass[b.o];
-        double xo[3], vo[3];
-        if (B.gtab) {
-          const Grid G = B.gtab[a.box];
-          resolve_one(a, b, ma, mb, G, t, dt, e, xo, vo);
-        } else {
-          resolve_one(a, b, ma, mb, G0, t, dt, e, xo, vo);
-        }
-        OutRec o;
-        o.x = xo[0];
-        o.y = xo[1];
-        o.z = xo[2];
-        o.vx = vo[0];
-        o.vy = vo[1];
-        o.vz = vo[2];
-        o.t = t;
-        o.partner = b.o;
-        o.pad = 0u;
-        out[i] = o;
-        status[i] = ST_COLLIDED;
-        if (i < p) npair = 1ull;
-      } else if (q >= 0 && key_j[q] == p) {
-        status[i] = ST_DIRTY;  // p pairs with q this sweep
-      }
-    }
+__device__ __forceinline__ unsigned long long resolve_pair(const SweepArgs &A, int i, int p) {
+  if (SPIN) {
+    if (i > p) return 0ull;
+    const Rec a = A.rec[i], b = A.rec[p];
+    const double t = A.key_t[i];
+    const double ma = A.mass[a.o], mb = A.mass[b.o];
+    const Spin &S = A.spin;
+    const double wa[3] = {S.wx[a.o], S.wy[a.o], S.wz[a.o]};
+    const double wb[3] = {S.wx[b.o], S.wy[b.o], S.wz[b.o]};
+    double xo[3], vo[3], wo[3];
+    resolve_one_spin(a, b, ma, mb, wa, wb, A.G, t, A.dt, A.e, S.mu, xo, vo, wo);
+    A.out[i] = OutRec{xo[0], xo[1], xo[2], vo[0], vo[1], vo[2], t, b.o, 0u};
+    S.wx[a.o] = wo[0];
+    S.wy[a.o] = wo[1];
+    S.wz[a.o] = wo[2];
+    resolve_one_spin(b, a, mb, ma, wb, wa, A.G, t, A.dt, A.e, S.mu, xo, vo, wo);
+    A.out[p] = OutRec{xo[0], xo[1], xo[2], vo[0], vo[1], vo[2], t, a.o, 0u};
+    S.wx[b.o] = wo[0];
+    S.wy[b.o] = wo[1];
+    S.wz[b.o] = wo[2];
+    A.status[i] = ST_COLLIDED;
+    A.status[p] = ST_COLLIDED;
+    return 1ull;
   }
-  block_add(npair, &my_shard(ctr).pairs);
+  const Rec a = A.rec[i], b = A.rec[p];
+  const double t = A.key_t[i];
+  const double ma = A.mass[a.o], mb = A.mass[b.o];
+  double xo[3], vo[3];
+  if (A.B.gtab) {
+    const Grid G = A.B.gtab[a.box];
+    resolve_one(a, b, ma, mb, G, t, A.dt, A.e, xo, vo);
+  } else {
+    resolve_one(a, b, ma, mb, A.G, t, A.dt, A.e, xo, vo);
+  }
+  A.out[i] = OutRec{xo[0], xo[1], xo[2], vo[0], vo[1], vo[2], t, b.o, 0u};
+  A.status[i] = ST_COLLIDED;
+  return i < p ? 1ull : 0ull;
 }
 
-hipError_t launch_resolve_sweep(hipStream_t s, int n, const Rec *rec, const Grid &G, double dt,
-                                double e, const double *mass, const int *key_j,
-                                const double *key_t, uint8_t *status, OutRec *out,
-                                SweepCounters *ctr, const BatchDev *B,
-                                const int *list, int nlist, const Spin *spin) {
-  const int items = list ? nlist : n;
-  if (items <= 0) return hipSuccess;
-  BatchDev none{};
-  if (spin && spin->wx)
-    hipLaunchKernelGGL(k_resolve_sweep<true>, dim3((items + 255) / 256), dim3(256), 0, s, n, rec,
-                       G, dt, e, mass, key_j, key_t, status, out, ctr, B ? *B : none, list, nlist,
-                       *spin);
-  else
-    hipLaunchKernelGGL(k_resolve_sweep<false>, dim3((items + 255) / 256), dim3(256), 0, s, n, rec,
-                       G, dt, e, mass, key_j, key_t, status, out, ctr, B ? *B : none, list, nlist,
-                       Spin{nullptr, nullptr, nullptr, 0.0});
-  return hipGetLastError();
+// Pairs resolved by sweep `s` of the queue.  The first sweep adds its pairs up on
+// all shards: 62,500 workgroups adding to four addresses took 0.4 ms at 16M.
+__device__ __forceinline__ unsigned long long sweep_pairs(const SweepCounters *ctr, int s) {
+  unsigned long long t = 0ull;
+  if (s == 0) {
+    for (int k = 0; k < NSHARD; ++k) t += ctr->shard[k].pairs;
+  }
+#pragma unroll
+  for (int k = 0; k < PAIR_SHARDS; ++k) t += ctr->pairs[s][k];
+  return t;
 }
 
-// The spheres a sweep left ACTIVE or DIRTY, in sorted order, as a list for the
-// later sweeps (the others are done for the step): per-workgroup counts, an
-// exclusive scan of the counts (launch_scan), then each workgroup writes its
-// spheres from its offset.  No shared counter.
-__global__ __launch_bounds__(256) void k_keep_count(const uint8_t *status, int n, int *count) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const bool keep = i < n && (status[i] == ST_ACTIVE || status[i] == ST_DIRTY);
+// Append this thread's i (where keep) to shard sh of a list behind one atomic per
+// workgroup on its count.
+__device__ __forceinline__ void list_append(bool keep, int i, int *count, int *list) {
   __shared__ int part[256 / WAVE];
-  const int c = __popcll(__ballot(keep));
-  if (__lane_id() == 0) part[threadIdx.x / WAVE] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) count[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
-}
-
-__global__ __launch_bounds__(256) void k_keep_write(const uint8_t *status, int n, const int *off,
-                                                    int *list) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  const bool keep = i < n && (status[i] == ST_ACTIVE || status[i] == ST_DIRTY);
-  __shared__ int part[256 / WAVE];
-  const unsigned long long m = __ballot(keep);
+  __shared__ int at;
+  const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
   const int w = threadIdx.x / WAVE;
   if (__lane_id() == 0) part[w] = __popcll(m);
   __syncthreads();
-  int base = off[blockIdx.x];
+  if (threadIdx.x == 0) {
+    const int c = part[0] + part[1] + part[2] + part[3];
+    at = c ? atomicAdd(count, c) : 0;
+  }
+  __syncthreads();
+  int base = at;
   for (int k = 0; k < w; ++k) base += part[k];
   if (keep) list[base + __popcll(m & ((1ull << __lane_id()) - 1ull))] = i;
+  __syncthreads();  // part and at are free again
 }
 
-hipError_t launch_keep_list(hipStream_t s, const uint8_t *status, int n, int *count, int *off,
-                            int *blocksum, ReachOut *scratch_out, int *list) {
-  if (n <= 0) return hipSuccess;
-  const int nb = (n + 255) / 256;
-  hipLaunchKernelGGL(k_keep_count, dim3(nb), dim3(256), 0, s, status, n, count);
-  hipError_t e = launch_scan(s, count, nb, off, blocksum, scratch_out);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_keep_write, dim3(nb), dim3(256), 0, s, status, n, off, list);
+// The first sweep (rule 3-4), over every sphere in cell-sorted order.  A sphere
+// whose partner has it as partner collides; one whose partner pairs with a
+// third sphere becomes DIRTY (k_rekey finds it another); one without a partner
+// is FREE for the step.  Each thread writes its own status only and reads keys
+// only, so the sweep is a pure function of the keys.  Partners are spatial
+// neighbours, so the partner reads stay within a few cells of the sorted order.
+// The spheres left for the later sweeps (8.5% at 16M) go to a list: each
+// workgroup appends its own behind one atomic, to the part of the list that
+// belongs to its shard.  Shards take every 64th workgroup, so the workgroups
+// that run at one time spread over all of them (shards of consecutive
+// workgroups, and with them one address for most of the chip: 600 us at 16M).
+template <bool SPIN>
+__global__ __launch_bounds__(256) void k_sweep_first(SweepArgs A, const int *key) {
+  if ((A.err && *A.err) || (!A.exact && A.ctr->n_overflow != 0u)) return;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  unsigned long long npair = 0ull;
+  bool keep = false;
+  if (i < A.n) {
+    const int p = key[i];
+    if (p < 0) {
+      A.status[i] = ST_FREE;
+    } else {
+      const int q = key[p];
+      if (q == i) {
+        npair = resolve_pair<SPIN>(A, i, p);
+      } else {
+        keep = true;
+        A.status[i] = q >= 0 && key[q] == p ? ST_DIRTY : ST_ACTIVE;
+      }
+    }
+  }
+  const int sh = blockIdx.x % A.shards;
+  list_append(keep, i, &A.ctr->list[sh].n[0], A.list[0] + (size_t)sh * A.shard_blocks * 256);
+  block_add(npair, &my_shard(A.ctr).pairs);
+}
+
+// Spheres no longer eligible during k_rekey: those that collided.
+struct GoneCollided {
+  const uint8_t *status;
+  __device__ __forceinline__ bool one(int j) const { return status[j] == ST_COLLIDED; }
+  __device__ __forceinline__ void operator()(const int (&j)[4], bool (&g)[4]) const {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g[u] = status[j[u]] == ST_COLLIDED;
+  }
+};
+
+// Spheres no longer eligible after a sweep with the keys `in`: those done before
+// it and those that collide in it (in[in[j]] == j), whatever status they have by
+// now.
+struct GoneInSweep {
+  const uint8_t *status;
+  const int *in;
+  __device__ __forceinline__ bool one(int j) const {
+    if (status[j] != ST_ACTIVE) return true;
+    const int p = in[j];
+    return p >= 0 && in[p] == j;
+  }
+  __device__ __forceinline__ void operator()(const int (&j)[4], bool (&g)[4]) const {
+    bool act[4];
+    int p[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      act[u] = status[j[u]] == ST_ACTIVE;
+      p[u] = in[j[u]];  // a key only where j is active
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) p[u] = act[u] && p[u] >= 0 ? p[u] : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g[u] = !act[u] || (p[u] >= 0 && in[p[u]] == j[u]);
+  }
+};
+
+// New partner of a listed sphere i (need: it wants one, else the lane only takes
+// part) among those not gone: from its slots, or (EXACT) by the exact search,
+// the wave on one sphere after another, where its contacts overflowed them or
+// the grid is too small for the pair tests.
+template <bool EXACT, typename Gone>
+__device__ __forceinline__ void new_partner(const SweepArgs &A, bool need, int i, const Gone &gone,
+                                            int &bj, double &bt) {
+  bj = -1;
+  bt = INFINITY;
+  bool search = false;
+  if (need) {
+    const int c = EXACT && A.small ? 0 : A.cnt[i];
+    search = EXACT && (A.small || c > A.K);
+    if (!search)
+      slot_choice(i, c, (size_t)A.n, A.slot_t, A.slot_j, A.rec, A.G, A.crank, gone, bj, bt);
+  }
+  if (!EXACT) return;
+  unsigned long long todo = __builtin_amdgcn_ballot_w64(search);
+  if (!todo) return;
+  if (!A.small && (int)__lane_id() == __ffsll((long long)todo) - 1)
+    atomicAdd(&A.ctr->ovf_later, (unsigned int)__popcll(todo));
+  while (todo) {
+    const int l = __ffsll((long long)todo) - 1;
+    todo &= todo - 1ull;
+    const int w = __builtin_amdgcn_readlane(i, l);
+    const Rec a = A.rec[w];
+    const auto is_gone = [&](int j) { return gone.one(j); };
+    int j;
+    double t;
+    if (A.B.gtab)
+      exact_partner(w, a, A.B.gtab[a.box], A.start + A.B.cell_base[a.box], A.rec, A.dt, A.crank,
+                    is_gone, j, t);
+    else
+      exact_partner(w, a, A.G, A.start, A.rec, A.dt, A.crank, is_gone, j, t);
+    if ((int)__lane_id() == l) {
+      bj = j;
+      bt = t;
+    }
+  }
+}
+
+// Whether a kernel of the later sweeps has nothing to do: an error, or no exact
+// search in a step that needs it (some sphere's contacts overflowed its slots):
+// the host sees the overflow and queues the sweeps again with it.  The search
+// costs 30 registers, so steps without overflow go without.
+template <bool EXACT>
+__device__ __forceinline__ bool sweep_off(const SweepArgs &A) {
+  return (A.err && *A.err) || (!EXACT && A.ctr->n_overflow != 0u);
+}
+
+// The partners of the spheres that sweep 1 left DIRTY (in place: only DIRTY keys
+// change and no key is read).
+template <bool EXACT>
+__global__ __launch_bounds__(256) void k_rekey(SweepArgs A, int *key) {
+  if (sweep_off<EXACT>(A)) return;
+  const int sh = blockIdx.y, count = A.ctr->list[sh].n[0];
+  const int *list = A.list[0] + (size_t)sh * A.shard_blocks * 256;
+  const GoneCollided gone{A.status};
+  for (int t0 = blockIdx.x * 256; t0 < count; t0 += gridDim.x * 256) {
+    const int t = t0 + threadIdx.x;
+    const int i = t < count ? list[t] : 0;
+    const bool need = t < count && A.status[i] == ST_DIRTY;
+    int bj;
+    double bt;
+    new_partner<EXACT>(A, need, i, gone, bj, bt);
+    if (need) {
+      key[i] = bj;
+      A.key_t[i] = bt;
+      A.status[i] = ST_ACTIVE;
+    }
+  }
+}
+
+// A later sweep over the list, `in` its keys: the mutual pairs collide, and a
+// sphere whose partner collides with a third one takes its next partner at
+// once, so the keys of the next sweep (out) leave with this kernel and a sweep
+// is one launch.  Whether a sphere collides in this sweep follows from the keys
+// alone (in[in[j]] == j), so nothing waits for the statuses other threads write
+// meanwhile.  Only listed spheres are ever looked up: an eligible contact of an
+// active sphere is active itself.  The spheres still active go to the next
+// sweep's list: list lin is read, the other one written; of the three counts of
+// a shard, this sweep reads count c, adds to the next and clears the one after.
+// The sweep runs if the one before it (s - 1) resolved a pair, or if it is the
+// first over the list or of its queue.
+template <bool SPIN, bool EXACT>
+__global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const int *in, int *out, int s,
+                                               int first, int lin, int c) {
+  if (sweep_off<EXACT>(A)) return;
+  if (!first && sweep_pairs(A.ctr, s - 1) == 0ull) return;
+  const int sh = blockIdx.y;
+  const int c1 = c == 2 ? 0 : c + 1, c2 = c1 == 2 ? 0 : c1 + 1;
+  const int count = A.ctr->list[sh].n[c];
+  if (blockIdx.x == 0 && threadIdx.x == 0) A.ctr->list[sh].n[c2] = 0;
+  if ((int)blockIdx.x * 256 >= count) return;
+  const size_t at = (size_t)sh * A.shard_blocks * 256;
+  const int *list = A.list[lin] + at;
+  int *next = A.list[lin ^ 1] + at;
+  const GoneInSweep gone{A.status, in};
+  unsigned long long npair = 0ull;
+  for (int t0 = blockIdx.x * 256; t0 < count; t0 += gridDim.x * 256) {
+    const int t = t0 + threadIdx.x;
+    const int i = t < count ? list[t] : 0;
+    bool need = false, keep = false;
+    if (t < count && A.status[i] == ST_ACTIVE) {
+      const int p = in[i];
+      if (p < 0) {
+        A.status[i] = ST_FREE;
+      } else {
+        const int q = in[p];
+        if (q == i) {
+          npair += resolve_pair<SPIN>(A, i, p);
+        } else {
+          keep = true;
+          need = q >= 0 && in[q] == p;
+          if (!need) out[i] = p;
+        }
+      }
+    }
+    if (__builtin_amdgcn_ballot_w64(need)) {
+      int bj;
+      double bt;
+      new_partner<EXACT>(A, need, i, gone, bj, bt);
+      if (need) {
+        out[i] = bj;
+        A.key_t[i] = bt;
+      }
+    }
+    list_append(keep, i, &A.ctr->list[sh].n[c1], next);
+  }
+  block_add(npair, &A.ctr->pairs[s][blockIdx.x % PAIR_SHARDS]);
+}
+
+// Shards of the list for n spheres (at least 8 workgroups of the first sweep
+// each) and their room in it, in workgroups.
+void sweep_shards(SweepArgs &A) {
+  const int nb = (A.n + 255) / 256;
+  A.shards = std::min(NSHARD, std::max(1, nb / 8));
+  A.shard_blocks = (nb + A.shards - 1) / A.shards;
+}
+
+hipError_t launch_sweep_first(hipStream_t s, const SweepArgs &A, const int *key) {
+  if (A.n <= 0) return hipSuccess;
+  const dim3 grid((A.n + 255) / 256);
+  if (A.spin.wx)
+    hipLaunchKernelGGL(k_sweep_first<true>, grid, dim3(256), 0, s, A, key);
+  else
+    hipLaunchKernelGGL(k_sweep_first<false>, grid, dim3(256), 0, s, A, key);
   return hipGetLastError();
 }
 
+// Grid of a kernel over the list: one row of workgroups per shard, enough for
+// a quarter of the spheres at once (a tenth is usual; more take another turn).
+static dim3 list_grid(const SweepArgs &A) {
+  return dim3((A.shard_blocks + 3) / 4, A.shards);
+}
+
+hipError_t launch_rekey(hipStream_t s, const SweepArgs &A, int *key) {
+  if (A.n <= 0) return hipSuccess;
+  if (A.exact)
+    hipLaunchKernelGGL(k_rekey<true>, list_grid(A), dim3(256), 0, s, A, key);
+  else
+    hipLaunchKernelGGL(k_rekey<false>, list_grid(A), dim3(256), 0, s, A, key);
+  return hipGetLastError();
+}
+
+hipError_t launch_sweep(hipStream_t s, const SweepArgs &A, const int *in, int *out, int k,
+                        bool first, int turn) {
+  if (A.n <= 0) return hipSuccess;
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, list_grid(A), dim3(256), 0, s, A, in, out, k, (int)first, turn & 1,
+                       turn % 3);
+  };
+  if (A.spin.wx)
+    A.exact ? go(k_sweep<true, true>) : go(k_sweep<true, false>);
+  else
+    A.exact ? go(k_sweep<false, true>) : go(k_sweep<false, false>);
+  return hipGetLastError();
+}
+
+// What the host reads of a step, written to its memory by the last kernel.
+__device__ __forceinline__ void write_report(const SweepCounters *ctr, int nsweep,
+                                             StepReport *rep) {
+  const int t = threadIdx.x;
+  for (int k = t; k < nsweep; k += 256) rep->pairs[k] = sweep_pairs(ctr, k);
+  if (t < NSHARD) {
+    const unsigned long long c = wave_sum(ctr->shard[t].contacts),
+                             r = wave_sum(ctr->shard[t].recheck),
+                             e = wave_sum(ctr->shard[t].tests);
+    if (t == 0) {
+      rep->contacts = c;
+      rep->recheck = r;
+      rep->tests = e;
+      rep->n_overflow = ctr->n_overflow + ctr->ovf_later;
+    }
+  }
+}
+
 // a8 and the copy back: the end-of-step state of every sphere in the caller's
-// order (coalesced writes).  A sphere whose status (sorted order) says it
-// collided this step takes the output record its resolve wrote; any other
-// flies the whole step from its start state, still in the caller's arrays
+// order (coalesced writes), if the last of the nsweep sweeps queued resolved no
+// pair (otherwise the host queues more).  A sphere whose status (sorted order)
+// says it collided this step takes the output record its resolve wrote; any
+// other flies the whole step from its start state, still in the caller's arrays
 // (rule 5).  Only collided spheres read their 64-B output record; the others
 // read one status byte (a 1-B-per-sphere array that stays in the device's
 // last-level cache).
 __global__ __launch_bounds__(256) void k_finish(Particles P, const int *rank,
                                                 const OutRec *out, const uint8_t *status,
                                                 int *partner, double *tcoll, double dt, Grid G0,
-                                                BatchDev B) {
-  if (B.flags && (B.flags[FLAG_ERR] || B.flags[FLAG_UNFINISHED])) return;
+                                                BatchDev B, const SweepCounters *ctr, int nsweep,
+                                                int exact, StepReport *rep) {
+  if (blockIdx.x == 0) write_report(ctr, nsweep, rep);
+  if ((B.flags && B.flags[FLAG_ERR]) || (!exact && ctr->n_overflow != 0u) ||
+      sweep_pairs(ctr, nsweep - 1) != 0ull)
+    return;
   const int64_t o = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (o >= P.n) return;
   double x, y, z, vx, vy, vz, t;
@@ -1745,11 +1974,12 @@ __global__ __launch_bounds__(256) void k_finish(Particles P, const int *rank,
 
 hipError_t launch_finish(hipStream_t s, const Particles &P, const int *rank, const OutRec *out,
                          const uint8_t *status, int *partner, double *tcoll, double dt,
-                         const Grid &G, const BatchDev *B) {
+                         const Grid &G, const BatchDev *B, const SweepCounters *ctr, int nsweep,
+                         bool exact, StepReport *rep) {
   if (P.n <= 0) return hipSuccess;
   BatchDev none{};
   hipLaunchKernelGGL(k_finish, dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, s, P, rank, out,
-                     status, partner, tcoll, dt, G, B ? *B : none);
+                     status, partner, tcoll, dt, G, B ? *B : none, ctr, nsweep, (int)exact, rep);
   return hipGetLastError();
 }
 
@@ -2139,39 +2369,6 @@ hipError_t launch_detect_batched(hipStream_t s, const DetectArgs &A, const Batch
   if (cpw < 1 || total_cells <= 0) return cpw < 1 ? hipErrorInvalidValue : hipSuccess;
   hipLaunchKernelGGL(k_detect_batched, dim3((unsigned)((total_cells + cpw - 1) / cpw)), dim3(WAVE),
                      0, s, A, B, cpw);
-  return hipGetLastError();
-}
-
-// After a sweep's resolve: total the pairs it resolved (and the running totals),
-// clear the per-sweep counters, and mark the step done when the sweep resolved
-// none.  `last` marks the final sweep slot of a captured step: if pairs were
-// still resolved there, the step is unfinished and the host completes it.
-__global__ __launch_bounds__(64) void k_sweep_check(SweepCounters *ctr, unsigned int *flags,
-                                                    unsigned long long *totals, int last) {
-  if (flags[FLAG_ERR] || flags[FLAG_DONE]) return;
-  const int l = threadIdx.x;
-  unsigned long long p = ctr->shard[l].pairs, c = ctr->shard[l].contacts;
-  ctr->shard[l].pairs = 0ull;
-  ctr->shard[l].contacts = 0ull;
-  p = wave_sum(p);
-  c = wave_sum(c);
-  if (l == 0) {
-    totals[0] += p;
-    totals[1] += c;
-    totals[2] += ctr->n_overflow;
-    ctr->n_overflow = 0u;
-    flags[FLAG_SWEEPS] += 1u;
-    if (p == 0ull) {
-      flags[FLAG_DONE] = 1u;
-    } else if (last) {
-      flags[FLAG_UNFINISHED] = 1u;
-    }
-  }
-}
-
-hipError_t launch_sweep_check(hipStream_t s, SweepCounters *ctr, unsigned int *flags,
-                              unsigned long long *totals, int last) {
-  hipLaunchKernelGGL(k_sweep_check, dim3(1), dim3(64), 0, s, ctr, flags, totals, last);
   return hipGetLastError();
 }
 
