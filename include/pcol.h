@@ -191,9 +191,9 @@ pcol_status pcol_set_stream(pcol_ctx *ctx, void *hip_stream);
  * cell and counted per cell): validates the data, computes
  * reach = 2 max r + 2 max|v| dt and a uniform grid of cell side >= reach *
  * cell_mult per axis, and keeps a cell-sorted copy of the start-of-step state
- * in the context.  Reads only.  Synchronises (reads back the reach and the
- * largest cell).  A call with the sphere count, box, dt and walls of the
- * context's last binning counts the spheres into that binning's grid during
+ * in the context.  Reads only.  Synchronises (waits for the verdict on the data
+ * and the grid).  When the context's last two binnings of this sphere count,
+ * box, dt and walls had one grid, a large call counts the spheres into it during
  * the reach pass and keeps those counts when this call's reach gives the same
  * grid (the grid is always the one this call's reach determines). */
 pcol_status pcol_bin(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box, double dt);
@@ -228,10 +228,11 @@ pcol_status pcol_advance(pcol_ctx *ctx, pcol_particles *p, const pcol_box *box, 
  * flight and wrap; p is updated in place.  partner (device int32[n], nullable):
  * the caller index of the sphere i collided with, or -1.  tcoll (device
  * double[n], nullable): contact time within the step, NaN if none.
- * stats (host, nullable).  Synchronises once after validation, once after sweep
- * 1 (and after binning for the binary32 filter), then once per sweep for a
- * short sweep list, or once per group of sweeps run on the device for a long
- * one.  On PCOL_E_SWEEPS p is left as it was (the end-of-step state is written
+ * stats (host, nullable).  Synchronises at its end, once for every further group
+ * of sweeps when the step takes more of them than were queued, and once before
+ * the pair tests in the first call of a shape (sphere count, box, dt, walls), for
+ * grids with fewer than 3 cells on an axis, and when the grid outgrows the
+ * context's cell arrays or gains the extent split.  On PCOL_E_SWEEPS p is left as it was (the end-of-step state is written
  * only once the sweeps are done). */
 pcol_status pcol_step(pcol_ctx *ctx, pcol_particles *p, const pcol_box *box, double dt, double e,
                       int32_t *partner, double *tcoll, pcol_stats *stats);

@@ -32,10 +32,9 @@ struct pcol_ctx {
   int *slot = nullptr;
   int *count = nullptr;
   int *start = nullptr;
-  int *blocksum = nullptr;
+  ScanState *scan = nullptr;
   int64_t cell_cap = 0;
-  CellCount *cellc = nullptr;  // per-cell counts of the detect kernels
-  int64_t cellc_cap = 0;
+  bool counts_dirty = false;  // a call stopped between counting the cells and their scan
 
   // sweep state
   int *cnt = nullptr;
@@ -49,11 +48,10 @@ struct pcol_ctx {
   OutRec *out = nullptr;
   int *partner_tmp = nullptr;
   double *tcoll_tmp = nullptr;
-  ReachOut *reach_d = nullptr;
-  ReachPart *reach_parts = nullptr;     // REACH_BLOCKS partial results of the reach pass
-  unsigned int *reach_phist = nullptr;  // REACH_BLOCKS partial extent histograms
+  ReachScratch reach{};
   SweepCounters *ctr_d = nullptr;
-  ReachOut *reach_h = nullptr;
+  StepPlan *plan_d = nullptr;  // the plan of the last binning, made on the device,
+  StepPlan *plan_h = nullptr;  // and in page-locked host memory
   StepReport *rep = nullptr;  // page-locked host memory that the step's last kernel writes
   int exact_sweeps = 0;       // some step's contacts overflowed the slots: sweeps that can search
   int sweep_guess = 5;        // sweeps the last step took: so many are queued, and one more
@@ -62,39 +60,22 @@ struct pcol_ctx {
   bool binned = false;
   int64_t binned_n = -1;
   const double *binned_x = nullptr;
-  Grid G{};
-  double reach = 0.0;
-  double vmax = 0.0, rmin = 0.0, rmax = 0.0;
   double binned_dt = 0.0;
-  // extent split: spheres with r + |v| dt > rho_c live in a second layer of
-  // cells; the first layer's pair test then needs cells of side 2 rho_c only
-  bool split = false;
-  double rho_c = INFINITY, rho_max = 0.0;
-  int wide_first = 0, n_wide = 0;  // sorted range of the second layer
-  int *wide_h = nullptr;           // pinned read-back of that range
-  bool bin_pending = false;        // maxcell and the range still in flight (bin_readback)
+  StepPlan plan{};                 // the last binning's, once the host has waited for it
   const Spin *spin = nullptr;      // set by pcol_step_spin for the step: its spins are validated
   int walls = 0;                   // set by pcol_step_walls for the step: bit k = walls on axis k
   // pcol_deposit: position check flag, and the element sort's scratch with its capacities
   unsigned int *dep_flag_h = nullptr;
   unsigned char *dep_buf = nullptr;  // carved by deposit_layout
   int64_t dep_cap = 0;
-  // bounds for the first layer's pair test: reach, speed and radius
-  double reach_pass = 0.0, vmax_pass = 0.0, rmax_pass = 0.0;
-  double band = 0.0;   // FP32 filter band in use (relative to r_i + r_j)
-  double h[3] = {0, 0, 0};
-  int maxcell = 0;
-  bool small = false;  // some axis has fewer than 3 cells
-  // the last binning's grid, tried first by the next call of the same shape
-  // (sphere count, box, step, walls): its reach pass then bins on it as well
-  bool plan_valid = false;
-  int64_t plan_n = -1;
-  double plan_L[3] = {0, 0, 0}, plan_dt = 0.0;
-  int plan_walls = 0;
-  Grid plan_G{};
-  double plan_rho_c = INFINITY;
+  // The last two plans of a shape (sphere count, box, step, walls): the kernels of
+  // a step are sized by the last one, and if both gave one grid the reach pass of
+  // a large step counts the spheres on it.
+  bool shape_valid = false, steady = false;
+  int64_t shape_n = -1;
+  double shape_L[3] = {0, 0, 0}, shape_dt = 0.0;
+  int shape_walls = 0;
   bool detect_timed = false;
-  int cpw_used = 0;  // home cells per workgroup of the last sweep-1 detect (0: exact search)
   unsigned long long *crank = nullptr;  // literal order (opts.order = 1): curve rank per sorted sphere
   struct BatchPlan *bp = nullptr;  // batched form (pcol_step_batched)
 };
@@ -221,10 +202,9 @@ double ms_between(hipEvent_t a, hipEvent_t b) {
 
 // The deposition's scratch carved out of one buffer, each part on a 256-B
 // boundary: element id and slot per sphere, the element-sorted records, the
-// per-element counts, starts and scan block sums, the scan's statistics word and
-// the position flag.
+// per-element counts and starts, the scan's words and the position flag.
 struct DepositLayout {
-  int64_t eid, slot, rec, cnt, start, bsum, ro, flag, bytes;
+  int64_t eid, slot, rec, cnt, start, scan, flag, bytes;
 };
 
 DepositLayout deposit_layout(int64_t n, int64_t ne, int comp) {
@@ -240,8 +220,11 @@ DepositLayout deposit_layout(int64_t n, int64_t ne, int comp) {
   L.rec = take(n * deposit_record_bytes(comp));
   L.cnt = take((ne + 1) * (int64_t)sizeof(int));
   L.start = take((ne + 1) * (int64_t)sizeof(int));
-  L.bsum = take((ne / 4096 + 2) * (int64_t)sizeof(int));
-  L.ro = take((int64_t)sizeof(ReachOut));
+  // 8 bytes a tile; not less than the 4 bytes a tile and 8,232 that the size limit
+  // of the fixed scratch is stated with
+  const int64_t words = (ne / SCAN_B + 2) * 8 + (int64_t)sizeof(ScanState);
+  const int64_t least = ((ne / 4096 + 2) * 4 + 255) / 256 * 256 + 8448;
+  L.scan = take(words > least ? words : least);
   L.flag = take((int64_t)sizeof(unsigned int));
   L.bytes = at;
   return L;
@@ -289,8 +272,11 @@ hipError_t deposit_run(DepositArgs &D, const DepositLayout &Lo, unsigned char *b
   D.cnt = (int *)(base + Lo.cnt);
   D.start = (int *)(base + Lo.start);
   unsigned int *flag = (unsigned int *)(base + Lo.flag);
+  ScanState *scan = (ScanState *)(base + Lo.scan);
   hipError_t e = launch_fill_i32(s, D.cnt, 0, D.nnode);
   if (e != hipSuccess) return e;
+  const int64_t words = 2 * ((D.nnode + SCAN_B - 1) / SCAN_B + 1);
+  if ((e = launch_fill_u32(s, (unsigned int *)scan, 0u, words + 2)) != hipSuccess) return e;
   if (D.n > 0) {  // the count checks the positions; nothing of the caller's is written yet
     if ((e = launch_fill_u32(s, flag, 0u, 1)) != hipSuccess) return e;
     if ((e = launch_deposit_count(s, D, flag)) != hipSuccess) return e;
@@ -303,8 +289,7 @@ hipError_t deposit_run(DepositArgs &D, const DepositLayout &Lo, unsigned char *b
       return hipSuccess;
     }
   }
-  if ((e = launch_scan(s, D.cnt, (int)D.nnode, D.start, (int *)(base + Lo.bsum),
-                       (ReachOut *)(base + Lo.ro))) != hipSuccess)
+  if ((e = launch_scan(s, D.cnt, (int)D.nnode, nullptr, D.start, scan, nullptr)) != hipSuccess)
     return e;
   return launch_deposit(s, D);
 }
@@ -372,16 +357,15 @@ pcol_status pcol_set_stream(pcol_ctx *ctx, void *hip_stream) {
 void pcol_destroy(pcol_ctx *ctx) {
   if (!ctx) return;
   void *dev[] = {ctx->rec,    ctx->rank,   ctx->cid,         ctx->slot,
-                 ctx->count,  ctx->start,  ctx->blocksum, ctx->cnt,      ctx->slot_t,
+                 ctx->count,  ctx->start,  ctx->scan, ctx->cnt,      ctx->slot_t,
                  ctx->slot_j, ctx->key_j,  ctx->key_t,  ctx->status,      ctx->out,
                  ctx->ovf,    ctx->partner_tmp, ctx->tcoll_tmp, ctx->list_a,
-                 ctx->reach_d, ctx->cellc, ctx->ctr_d, ctx->dep_buf,
-                 ctx->crank, ctx->reach_parts, ctx->reach_phist};
+                 ctx->ctr_d, ctx->dep_buf, ctx->crank, ctx->reach.parts, ctx->reach.hist,
+                 ctx->reach.phist, ctx->plan_d};
   for (void *p : dev)
     if (p) (void)hipFree(p);
-  if (ctx->reach_h) (void)hipHostFree(ctx->reach_h);
+  if (ctx->plan_h) (void)hipHostFree(ctx->plan_h);
   if (ctx->rep) (void)hipHostFree(ctx->rep);
-  if (ctx->wide_h) (void)hipHostFree(ctx->wide_h);
   if (ctx->dep_flag_h) (void)hipHostFree(ctx->dep_flag_h);
   for (hipEvent_t &e : ctx->ev)
     if (e) (void)hipEventDestroy(e);
@@ -441,13 +425,15 @@ pcol_status pcol_create(pcol_ctx **out, int64_t n_max, void *hip_stream, const p
   A(dalloc(&ctx->partner_tmp, n));
   A(dalloc(&ctx->tcoll_tmp, n));
   if (ctx->opts.order == 1) A(dalloc(&ctx->crank, n));
-  A(dalloc(&ctx->reach_d, 1));
-  A(dalloc(&ctx->reach_parts, REACH_BLOCKS));
-  A(dalloc(&ctx->reach_phist, (int64_t)REACH_BLOCKS * RHO_BINS));
+  A(dalloc(&ctx->plan_d, 1));
+  A(dalloc(&ctx->reach.parts, REACH_BLOCKS));
+  A(dalloc(&ctx->reach.hist, RHO_BINS));
+  A(dalloc(&ctx->reach.phist, (int64_t)REACH_BLOCKS * RHO_BINS));
+  if (e == hipSuccess)
+    e = hipMemsetAsync(ctx->reach.hist, 0, RHO_BINS * sizeof(unsigned int), ctx->stream);
   A(dalloc(&ctx->ctr_d, 1));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->reach_h, sizeof(ReachOut));
+  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->plan_h, sizeof(StepPlan));
   if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->rep, sizeof(StepReport));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->wide_h, 2 * sizeof(int));
   for (hipEvent_t &ev : ctx->ev)
     if (e == hipSuccess) e = hipEventCreate(&ev);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -459,20 +445,60 @@ pcol_status pcol_create(pcol_ctx **out, int64_t n_max, void *hip_stream, const p
   return PCOL_OK;
 }
 
-// Host copies of the largest cell occupancy and the second layer's range,
-// once the read-backs pcol_bin queued have landed (after a stream
-// synchronisation).
-static void bin_readback(pcol_ctx *ctx) {
-  if (!ctx->bin_pending) return;
-  ctx->maxcell = (int)ctx->reach_h->maxcell;
-  ctx->wide_first = ctx->split ? ctx->wide_h[0] : (int)ctx->binned_n;
-  ctx->n_wide = (int)ctx->binned_n - ctx->wide_first;
-  ctx->bin_pending = false;
+// The cell arrays for `cells` cells (of both layers), with room for a grid a
+// little finer; the counts start at zero.
+static pcol_status grow_cells(pcol_ctx *ctx, int64_t cells) {
+  if (cells + 2 <= ctx->cell_cap) return PCOL_OK;
+  PCOL_HIP(hipStreamSynchronize(ctx->stream));
+  if (ctx->count) (void)hipFree(ctx->count);
+  if (ctx->start) (void)hipFree(ctx->start);
+  if (ctx->scan) (void)hipFree(ctx->scan);
+  ctx->count = ctx->start = nullptr;
+  ctx->scan = nullptr;
+  ctx->cell_cap = 0;
+  if (ctx->bp) ctx->bp->captured = false;  // its graph holds the old cell arrays
+  const int64_t cap = cells + cells / 4 + 64;
+  hipError_t e = dalloc(&ctx->count, (size_t)cap);
+  if (e == hipSuccess) e = dalloc(&ctx->start, (size_t)cap + 1);
+  if (e == hipSuccess)
+    e = hipMalloc((void **)&ctx->scan, sizeof(ScanState) + (size_t)(cap / SCAN_B + 2) * 8);
+  if (e == hipSuccess) e = hipMemsetAsync(ctx->count, 0, (size_t)cap * sizeof(int), ctx->stream);
+  if (e == hipSuccess)
+    e = hipMemsetAsync(ctx->scan, 0, sizeof(ScanState) + (size_t)(cap / SCAN_B + 2) * 8,
+                       ctx->stream);
+  if (e != hipSuccess) return fail(ctx, PCOL_E_NOMEM, "cell arrays");
+  ctx->cell_cap = cap;
+  ctx->counts_dirty = false;
+  return PCOL_OK;
 }
 
-pcol_status pcol_bin(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box, double dt) {
-  pcol_status st = check_common(ctx, p, box, dt);
-  if (st != PCOL_OK) return st;
+static bool same_grid(const StepPlan &a, const StepPlan &b) {
+  return a.G.nc[0] == b.G.nc[0] && a.G.nc[1] == b.G.nc[1] && a.G.nc[2] == b.G.nc[2] &&
+         a.G.layer2 == b.G.layer2 && (!a.split || a.rho_c == b.rho_c);
+}
+
+// The host's turn after a wait: the plan's verdict and, if it stands, the plan.
+static pcol_status take_plan(pcol_ctx *ctx) {
+  const unsigned int err = ctx->plan_h->err;
+  if (err & PLAN_INVALID) return fail(ctx, PCOL_E_INVALID, "non-finite value, r <= 0 or m <= 0");
+  if (err & PLAN_POSITION) return fail(ctx, PCOL_E_INVALID, "position outside [0, L)");
+  if (err & PLAN_BOX)
+    return fail(ctx, PCOL_E_BOX, "box side <= 2 * reach: minimum image not unique");
+  ctx->steady = ctx->shape_valid && same_grid(ctx->plan, *ctx->plan_h);
+  ctx->plan = *ctx->plan_h;
+  ctx->shape_valid = true;
+  ctx->binned = true;
+  return PCOL_OK;
+}
+
+// Enqueue the binning of p.  ahead: everything at once, for a caller that looks
+// at the plan after its next wait (take_plan; PLAN_AGAIN asks it to bin once more
+// without `ahead`), if the last call says how large the kernels behind the plan
+// have to be: the same shape and no small grid, whose kernels are others.
+// Otherwise (ahead then false) it waits for the plan, checks it and makes room for
+// its cells before it queues the rest.
+static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box, double dt,
+                             bool &ahead) {
   ctx->binned = false;
   Particles P = to_dev(p);
   if (ctx->spin) {
@@ -481,258 +507,104 @@ pcol_status pcol_bin(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box
     P.wz = ctx->spin->wz;
   }
   hipStream_t s = ctx->stream;
-  // The grid of the last binning is tried first when this call has its shape
-  // (sphere count, box, step, walls): the reach pass then also takes every
-  // sphere's cell and slot on it (a2), and the plan is kept only if the reach
-  // now measured leads to the same grid and split extent; otherwise the counts
-  // are redone on the new grid below.  Either way the grid is the one the
-  // reach of this call determines.
-  const bool tried = ctx->plan_valid && ctx->plan_n == p->n && ctx->plan_dt == dt &&
-                     ctx->plan_walls == ctx->walls && ctx->plan_L[0] == box->len[0] &&
-                     ctx->plan_L[1] == box->len[1] && ctx->plan_L[2] == box->len[2] &&
-                     (int64_t)(ctx->plan_G.layer2 ? 2 * ctx->plan_G.ncell : ctx->plan_G.ncell) +
-                             2 <= ctx->cell_cap;
-  ctx->plan_valid = false;
-  // a1: reach and data validity (one read-back); the histogram is accumulated
-  // into zeros, the other fields are written by the reduction
-  PCOL_HIP(hipMemsetAsync(ctx->reach_d, 0, sizeof(ReachOut), s));
+  // room for a usual grid: a cell holds some 13 spheres, and a split grid has two layers
+  if (ctx->cell_cap == 0) {
+    const pcol_status st = grow_cells(ctx, p->n / 4);
+    if (st != PCOL_OK) return st;
+  }
+  if (ctx->counts_dirty) {
+    PCOL_HIP(hipMemsetAsync(ctx->count, 0, (size_t)ctx->cell_cap * sizeof(int), s));
+    ctx->counts_dirty = false;
+  }
+  const bool shape = ctx->shape_valid && ctx->shape_n == p->n && ctx->shape_dt == dt &&
+                     ctx->shape_walls == ctx->walls && ctx->shape_L[0] == box->len[0] &&
+                     ctx->shape_L[1] == box->len[1] && ctx->shape_L[2] == box->len[2];
+  if (!shape) ctx->shape_valid = ctx->steady = false;
+  ahead = ahead && ctx->shape_valid && !ctx->plan.small && p->n > 0;
+  ctx->shape_n = p->n;
+  ctx->shape_dt = dt;
+  ctx->shape_walls = ctx->walls;
+  for (int a = 0; a < 3; ++a) ctx->shape_L[a] = box->len[a];
+  ctx->binned_n = p->n;
+  ctx->binned_dt = dt;
+  PlanArgs A{};
+  A.n = p->n;
+  A.cell_cap = ctx->cell_cap;
+  for (int a = 0; a < 3; ++a) A.L[a] = box->len[a];
+  A.dt = dt;
+  A.cell_mult = ctx->opts.cell_mult;
+  A.band_rel = ctx->opts.band_rel;
+  A.quantile = ctx->opts.split_quantile;
+  A.home_cells = ctx->opts.home_cells;
+  A.fp32 = ctx->opts.filter == 1;
+  A.walls = ctx->walls;
+  A.allow_small = !ahead;
+  A.allow_split = !ahead || ctx->plan.split;
+  A.tried_rho_c = INFINITY;
+  // Counting in the reach pass saves reading the spheres once more (0.66 ms for both
+  // at 16M spheres in random order, against 0.22 + 0.64 apart) but is thrown away
+  // if the grid changes, so only where the last two steps had the same one, and
+  // where a pass over the spheres costs more than a launch.
+  const bool tried = ctx->steady && p->n >= (1 << 18) && ctx->plan.cells + 2 <= ctx->cell_cap;
+  const StepPlan last = ctx->plan;
+  if (tried) {
+    A.tried = 1;
+    for (int a = 0; a < 3; ++a) A.tried_nc[a] = last.G.nc[a];
+    A.tried_layer2 = last.G.layer2;
+    A.tried_rho_c = last.rho_c;
+  }
   // the extent histogram only picks the split extent: above 2^20 spheres it
   // samples one sphere in 16 (the quantile of a million samples is as good)
   const int hist_shift = p->n >= (1 << 20) ? 4 : 0;
-  if (tried) {
-    const Grid &T = ctx->plan_G;
-    PCOL_HIP(launch_fill_i32(s, ctx->count, 0, T.layer2 ? 2 * T.ncell : T.ncell));
-    PCOL_HIP(launch_reach(s, P, box->len, dt, hist_shift, ctx->reach_d, ctx->reach_parts,
-                          ctx->reach_phist, &T, ctx->plan_rho_c, ctx->cid, ctx->slot,
-                          ctx->count));
-  } else {
-    PCOL_HIP(launch_reach(s, P, box->len, dt, hist_shift, ctx->reach_d, ctx->reach_parts,
-                          ctx->reach_phist));
-  }
-  PCOL_HIP(hipMemcpyAsync(ctx->reach_h, ctx->reach_d, sizeof(ReachOut), hipMemcpyDeviceToHost, s));
-  PCOL_HIP(hipStreamSynchronize(s));
-  const ReachOut ro = *ctx->reach_h;
-  if (ro.bad & 1u) return fail(ctx, PCOL_E_INVALID, "non-finite value, r <= 0 or m <= 0");
-  if (ro.bad & 2u) return fail(ctx, PCOL_E_INVALID, "position outside [0, L)");
-  double v2, rmax, rmin;
-  memcpy(&v2, &ro.v2max, sizeof(double));
-  memcpy(&rmax, &ro.rmax, sizeof(double));
-  memcpy(&rmin, &ro.rmin, sizeof(double));
-  const double reach = 2.0 * rmax + 2.0 * sqrt(v2) * dt;
-  for (int a = 0; a < 3; ++a)
-    if (!(box->len[a] > 2.0 * reach))
-      return fail(ctx, PCOL_E_BOX, "box side <= 2 * reach: minimum image not unique");
-  double rho_max;
-  memcpy(&rho_max, &ro.rhomax, sizeof(double));
-  // Extent split: the first layer holds the spheres whose extent is at most
-  // rho_c, the upper edge of the histogram bin where the split quantile of the
-  // extents falls; pairs of them are at most 2 rho_c apart when they can touch.
-  // Used only when it shrinks the cells enough to pay for the separate search
-  // of the others, and the grid keeps 3 cells per axis.
-  double rho_c = INFINITY;
-  const double q = ctx->opts.split_quantile;
-  double sampled = 0.0;
-  for (int k = 0; k < RHO_BINS; ++k) sampled += ro.hist[k];
-  if (q > 0.0 && q < 1.0 && p->n >= 4096) {
-    const double target = ceil(q * sampled);
-    double cum = 0.0;
-    for (int k = 0; k < RHO_BINS - 1; ++k) {
-      cum += ro.hist[k];
-      if (cum >= target) {
-        // upper edge of bin k: the lower edge of bin k + 1
-        const uint64_t top = (uint64_t)((1023 - 64) * 16 + k + 1);
-        const uint64_t bits = top << 48;
-        memcpy(&rho_c, &bits, sizeof(double));
-        break;
-      }
+  ctx->counts_dirty = true;  // until the scan is queued behind a plan that stands
+  if (tried)
+    PCOL_HIP(launch_reach(s, P, dt, hist_shift, A, ctx->reach, ctx->ctr_d, ctx->scan, ctx->plan_d,
+                          ctx->plan_h, &last.G, last.rho_c, ctx->cid, ctx->slot, ctx->count));
+  else
+    PCOL_HIP(launch_reach(s, P, dt, hist_shift, A, ctx->reach, ctx->ctr_d, ctx->scan, ctx->plan_d,
+                          ctx->plan_h));
+  int cells = last.cells;
+  if (!ahead) {
+    PCOL_HIP(hipStreamSynchronize(s));
+    if (ctx->plan_h->err == PLAN_AGAIN) {  // more cells than there is room for
+      const pcol_status st = grow_cells(ctx, ctx->plan_h->cells);
+      if (st != PCOL_OK) return st;
+      ctx->steady = false;
+      return bin_queue(ctx, p, box, dt, ahead);
     }
-    if (!(2.0 * rho_c < 0.85 * reach)) rho_c = INFINITY;
-    for (int a = 0; a < 3 && isfinite(rho_c); ++a)
-      if (box->len[a] / (2.0 * rho_c * ctx->opts.cell_mult * (1.0 + 1e-9)) < 3.0) rho_c = INFINITY;
+    const pcol_status st = take_plan(ctx);
+    if (st != PCOL_OK) return st;
+    cells = ctx->plan.cells;
   }
-  const bool split = isfinite(rho_c);
-  const double reach_pass = split ? 2.0 * rho_c : reach;
-  // grid: cell side >= (split ? 2 rho_c : reach) * cell_mult, at most 2^26 cells per layer
-  Grid G{};
-  double cell = reach_pass * ctx->opts.cell_mult;
-  if (!(cell > 0.0)) cell = box->len[0];  // no motion and no size: one cell
-  for (;;) {
-    int64_t ncell = 1;
-    for (int a = 0; a < 3; ++a) {
-      double q3 = floor(box->len[a] / (cell * (1.0 + 1e-9)));
-      if (!(q3 >= 1.0)) q3 = 1.0;
-      if (q3 > 1024.0) q3 = 1024.0;
-      G.nc[a] = (int)q3;
-      ncell *= G.nc[a];
-    }
-    if (ncell <= (1 << 26)) {
-      G.ncell = (int)ncell;
-      break;
-    }
-    cell *= 1.25;
-  }
-  ctx->small = false;
-  G.walls = ctx->walls;
-  for (int a = 0; a < 3; ++a) {
-    const bool wall = (ctx->walls >> a) & 1;
-    G.L[a] = box->len[a];
-    // between walls there is no minimum image and no periodic image shift
-    G.halfL[a] = wall ? INFINITY : 0.5 * box->len[a];
-    G.sL[a] = wall ? 0.0 : box->len[a];
-    G.inv_h[a] = (double)G.nc[a] / box->len[a];
-    G.h[a] = box->len[a] / G.nc[a];
-    ctx->h[a] = G.h[a];
-    if (G.nc[a] < 3) ctx->small = true;
-  }
-  G.layer2 = split ? G.ncell : 0;
-  G.rho_max = split ? rho_max : 0.0;
-  G.inv_row = 1.0 / G.nc[0];
-  G.inv_layer = 1.0 / ((double)G.nc[0] * G.nc[1]);
-  const int cells_all = split ? 2 * G.ncell : G.ncell;
-  if ((int64_t)cells_all + 2 > ctx->cell_cap) {
-    if (ctx->count) (void)hipFree(ctx->count);
-    if (ctx->start) (void)hipFree(ctx->start);
-    if (ctx->blocksum) (void)hipFree(ctx->blocksum);
-    ctx->count = ctx->start = ctx->blocksum = nullptr;
-    ctx->cell_cap = 0;
-    if (ctx->bp) ctx->bp->captured = false;  // its graph holds the old cell arrays
-    const int64_t cap = (int64_t)cells_all + 2;
-    hipError_t e = dalloc(&ctx->count, (size_t)cap);
-    if (e == hipSuccess) e = dalloc(&ctx->start, (size_t)cap + 1);
-    if (e == hipSuccess) e = dalloc(&ctx->blocksum, (size_t)(cap / 4096 + 2));
-    if (e != hipSuccess) return fail(ctx, PCOL_E_NOMEM, "cell arrays");
-    ctx->cell_cap = cap;
-  }
-  // a2-a4: counting sort into cell-sorted records (the counts already taken by
-  // the reach pass when the tried grid is this one)
-  const bool binned_on_plan = tried && ctx->plan_G.nc[0] == G.nc[0] &&
-                              ctx->plan_G.nc[1] == G.nc[1] && ctx->plan_G.nc[2] == G.nc[2] &&
-                              ctx->plan_G.layer2 == G.layer2 &&
-                              (!split || ctx->plan_rho_c == rho_c);
-  if (!binned_on_plan) {
-    PCOL_HIP(launch_fill_i32(s, ctx->count, 0, cells_all));
-    PCOL_HIP(launch_cell_hist(s, P, G, dt, rho_c, ctx->cid, ctx->slot, ctx->count));
-  }
-  PCOL_HIP(launch_scan(s, ctx->count, cells_all, ctx->start, ctx->blocksum, ctx->reach_d));
-  PCOL_HIP(launch_scatter(s, P, ctx->cid, ctx->slot, ctx->start, ctx->rec, ctx->rank, nullptr));
-  if (ctx->opts.order == 1) {
-    // the literal order's ranks on the curve grid: cell side >= the reach
-    // (2 max r + 2 max|v| dt, whatever grid the pair tests use), at most 2048
-    // cells per axis
-    CurveGrid C{};
-    for (int a = 0; a < 3; ++a) {
-      double q3 = floor(box->len[a] / (reach * (1.0 + 1e-9)));
-      if (!(q3 >= 1.0)) q3 = 1.0;
-      if (q3 > 2048.0) q3 = 2048.0;
-      C.nc[a] = (int)q3;
-      C.h[a] = box->len[a] / C.nc[a];
-    }
-    PCOL_HIP(launch_curve_rank(s, ctx->rec, (int)p->n, C, ctx->crank));
-  }
-  // the largest cell and the second layer's range are read back without a
-  // wait; they are read after the next synchronisation (bin_readback)
-  PCOL_HIP(hipMemcpyAsync(&ctx->reach_h->maxcell, &ctx->reach_d->maxcell, sizeof(unsigned int),
-                          hipMemcpyDeviceToHost, s));
-  if (split)
-    PCOL_HIP(hipMemcpyAsync(ctx->wide_h, ctx->start + G.layer2, sizeof(int), hipMemcpyDeviceToHost, s));
-  ctx->bin_pending = true;
-  ctx->G = G;
-  ctx->reach = reach;
-  ctx->vmax = sqrt(v2);
-  ctx->rmin = rmin;
-  ctx->rmax = rmax;
-  ctx->binned_dt = dt;
-  ctx->split = split;
-  ctx->rho_c = rho_c;
-  ctx->rho_max = rho_max;
-  // first-layer bounds: extent <= rho_c gives |v| <= (rho_c - r_min) / dt, r <= rho_c
-  ctx->reach_pass = reach_pass;
-  ctx->vmax_pass = split ? std::min(ctx->vmax, (rho_c - rmin) / dt) : ctx->vmax;
-  ctx->rmax_pass = split ? std::min(rmax, rho_c) : rmax;
-  ctx->binned = true;
-  ctx->binned_n = p->n;
-  ctx->binned_x = p->x;
-  ctx->plan_valid = true;
-  ctx->plan_n = p->n;
-  ctx->plan_dt = dt;
-  ctx->plan_walls = ctx->walls;
-  for (int a = 0; a < 3; ++a) ctx->plan_L[a] = box->len[a];
-  ctx->plan_G = G;
-  ctx->plan_rho_c = rho_c;
+  // a2-a4: counting sort into cell-sorted records
+  PCOL_HIP(launch_cell_hist(s, P, ctx->plan_d, dt, tried ? last.cells : 0, ctx->cid, ctx->slot,
+                            ctx->count));
+  PCOL_HIP(launch_scan(s, ctx->count, cells, ctx->plan_d, ctx->start, ctx->scan,
+                       &ctx->ctr_d->maxcell));
+  ctx->counts_dirty = ahead;
+  PCOL_HIP(launch_scatter(s, P, ctx->cid, ctx->slot, ctx->start, ctx->rec, ctx->rank, ctx->cnt,
+                          nullptr, &ctx->plan_d->err));
+  if (ctx->opts.order == 1)
+    PCOL_HIP(launch_curve_rank(s, ctx->rec, (int)p->n, ctx->plan_d, ctx->crank));
   return PCOL_OK;
+}
+
+pcol_status pcol_bin(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box, double dt) {
+  pcol_status st = check_common(ctx, p, box, dt);
+  if (st != PCOL_OK) return st;
+  bool ahead = false;
+  return bin_queue(ctx, p, box, dt, ahead);
 }
 
 static pcol_status check_binned(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box,
                                 double dt) {
   if (!ctx->binned || ctx->binned_n != p->n)
     return fail(ctx, PCOL_E_STATE, "pcol_bin must run first on the same particle set");
-  if (ctx->G.walls) return fail(ctx, PCOL_E_STATE, "the last binning was for a box with walls");
+  if (ctx->plan.G.walls) return fail(ctx, PCOL_E_STATE, "the last binning was for a box with walls");
   if (dt != ctx->binned_dt) return fail(ctx, PCOL_E_STATE, "dt differs from pcol_bin");
   for (int a = 0; a < 3; ++a)
-    if (box->len[a] != ctx->G.L[a]) return fail(ctx, PCOL_E_STATE, "box differs from pcol_bin");
+    if (box->len[a] != ctx->plan.G.L[a]) return fail(ctx, PCOL_E_STATE, "box differs from pcol_bin");
   return PCOL_OK;
-}
-
-// Contact-distance factor of the FP32 filter.  Bounds (unit roundoff u = 2^-24)
-// on the FP32 errors of the filter quantities for any pair the binary64 rule
-// can keep (|d| <= reach, |u| <= 2 vmax, coordinates within 1.5 h of the home
-// cell centre):
-//   separation   Dd = (2 h + reach) u       relative velocity  Du = 4 vmax u
-//   c' = |d|^2 - (s k)^2:  2 sqrt3 reach Dd + 3 u reach^2 + 6 u (2 rmax k)^2
-//   b' dt2f = d.u dt2f:    (sqrt3 (reach Du + 2 vmax Dd) + 6 u reach vmax) 2 dt (1 + 2^-11)
-// The inflation (k^2 - 1) s_min^2 >= 2 (k - 1) s_min^2 must cover their sum; k
-// is chosen so that it covers twice the sum, and never below 1 + band_rel.
-static double fp32_band(const pcol_ctx *ctx, double dt) {  // returns the band
-  const double u = 0x1.0p-24;
-  double h = ctx->h[0];
-  for (int a = 1; a < 3; ++a) h = ctx->h[a] > h ? ctx->h[a] : h;
-  const double R = ctx->reach_pass, V = ctx->vmax_pass, smin = 2.0 * ctx->rmin;
-  const double k0 = 1.0 + ctx->opts.band_rel + 1e-3;  // generous k for the radius term
-  const double Dd = (2.0 * h + R) * u, Du = 4.0 * V * u;
-  const double ec = 2.0 * sqrt(3.0) * R * Dd + 3.0 * u * R * R +
-                    6.0 * u * (2.0 * ctx->rmax_pass * k0) * (2.0 * ctx->rmax_pass * k0);
-  const double eb = (sqrt(3.0) * (R * Du + 2.0 * V * Dd) + 6.0 * u * R * V) * 2.0 * dt *
-                    (1.0 + 0x1.0p-11);
-  const double need = 2.0 * (ec + eb) / (2.0 * smin * smin);
-  return ctx->opts.band_rel > need ? ctx->opts.band_rel : need;
-}
-
-// Tolerance of the binary64 Gram filter (filter 0).  The filter evaluates
-// g = beta_i + <P_i, Q_j> (seven FMAs from beta_i) and passes the pair when
-// g <= fl(tol - beta_j); in real numbers that is F = g + beta_j <= tol.  For a
-// pair the rule keeps, the real F is at most
-// E0 = 3 eps ((reach^2 + (2 r_max)^2) + reach 2 v_max dt2) (the binary64 argument:
-// the kept root c / (-b + sqrt D) <= dt gives c <= 2 |b| dt (1 + 6 eps) < |b| dt2).
-// The evaluation differs from the real F by
-//  * the image shift of the candidate: one rounding per axis of a value below
-//    L + h, so the separation d is off by at most delta = 2 eps (Lmax + h), which
-//    moves F by at most delta (2 reach + 2 v_max dt2) + delta^2;
-//  * beta_i, beta_j, Q, (a few roundings each, <= 6 eps relative) and the seven
-//    FMAs of the sum (<= 7 eps of the sum of magnitudes): at most
-//    16 eps (2 B + S) with B, S the bounds of |beta| and sum_k |P_k Q_k| for
-//    |x| <= X, the norm of the box sides each lengthened by a cell;
-//  * the threshold's one rounding, at most eps (tol + |beta_j|): the eps tol part
-//    is covered by the factor two below, the eps B part by a 17th eps.
-// The tolerance is twice the sum.
-static double gram64_tolerance(double X, double h, double R, double V, double r, double Lmax,
-                               double dt2) {
-  const double eps = 0x1.0p-53;
-  X *= 1.0 + 1e-6;
-  const double B = X * X + dt2 * X * V + r * r;
-  const double S = X * (2.0 * X + dt2 * V) + V * dt2 * X + 2.0 * r * r;
-  const double E0 = 3.0 * eps * ((R * R + 4.0 * r * r) + R * 2.0 * V * dt2);
-  const double delta = 2.0 * eps * (Lmax + h);
-  const double Epos = delta * (2.0 * R + 2.0 * V * dt2) + delta * delta;
-  const double E = 17.0 * eps * (2.0 * B + S);
-  return 2.0 * (E0 + Epos + E);
-}
-
-// Norm of the box sides, each lengthened by a cell: bounds every position and
-// periodic image that the pair tests meet.
-static double grid_norm(const Grid &G) {
-  double q = 0.0;
-  for (int a = 0; a < 3; ++a) q += (G.L[a] + G.h[a]) * (G.L[a] + G.h[a]);
-  return sqrt(q);
 }
 
 // sweep 1: keys of all spheres (all active) into ctx->key_j / key_t (sorted
@@ -740,23 +612,14 @@ static double grid_norm(const Grid &G) {
 static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long *crank) {
   hipStream_t s = ctx->stream;
   const int n = (int)ctx->binned_n;
-  if (!ctx->small) {
-    if (ctx->G.ncell > ctx->cellc_cap) {
-      if (ctx->cellc) (void)hipFree(ctx->cellc);
-      ctx->cellc = nullptr;
-      ctx->cellc_cap = 0;
-      if (dalloc(&ctx->cellc, (size_t)ctx->G.ncell) != hipSuccess)
-        return fail(ctx, PCOL_E_NOMEM, "cell counts");
-      ctx->cellc_cap = ctx->G.ncell;
-    }
+  // sized by the last plan that the host has seen: this binning's, or for a step
+  // that has not waited yet the one before it (which then had no small grid, and a
+  // split grid if this one has)
+  const StepPlan &pl = ctx->plan;
+  const unsigned int *err = &ctx->plan_d->err;
+  const Grid *G = &ctx->plan_d->G;
+  if (!pl.small) {
     DetectArgs A{};
-    A.cellc = ctx->cellc;
-    // sparse cells (the split grid holds about 13 spheres per cell at 16M): four
-    // cells per workgroup, so their survivors are decided together; opts.home_cells
-    // overrides the choice
-    A.cpw = ctx->opts.home_cells > 0 ? ctx->opts.home_cells
-                                     : (n < 24 * (int64_t)ctx->G.ncell ? 4 : 1);
-    ctx->cpw_used = A.cpw;
     A.rec = ctx->rec;
     A.start = ctx->start;
     A.cnt = ctx->cnt;
@@ -764,51 +627,25 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     A.slot_j = ctx->slot_j;
     A.ctr = ctx->ctr_d;
     A.n = n;
-    A.G = ctx->G;
+    A.K = ctx->K;
+    A.plan = ctx->plan_d;
     A.dt = dt;
     A.dt2 = 2.0 * dt * (1.0 + 0x1.0p-20);
-    {
-      // 16 eps (reach^2 + (2 rmax)^2 + reach * 2 vmax * dt2): twice the bound on the
-      // differences between the filter's FMA values and the rule's b, c (pair64)
-      const double R = ctx->reach_pass, smax = 2.0 * ctx->rmax_pass;
-      A.tol = 16.0 * 0x1.0p-53 * (R * R + smax * smax + R * 2.0 * ctx->vmax_pass * A.dt2);
-      double h = ctx->h[0], Lmax = ctx->G.L[0];
-      for (int a = 1; a < 3; ++a) {
-        h = ctx->h[a] > h ? ctx->h[a] : h;
-        Lmax = ctx->G.L[a] > Lmax ? ctx->G.L[a] : Lmax;
-      }
-      A.tol64 = gram64_tolerance(grid_norm(ctx->G), h, R, ctx->vmax_pass, ctx->rmax_pass, Lmax, A.dt2);
-      // pairs with a sphere above the split extent: |d| up to the full reach
-      const double Rw = ctx->reach, sw = 2.0 * ctx->rmax;
-      A.tol_wide = 16.0 * 0x1.0p-53 * (Rw * Rw + sw * sw + Rw * 2.0 * ctx->vmax * A.dt2);
-      A.rho_c = ctx->rho_c;
-    }
-    A.K = ctx->K;
-    A.fp32 = ctx->opts.filter == 1;
-    ctx->band = A.fp32 ? fp32_band(ctx, dt) : 0.0;
-    // round the factor up so the float never shrinks the inflation
-    const double kb = 1.0 + ctx->band;
-    A.kband = (float)kb;
-    if ((double)A.kband < kb) A.kband = nextafterf(A.kband, 2.0f);
-    A.dt2f = (float)(2.0 * dt * (1.0 + 0x1.0p-12));
-    PCOL_HIP(launch_fill_i32(s, ctx->cnt, 0, n));
     if (ctx->opts.timing) PCOL_HIP(hipEventRecord(ctx->ev[5], s));
-    PCOL_HIP(launch_detect_half(s, A));
-    PCOL_HIP(launch_cell_counts(s, ctx->cellc, detect_half_blocks(A), ctx->ctr_d));
+    PCOL_HIP(launch_detect_half(s, A, ctx->opts.filter == 1,
+                                (pl.G.ncell + pl.cpw - 1) / (pl.cpw > 0 ? pl.cpw : 1)));
     // spheres of large extent: exact search of their wider neighbourhood
-    if (ctx->split) PCOL_HIP(launch_detect_wide(s, A, ctx->start + ctx->G.layer2, n));
+    if (pl.split) PCOL_HIP(launch_detect_wide(s, A));
     if (ctx->opts.timing) PCOL_HIP(hipEventRecord(ctx->ev[6], s));
     ctx->detect_timed = true;
     PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
-                             ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, nullptr, &ctx->G,
-                             crank));
+                             ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err, G, crank));
     PCOL_HIP(launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
-                                 ctx->G, dt, nullptr, ctx->key_j, ctx->key_t, nullptr, crank));
+                                 G, dt, nullptr, ctx->key_j, ctx->key_t, nullptr, err, crank));
   } else {
     // fewer than 3 cells on some axis: exact search for every sphere
-    ctx->cpw_used = 0;
-    PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, -1, ctx->rec, ctx->start, ctx->G, dt,
-                                 nullptr, ctx->key_j, ctx->key_t, nullptr, crank));
+    PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, -1, ctx->rec, ctx->start, G, dt,
+                                 nullptr, ctx->key_j, ctx->key_t, nullptr, err, crank));
   }
   return PCOL_OK;
 }
@@ -822,14 +659,16 @@ pcol_status pcol_detect(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *
   hipStream_t s = ctx->stream;
   const int n = (int)p->n;
   if (n == 0) return PCOL_OK;
-  PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
   if (!active) {
+    PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
+    PCOL_HIP(launch_fill_i32(s, ctx->cnt, 0, n));
     if ((st = detect_all(ctx, dt, nullptr)) != PCOL_OK) return st;
   } else {
     PCOL_HIP(launch_status_from_active(s, active, ctx->rec, n, ctx->status));
     PCOL_HIP(launch_fill_i32(s, ctx->key_j, -1, n));
-    PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, ST_ACTIVE, ctx->rec, ctx->start, ctx->G,
-                                 dt, ctx->status, ctx->key_j, ctx->key_t, nullptr));
+    PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, ST_ACTIVE, ctx->rec, ctx->start,
+                                 &ctx->plan_d->G, dt, ctx->status, ctx->key_j, ctx->key_t, nullptr,
+                                 &ctx->plan_d->err));
   }
   PCOL_HIP(launch_export_keys(s, n, ctx->rec, ctx->key_j, ctx->key_t,
                               active ? ctx->status : nullptr, key_out, tmin_out));
@@ -844,7 +683,7 @@ pcol_status pcol_resolve(pcol_ctx *ctx, pcol_particles *p, const pcol_box *box, 
   if (!(e >= 0.0 && e <= 1.0)) return fail(ctx, PCOL_E_INVALID, "e outside [0, 1]");
   if ((st = check_binned(ctx, p, box, dt)) != PCOL_OK) return st;
   if (p->n > 0 && (!key || !active)) return fail(ctx, PCOL_E_INVALID, "key or active is null");
-  PCOL_HIP(launch_resolve_public(ctx->stream, (int)p->n, ctx->rec, ctx->rank, ctx->G, dt, e, key,
+  PCOL_HIP(launch_resolve_public(ctx->stream, (int)p->n, ctx->rec, ctx->rank, ctx->plan.G, dt, e, key,
                                  to_dev(p), active, partner, tcoll, (long long *)n_pairs_dev));
   return PCOL_OK;
 }
@@ -865,11 +704,12 @@ static SweepArgs sweep_args(const pcol_ctx *ctx, const Particles &P, double dt, 
   SweepArgs W{};
   W.n = (int)P.n;
   W.K = ctx->K;
-  W.small = ctx->small;
-  W.exact = ctx->small || ctx->exact_sweeps;
+  W.small = ctx->plan.small;
+  W.exact = ctx->plan.small || ctx->exact_sweeps;
   W.rec = ctx->rec;
   W.start = ctx->start;
-  W.G = ctx->G;
+  W.G = &ctx->plan_d->G;
+  W.err = &ctx->plan_d->err;
   W.dt = dt;
   W.e = e;
   W.mass = P.m;
@@ -924,7 +764,11 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
   hipStream_t s = ctx->stream;
   const bool timing = ctx->opts.timing != 0;
   if (timing) PCOL_HIP(hipEventRecord(ctx->ev[0], s));
-  if ((st = pcol_bin(ctx, p, box, dt)) != PCOL_OK) return st;
+  // The binning is queued ahead of its plan where that can be done.  If the plan
+  // turns out not to fit, nothing has run, and the step is queued again behind a
+  // wait.
+  bool ahead = true;
+  if ((st = bin_queue(ctx, p, box, dt, ahead)) != PCOL_OK) return st;
   if (timing) PCOL_HIP(hipEventRecord(ctx->ev[1], s));
   const int n = (int)p->n;
   int32_t *part = partner ? partner : ctx->partner_tmp;
@@ -934,7 +778,6 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
   unsigned long long contacts = 0ull, recheck = 0ull, tests = 0ull;
   double ms_detect = 0.0;
   if (n > 0) {
-    PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
     // sweep 1: every contact within dt, then the earliest partner of each sphere
     ctx->detect_timed = false;
     if ((st = detect_all(ctx, dt, crank)) != PCOL_OK) return st;
@@ -957,9 +800,23 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
       const int begin = first ? 0 : 1, end = begin + group;
       PCOL_HIP(queue_sweeps(ctx, W, s, end, first));
       if (timing) PCOL_HIP(hipEventRecord(ctx->ev[3], s));
-      PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G, nullptr,
-                             ctx->ctr_d, end, W.exact != 0, ctx->rep));
+      PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->plan_d,
+                             ctx->start, nullptr, ctx->ctr_d, end, W.exact != 0,
+                             &ctx->plan_d->err, ctx->rep));
       PCOL_HIP(hipStreamSynchronize(s));
+      if (ahead) {
+        ahead = false;
+        if (ctx->plan_h->err == PLAN_AGAIN) {
+          if ((st = bin_queue(ctx, p, box, dt, ahead)) != PCOL_OK) return st;
+          if ((st = detect_all(ctx, dt, crank)) != PCOL_OK) return st;
+          W = sweep_args(ctx, P, dt, e);
+          W.crank = crank;
+          if (spin) W.spin = *spin;
+          continue;
+        }
+        if ((st = take_plan(ctx)) != PCOL_OK) return st;
+        ctx->counts_dirty = false;
+      }
       if (!W.exact && ctx->rep->n_overflow) {  // nothing ran: again, with the exact search
         W.exact = ctx->exact_sweeps = 1;
         continue;
@@ -977,7 +834,6 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
       first = false;
     }
     ctx->sweep_guess = (int)std::min(sweeps, (int64_t)MAX_QUEUE);
-    bin_readback(ctx);
     contacts = ctx->rep->contacts / 2ull;
     recheck = ctx->rep->recheck;
     tests = ctx->rep->tests;
@@ -990,26 +846,23 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
     }
   }
   if (stats) {
-    if (ctx->bin_pending) {  // an empty step: nothing waited for the read-backs yet
-      PCOL_HIP(hipStreamSynchronize(s));
-      bin_readback(ctx);
-    }
     memset(stats, 0, sizeof(*stats));
     stats->n_pairs = pairs;
     stats->n_sweeps = sweeps;
     stats->contacts = (int64_t)contacts;
     stats->n_overflow = ovf_total;
     stats->n_recheck = (int64_t)recheck;
-    stats->band = ctx->band;
+    const StepPlan &pl = ctx->plan;
+    stats->band = pl.band;
     for (int a = 0; a < 3; ++a) {
-      stats->nc[a] = ctx->G.nc[a];
-      stats->h[a] = ctx->h[a];
+      stats->nc[a] = pl.G.nc[a];
+      stats->h[a] = pl.G.h[a];
     }
-    stats->max_cell = ctx->maxcell;
-    stats->home_cells = ctx->cpw_used;
-    stats->reach = ctx->reach;
-    stats->n_wide = ctx->n_wide;
-    stats->rho_c = ctx->split ? ctx->rho_c : 0.0;
+    stats->max_cell = n > 0 ? (int)ctx->rep->maxcell : 0;
+    stats->home_cells = n > 0 ? pl.cpw : 0;
+    stats->reach = pl.reach;
+    stats->n_wide = n > 0 ? n - ctx->rep->wide_first : 0;
+    stats->rho_c = pl.split ? pl.rho_c : 0.0;
     stats->pair_tests = (int64_t)tests;
     if (timing && n > 0) {
       stats->ms_bin = ms_between(ctx->ev[0], ctx->ev[1]);
@@ -1300,19 +1153,8 @@ static pcol_status batch_plan(pcol_ctx *ctx, int nbox, const int64_t *box_off,
   PCOL_HIP(hipMemcpyAsync(bp->gtab, bp->gtab_h.data(), nbox * sizeof(Grid), hipMemcpyHostToDevice, s));
   PCOL_HIP(hipMemcpyAsync(bp->cell_base, bp->cell_base_h.data(), (nbox + 1) * sizeof(int),
                           hipMemcpyHostToDevice, s));
-  if (total + 2 > ctx->cell_cap) {
-    if (ctx->count) (void)hipFree(ctx->count);
-    if (ctx->start) (void)hipFree(ctx->start);
-    if (ctx->blocksum) (void)hipFree(ctx->blocksum);
-    ctx->count = ctx->start = ctx->blocksum = nullptr;
-    ctx->cell_cap = 0;
-    const int64_t cap = total + 2;
-    hipError_t a = dalloc(&ctx->count, (size_t)cap);
-    if (a == hipSuccess) a = dalloc(&ctx->start, (size_t)cap + 1);
-    if (a == hipSuccess) a = dalloc(&ctx->blocksum, (size_t)(cap / 4096 + 2));
-    if (a != hipSuccess) return fail(ctx, PCOL_E_NOMEM, "cell arrays");
-    ctx->cell_cap = cap;
-  }
+  const pcol_status room = grow_cells(ctx, total);
+  if (room != PCOL_OK) return room;
   PCOL_HIP(hipStreamSynchronize(s));
   bp->tables = true;
   bp->cell_mult = mult;
@@ -1323,7 +1165,7 @@ static SweepArgs batch_sweep_args(const pcol_ctx *ctx, const Particles &P, doubl
   SweepArgs W = sweep_args(ctx, P, dt, e);
   W.small = 0;
   W.exact = ctx->exact_sweeps;
-  W.G = Grid{};  // periodic boxes; each sphere's grid is its box's
+  W.G = nullptr;  // periodic boxes; each sphere's grid is its box's
   W.B = batch_dev(ctx->bp);
   W.err = ctx->bp->flags + FLAG_ERR;
   return W;
@@ -1341,10 +1183,12 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   // reach check and cell ids in one pass over the spheres (the counts are
   // discarded with everything else if the check fails)
   PCOL_HIP(launch_fill_i32(s, ctx->count, 0, ncell));
+  PCOL_HIP(launch_fill_u32(s, (unsigned int *)ctx->scan, 0u,
+                           2 + 2 * (int64_t)((ncell + SCAN_B - 1) / SCAN_B + 1)));
   PCOL_HIP(launch_breach(s, P, B, dt, 1, ctx->cid, ctx->slot, ctx->count));
-  PCOL_HIP(launch_scan(s, ctx->count, ncell, ctx->start, ctx->blocksum, ctx->reach_d));
-  PCOL_HIP(launch_scatter(s, P, ctx->cid, ctx->slot, ctx->start, ctx->rec, ctx->rank, &B));
-  PCOL_HIP(launch_fill_i32(s, ctx->cnt, 0, n));
+  PCOL_HIP(launch_scan(s, ctx->count, ncell, nullptr, ctx->start, ctx->scan, nullptr));
+  PCOL_HIP(launch_scatter(s, P, ctx->cid, ctx->slot, ctx->start, ctx->rec, ctx->rank, ctx->cnt, &B,
+                          bp->flags + FLAG_ERR));
   DetectArgs A{};
   A.rec = ctx->rec;
   A.start = ctx->start;
@@ -1362,7 +1206,6 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   double hmax = 0.0;
   for (const Grid &G : bp->gtab_h)
     for (int a = 0; a < 3; ++a) hmax = G.h[a] > hmax ? G.h[a] : hmax;
-  A.tol = 16.0 * 0x1.0p-53 * hmax * hmax * (2.0 + A.dt2 / dt);
   {
     // reach <= hmax, 2 r_max <= hmax and 2 v_max dt <= hmax in every box (see above)
     double Lmax = 0.0, X = 0.0;
@@ -1373,16 +1216,17 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
     A.tol64 = gram64_tolerance(X, hmax, hmax, hmax / (2.0 * dt), 0.5 * hmax, Lmax, A.dt2);
   }
   A.K = ctx->K;
-  A.fp32 = 0;
   PCOL_HIP(launch_detect_batched(s, A, B, bp->total_cells, cpw));
   PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec, ctx->key_j,
                            ctx->key_t, ctx->ovf, ctx->ctr_d, bp->flags + FLAG_ERR));
   PCOL_HIP(launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
-                               ctx->G, dt, nullptr, ctx->key_j, ctx->key_t, &B));
+                               nullptr, dt, nullptr, ctx->key_j, ctx->key_t, &B,
+                               bp->flags + FLAG_ERR));
   SweepArgs W = batch_sweep_args(ctx, P, dt, e);
   PCOL_HIP(queue_sweeps(ctx, W, s, kmax, true));
-  PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G, &B,
-                         ctx->ctr_d, kmax, W.exact != 0, ctx->rep));
+  PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, nullptr,
+                         nullptr, &B, ctx->ctr_d, kmax, W.exact != 0, bp->flags + FLAG_ERR,
+                         ctx->rep));
   return PCOL_OK;
 }
 
@@ -1418,8 +1262,9 @@ static pcol_status batch_finish(pcol_ctx *ctx, const Particles &P, int32_t *part
   for (int end = 5;; end = std::min(2 * end, MAX_QUEUE)) {
     PCOL_HIP(hipMemsetAsync(ctx->ctr_d->pairs, 0, sizeof(ctx->ctr_d->pairs), s));
     PCOL_HIP(queue_sweeps(ctx, W, s, end, false));
-    PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G, &B,
-                           ctx->ctr_d, end, W.exact != 0, ctx->rep));
+    PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, nullptr,
+                           nullptr, &B, ctx->ctr_d, end, W.exact != 0, bp->flags + FLAG_ERR,
+                           ctx->rep));
     PCOL_HIP(hipStreamSynchronize(s));
     for (int k = 1; k < end; ++k) {
       ++sweeps;
@@ -1636,8 +1481,9 @@ extern "C" pcol_status pcol_step_batched(pcol_ctx *ctx, int32_t nbox, const int6
     SweepArgs W = batch_sweep_args(ctx, P, dt, e);
     const BatchDev B = batch_dev(bp);
     PCOL_HIP(queue_sweeps(ctx, W, ctx->stream, bp->kmax, true));
-    PCOL_HIP(launch_finish(ctx->stream, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->G,
-                           &B, ctx->ctr_d, bp->kmax, true, ctx->rep));
+    PCOL_HIP(launch_finish(ctx->stream, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, nullptr,
+                           nullptr, &B, ctx->ctr_d, bp->kmax, true, bp->flags + FLAG_ERR,
+                           ctx->rep));
     PCOL_HIP(hipStreamSynchronize(ctx->stream));
   }
   int64_t pairs = 0, sweeps = 0;

@@ -93,17 +93,6 @@ struct alignas(16) Rec32 {
   float vx, vy, vz, pad;
 };
 
-// Values the reach kernel reduces (non-negative doubles compared as bit patterns).
-struct ReachOut {
-  unsigned long long v2max;  // max over spheres of (vx^2 + vy^2) + vz^2
-  unsigned long long rmax;
-  unsigned long long rmin;   // initialised to the bits of +inf
-  unsigned long long rhomax; // max extent r + |v| dt
-  unsigned int bad;          // bit 0: non-finite / r <= 0 / m <= 0; bit 1: position outside [0, L)
-  unsigned int maxcell;      // filled by the scan
-  unsigned int hist[RHO_BINS];  // extents by rho_bin
-};
-
 // One workgroup's share of the reach pass: the bits of its maxima (of
 // non-negative doubles, so they order as the values), of its smallest radius
 // (+inf if none) and its validity bits.
@@ -124,6 +113,229 @@ struct CurveGrid {
   int nc[3];
   double h[3];
 };
+
+// Scratch of the reach pass: REACH_BLOCKS partial results, the extent histogram
+// (RHO_BINS bins, zero between passes) and REACH_BLOCKS partial ones.
+struct ReachScratch {
+  ReachPart *parts;
+  unsigned int *hist, *phist;
+};
+
+// Exclusive scan: SCAN_T threads of SCAN_E cells per tile; the words (zero before
+// a scan) hold each tile's sum or running total.
+constexpr int SCAN_T = 1024;
+constexpr int SCAN_E = 4;
+constexpr int SCAN_B = SCAN_T * SCAN_E;
+struct ScanState {
+  int ticket, pad;
+  unsigned long long word[1];  // one per tile, and one more
+};
+
+// What a step's plan is made of besides its data.
+enum : unsigned int {
+  PLAN_INVALID = 1u,   // non-finite value, r <= 0 or m <= 0
+  PLAN_POSITION = 2u,  // position outside [0, L)
+  PLAN_BOX = 4u,       // a box side <= 2 * reach
+  PLAN_AGAIN = 8u      // not what the queued kernels were sized for: the host starts over
+};
+struct PlanArgs {
+  int64_t n, cell_cap;
+  double L[3], dt, cell_mult, band_rel, quantile;
+  int home_cells, fp32, walls;
+  int allow_split, allow_small;  // kernels for them are queued behind the plan
+  // the grid that the reach pass has counted the spheres on (tried)
+  int tried, tried_nc[3], tried_layer2;
+  double tried_rho_c;
+};
+struct StepPlan {
+  unsigned int err;   // PLAN_* bits; nonzero: the step does nothing
+  int hit;            // the spheres have been counted on this grid
+  int small;          // some axis has fewer than 3 cells
+  int split;
+  int cells;          // of both layers
+  int cpw;            // home cells per workgroup of the pair tests
+  double reach, rho_c, rho_max;  // rho_c: +inf without a split
+  double band, tol64, tol_wide;
+  float kband, dt2f;
+  Grid G;
+  CurveGrid C;
+};
+
+// Contact-distance factor of the FP32 filter.  Bounds (unit roundoff u = 2^-24)
+// on the FP32 errors of the filter quantities for any pair the binary64 rule
+// can keep (|d| <= reach, |u| <= 2 vmax, coordinates within 1.5 h of the home
+// cell centre):
+//   separation   Dd = (2 h + reach) u       relative velocity  Du = 4 vmax u
+//   c' = |d|^2 - (s k)^2:  2 sqrt3 reach Dd + 3 u reach^2 + 6 u (2 rmax k)^2
+//   b' dt2f = d.u dt2f:    (sqrt3 (reach Du + 2 vmax Dd) + 6 u reach vmax) 2 dt (1 + 2^-11)
+// The inflation (k^2 - 1) s_min^2 >= 2 (k - 1) s_min^2 must cover their sum; k
+// is chosen so that it covers twice the sum, and never below 1 + band_rel.
+// Returns the band.
+__host__ __device__ inline double fp32_band(double h, double R, double V, double rmax, double rmin,
+                                            double band_rel, double dt) {
+  const double u = 0x1.0p-24, smin = 2.0 * rmin;
+  const double k0 = 1.0 + band_rel + 1e-3;  // generous k for the radius term
+  const double Dd = (2.0 * h + R) * u, Du = 4.0 * V * u;
+  const double ec = 2.0 * sqrt(3.0) * R * Dd + 3.0 * u * R * R +
+                    6.0 * u * (2.0 * rmax * k0) * (2.0 * rmax * k0);
+  const double eb = (sqrt(3.0) * (R * Du + 2.0 * V * Dd) + 6.0 * u * R * V) * 2.0 * dt *
+                    (1.0 + 0x1.0p-11);
+  const double need = 2.0 * (ec + eb) / (2.0 * smin * smin);
+  return band_rel > need ? band_rel : need;
+}
+
+// Tolerance of the binary64 Gram filter (filter 0).  The filter evaluates
+// g = beta_i + <P_i, Q_j> (seven FMAs from beta_i) and passes the pair when
+// g <= fl(tol - beta_j); in real numbers that is F = g + beta_j <= tol.  For a
+// pair the rule keeps, the real F is at most
+// E0 = 3 eps ((reach^2 + (2 r_max)^2) + reach 2 v_max dt2) (the binary64 argument:
+// the kept root c / (-b + sqrt D) <= dt gives c <= 2 |b| dt (1 + 6 eps) < |b| dt2).
+// The evaluation differs from the real F by
+//  * the image shift of the candidate: one rounding per axis of a value below
+//    L + h, so the separation d is off by at most delta = 2 eps (Lmax + h), which
+//    moves F by at most delta (2 reach + 2 v_max dt2) + delta^2;
+//  * beta_i, beta_j, Q, (a few roundings each, <= 6 eps relative) and the seven
+//    FMAs of the sum (<= 7 eps of the sum of magnitudes): at most
+//    16 eps (2 B + S) with B, S the bounds of |beta| and sum_k |P_k Q_k| for
+//    |x| <= X, the norm of the box sides each lengthened by a cell;
+//  * the threshold's one rounding, at most eps (tol + |beta_j|): the eps tol part
+//    is covered by the factor two below, the eps B part by a 17th eps.
+// The tolerance is twice the sum.
+__host__ __device__ inline double gram64_tolerance(double X, double h, double R, double V,
+                                                   double r, double Lmax, double dt2) {
+  const double eps = 0x1.0p-53;
+  X *= 1.0 + 1e-6;
+  const double B = X * X + dt2 * X * V + r * r;
+  const double S = X * (2.0 * X + dt2 * V) + V * dt2 * X + 2.0 * r * r;
+  const double E0 = 3.0 * eps * ((R * R + 4.0 * r * r) + R * 2.0 * V * dt2);
+  const double delta = 2.0 * eps * (Lmax + h);
+  const double Epos = delta * (2.0 * R + 2.0 * V * dt2) + delta * delta;
+  const double E = 17.0 * eps * (2.0 * B + S);
+  return 2.0 * (E0 + Epos + E);
+}
+
+// Norm of the box sides, each lengthened by a cell: bounds every position and
+// periodic image that the pair tests meet.
+__host__ __device__ inline double grid_norm(const Grid &G) {
+  double q = 0.0;
+  for (int a = 0; a < 3; ++a) q += (G.L[a] + G.h[a]) * (G.L[a] + G.h[a]);
+  return sqrt(q);
+}
+
+// The plan of a step from its reach pass: the verdict on the data, the split extent
+// (kbin: the histogram bin where the split quantile of the extents falls, -1 for
+// none), the grid and what the pair tests derive from it.
+__host__ __device__ inline void make_plan(const PlanArgs &A, const ReachPart &r, int kbin,
+                                          StepPlan &P) {
+  union Bits {
+    unsigned long long u;
+    double d;
+  };
+  const double inf = __builtin_inf();
+  P = StepPlan{};
+  P.rho_c = inf;
+  P.err = (r.bad & 1u ? PLAN_INVALID : 0u) | (r.bad & 2u ? PLAN_POSITION : 0u);
+  if (P.err) return;
+  const double rmax = Bits{r.rmax}.d, rmin = Bits{r.rmin}.d;
+  const double vmax = __builtin_sqrt(Bits{r.v2max}.d);
+  const double reach = 2.0 * rmax + 2.0 * vmax * A.dt;
+  P.reach = reach;
+  for (int a = 0; a < 3; ++a)
+    if (!(A.L[a] > 2.0 * reach)) P.err = PLAN_BOX;
+  if (P.err) return;
+  // Extent split: the first layer holds the spheres whose extent is at most
+  // rho_c, the upper edge of the bin; pairs of them are at most 2 rho_c apart
+  // when they can touch.  Used only when it shrinks the cells enough to pay for
+  // the separate search of the others, and the grid keeps 3 cells per axis.
+  double rho_c = inf;
+  if (A.quantile > 0.0 && A.quantile < 1.0 && A.n >= 4096 && kbin >= 0) {
+    rho_c = Bits{(unsigned long long)((1023 - 64) * 16 + kbin + 1) << 48}.d;
+    if (!(2.0 * rho_c < 0.85 * reach)) rho_c = inf;
+    for (int a = 0; a < 3; ++a)
+      if (A.L[a] / (2.0 * rho_c * A.cell_mult * (1.0 + 1e-9)) < 3.0) rho_c = inf;
+  }
+  const bool split = rho_c < inf;
+  const double reach_pass = split ? 2.0 * rho_c : reach;
+  // grid: cell side >= (split ? 2 rho_c : reach) * cell_mult, at most 2^26 cells per layer
+  Grid &G = P.G;
+  double cell = reach_pass * A.cell_mult;
+  if (!(cell > 0.0)) cell = A.L[0];  // no motion and no size: one cell
+  for (;;) {
+    long long ncell = 1;
+    for (int a = 0; a < 3; ++a) {
+      double q = floor(A.L[a] / (cell * (1.0 + 1e-9)));
+      if (!(q >= 1.0)) q = 1.0;
+      if (q > 1024.0) q = 1024.0;
+      G.nc[a] = (int)q;
+      ncell *= G.nc[a];
+    }
+    if (ncell <= (1 << 26)) {
+      G.ncell = (int)ncell;
+      break;
+    }
+    cell *= 1.25;
+  }
+  G.walls = A.walls;
+  double h = 0.0, Lmax = 0.0;
+  for (int a = 0; a < 3; ++a) {
+    const bool wall = (A.walls >> a) & 1;
+    G.L[a] = A.L[a];
+    // between walls there is no minimum image and no periodic image shift
+    G.halfL[a] = wall ? inf : 0.5 * A.L[a];
+    G.sL[a] = wall ? 0.0 : A.L[a];
+    G.inv_h[a] = (double)G.nc[a] / A.L[a];
+    G.h[a] = A.L[a] / G.nc[a];
+    h = G.h[a] > h ? G.h[a] : h;
+    Lmax = A.L[a] > Lmax ? A.L[a] : Lmax;
+    if (G.nc[a] < 3) P.small = 1;
+  }
+  G.layer2 = split ? G.ncell : 0;
+  P.rho_max = Bits{r.rhomax}.d;
+  G.rho_max = split ? P.rho_max : 0.0;
+  G.inv_row = 1.0 / G.nc[0];
+  G.inv_layer = 1.0 / ((double)G.nc[0] * G.nc[1]);
+  P.split = split;
+  P.rho_c = rho_c;
+  P.cells = split ? 2 * G.ncell : G.ncell;
+  if ((long long)P.cells + 2 > A.cell_cap || (P.small && !A.allow_small) ||
+      (split && !A.allow_split)) {
+    P.err = PLAN_AGAIN;
+    return;
+  }
+  P.hit = A.tried && A.tried_nc[0] == G.nc[0] && A.tried_nc[1] == G.nc[1] &&
+          A.tried_nc[2] == G.nc[2] && A.tried_layer2 == G.layer2 &&
+          (!split || A.tried_rho_c == rho_c);
+  // sparse cells (the split grid holds about 13 spheres per cell at 16M): four
+  // cells per workgroup, so their survivors are decided together; home_cells
+  // overrides the choice
+  P.cpw = P.small ? 0
+                  : (A.home_cells > 0 ? A.home_cells : (A.n < 24 * (long long)G.ncell ? 4 : 1));
+  // first-layer bounds: extent <= rho_c gives |v| <= (rho_c - r_min) / dt, r <= rho_c
+  const double vb = (rho_c - rmin) / A.dt;
+  const double V = split && vb < vmax ? vb : vmax, rp = split && rho_c < rmax ? rho_c : rmax;
+  const double dt2 = 2.0 * A.dt * (1.0 + 0x1.0p-20);
+  P.tol64 = gram64_tolerance(grid_norm(G), h, reach_pass, V, rp, Lmax, dt2);
+  // pairs with a sphere above the split extent: |d| up to the full reach
+  const double sw = 2.0 * rmax;
+  P.tol_wide = 16.0 * 0x1.0p-53 * (reach * reach + sw * sw + reach * 2.0 * vmax * dt2);
+  if (A.fp32 && !P.small) {
+    P.band = fp32_band(h, reach_pass, V, rp, rmin, A.band_rel, A.dt);
+    // round the factor up so the float never shrinks the inflation
+    const double kb = 1.0 + P.band;
+    P.kband = (float)kb;
+    if ((double)P.kband < kb) P.kband = P.kband * (1.0f + 0x1.0p-23f);
+  }
+  P.dt2f = (float)(2.0 * A.dt * (1.0 + 0x1.0p-12));
+  // the literal order's curve grid: cell side >= the reach (whatever grid the pair
+  // tests use), at most 2048 cells per axis
+  for (int a = 0; a < 3; ++a) {
+    double q = floor(A.L[a] / (reach * (1.0 + 1e-9)));
+    if (!(q >= 1.0)) q = 1.0;
+    if (q > 2048.0) q = 2048.0;
+    P.C.nc[a] = (int)q;
+    P.C.h[a] = A.L[a] / P.C.nc[a];
+  }
+}
 
 // Counters of a step, zero at its start.  Sums are spread over NSHARD counters on
 // separate 128-B lines (one atomic per workgroup on shard blockIdx % NSHARD), so
@@ -147,14 +359,16 @@ struct SweepCounters {
   ListShard list[NSHARD];
   unsigned int n_overflow;  // spheres with more contacts than slots (list length)
   unsigned int ovf_later;   // the same among those that took a new partner later
-  unsigned int pad[30];
+  unsigned int maxcell;     // largest cell occupancy
+  unsigned int pad[29];
   unsigned long long pairs[MAX_QUEUE][PAIR_SHARDS];  // pairs resolved by each later sweep
 };
 
 // What the host reads of a step (page-locked host memory, written by k_finish).
 struct StepReport {
   unsigned long long contacts, recheck, tests;
-  unsigned int n_overflow, pad;
+  unsigned int n_overflow, maxcell;
+  int wide_first, pad;  // sorted position of the first sphere above the split extent
   unsigned long long pairs[MAX_QUEUE];
 };
 
@@ -415,7 +629,7 @@ struct SweepArgs {
   int shards, shard_blocks;  // shards of the list, each with room for so many workgroups
   const Rec *rec;
   const int *start;
-  Grid G;
+  const Grid *G;     // device: the single box's grid (null in the batched form)
   BatchDev B;        // tables of the batched form (gtab null: one box)
   double dt, e;
   const double *mass;
@@ -427,14 +641,9 @@ struct SweepArgs {
   int *list[2];      // n entries each and one workgroup more for each shard
   SweepCounters *ctr;
   const unsigned long long *crank;
-  const unsigned int *err;  // nullable; nonzero: the step does nothing
+  const unsigned int *err;  // nonzero: the step does nothing
   Spin spin;         // wx null: none
   int turn = 0, rekeyed = 0;  // host: sweeps over the list queued so far, and sweep 1's DIRTY done
-};
-
-// Pair tests and filter survivors of one workgroup of the k_detect_half kernels.
-struct CellCount {
-  unsigned long long tests, recheck;
 };
 
 // Everything the sweep-1 detect needs.
@@ -446,58 +655,52 @@ struct DetectArgs {
   int *slot_j;        // [n * K]
   SweepCounters *ctr;
   int n;              // spheres (slot arrays are k-major: slot[k * n + i])
-  Grid G;
+  int K;
+  const StepPlan *plan;  // one box: grid and tolerances (null in the batched form)
   double dt;
   double dt2;         // 2 dt (1 + 2^-20): step bound of the FP64 filter
-  double tol;         // binary32 filter: unused; kept for the FMA form's bound
   double tol64;       // binary64 Gram filter tolerance (see gram64_tolerance)
-  double tol_wide;    // the same for pairs with a sphere above the split extent (full reach)
-  double rho_c;       // split extent (first-layer spheres have extent <= rho_c)
-  int K;
-  int fp32;           // FP32 filter + FP64 recheck
   float kband;        // FP32 filter: contact distance inflated to s * kband
   float dt2f;         // FP32 filter: 2 dt (1 + 2^-12)
-  CellCount *cellc;   // per workgroup of the one-box detect kernels (G.ncell entries)
-  int cpw;            // binary64 filter: home cells per workgroup (1: one cell per wave)
 };
 
 hipError_t launch_fill_u32(hipStream_t s, unsigned int *p, unsigned int v, int64_t n);
 hipError_t launch_fill_u8(hipStream_t s, uint8_t *p, uint8_t v, int64_t n);
 hipError_t launch_fill_f64(hipStream_t s, double *p, double v, int64_t n);
 hipError_t launch_fill_i32(hipStream_t s, int *p, int v, int64_t n);
-// hist_shift: the extent histogram covers the spheres whose index is a multiple
-// of 2^hist_shift (the maxima and the validity cover all).  parts and phist are
-// scratch of REACH_BLOCKS partial results and REACH_BLOCKS * RHO_BINS counts;
-// out->hist must be zero and out's other fields are overwritten.  G given: the
-// pass also bins the spheres on G with split extent rho_c into cid, slot and
-// count (zero on entry), as launch_cell_hist does.
-hipError_t launch_reach(hipStream_t s, const Particles &P, const double L[3], double dt,
-                        int hist_shift, ReachOut *out, ReachPart *parts, unsigned int *phist,
+// The reach pass and the plan.  hist_shift: the extent histogram covers the
+// spheres whose index is a multiple of 2^hist_shift.  G given: the pass also bins
+// the spheres on G with split extent rho_c into cid, slot and count (zero on
+// entry), as launch_cell_hist does.
+hipError_t launch_reach(hipStream_t s, const Particles &P, double dt, int hist_shift,
+                        const PlanArgs &A, const ReachScratch &R, SweepCounters *ctr,
+                        ScanState *scan, StepPlan *plan, StepPlan *plan_host,
                         const Grid *G = nullptr, double rho_c = 0.0, int *cid = nullptr,
                         int *slot = nullptr, int *count = nullptr);
-hipError_t launch_cell_hist(hipStream_t s, const Particles &P, const Grid &G, double dt,
-                            double rho_c, int *cid, int *slot, int *count);
-// the spheres of the second layer, sorted positions [*first_dev, n)
-hipError_t launch_detect_wide(hipStream_t s, const DetectArgs &A, const int *first_dev, int n);
-hipError_t launch_scan(hipStream_t s, const int *count, int ncell, int *start, int *blocksum,
-                       ReachOut *out);
+// tried_cells: cells of the grid that the reach pass counted on (0: none)
+hipError_t launch_cell_hist(hipStream_t s, const Particles &P, const StepPlan *plan, double dt,
+                            int tried_cells, int *cid, int *slot, int *count);
+// the spheres of the second layer, if there is one
+hipError_t launch_detect_wide(hipStream_t s, const DetectArgs &A);
+// one-pass scan of plan->cells counts (ncell: as many as the host expects) or, with
+// no plan, of ncell; clears the counts; *st zero on entry
+hipError_t launch_scan(hipStream_t s, int *count, int ncell, const StepPlan *plan, int *start,
+                        ScanState *st, unsigned int *maxcell);
 hipError_t launch_scatter(hipStream_t s, const Particles &P, const int *cid, const int *slot,
-                          const int *start, Rec *rec, int *rank, const BatchDev *B);
-hipError_t launch_detect_half(hipStream_t s, const DetectArgs &A);
-// workgroups of launch_detect_half, each writing one CellCount
-int detect_half_blocks(const DetectArgs &A);
-// adds the per-cell counts of launch_detect_half to the counter shards of ctr
-hipError_t launch_cell_counts(hipStream_t s, const CellCount *c, int n, SweepCounters *ctr);
+                          const int *start, Rec *rec, int *rank, int *cnt, const BatchDev *B,
+                          const unsigned int *err);
+hipError_t launch_detect_half(hipStream_t s, const DetectArgs &A, bool fp32, int groups);
 hipError_t launch_slot_min(hipStream_t s, int n, const int *cnt, const double *slot_t,
                            const int *slot_j, int K, const Rec *rec, int *key_j, double *key_t,
                            int *ovf_list, SweepCounters *ctr, const unsigned int *err,
-                           const Grid *G = nullptr,  // walls of the single box (none: periodic)
+                           const Grid *G = nullptr,  // device: walls of the box (none: periodic)
                            const unsigned long long *crank = nullptr);  // literal order's ranks
 hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const unsigned int *nlist_dev,
-                               int select, const Rec *rec, const int *start, const Grid &G,
+                               int select, const Rec *rec, const int *start, const Grid *G,
                                double dt, const uint8_t *status, int *key_j, double *key_t,
-                               const BatchDev *B, const unsigned long long *crank = nullptr);
-hipError_t launch_curve_rank(hipStream_t s, const Rec *rec, int n, const CurveGrid &C,
+                               const BatchDev *B, const unsigned int *err,
+                               const unsigned long long *crank = nullptr);
+hipError_t launch_curve_rank(hipStream_t s, const Rec *rec, int n, const StepPlan *plan,
                              unsigned long long *crank);
 // The sweeps of a step (sweep_shards sets the list's shards).  first: every sphere;
 // rekey: new partners for those it left DIRTY; sweep k >= 1: the list, keys in
@@ -511,8 +714,9 @@ hipError_t launch_sweep(hipStream_t s, const SweepArgs &A, const int *in, int *o
 // last of them resolved nothing
 hipError_t launch_finish(hipStream_t s, const Particles &P, const int *rank, const OutRec *out,
                          const uint8_t *status, int *partner, double *tcoll, double dt,
-                         const Grid &G, const BatchDev *B, const SweepCounters *ctr, int nsweep,
-                         bool exact, StepReport *rep);
+                         const StepPlan *plan, const int *start, const BatchDev *B,
+                         const SweepCounters *ctr, int nsweep, bool exact, const unsigned int *err,
+                         StepReport *rep);
 hipError_t launch_fill_box_of(hipStream_t s, int nbox, const int64_t *box_off, int *box_of);
 // count given (zero on entry): the pass also takes every sphere's global cell
 // (box's first cell + local cell on its planned grid) and its slot in that cell

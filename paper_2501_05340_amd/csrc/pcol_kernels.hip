@@ -139,9 +139,10 @@ hipError_t launch_fill_f64(hipStream_t s, double *p, double v, int64_t n) {
 // validity cover every sphere; the histogram, which only picks the split
 // extent (a performance choice), covers the spheres whose index is a multiple
 // of 2^hist_shift.  Grid-stride over at most REACH_BLOCKS workgroups; each
-// histograms in LDS and stores its partial results (maxima and its whole
-// histogram) in parts, which k_reach_final reduces: no address takes an atomic
-// from every workgroup.
+// histograms in LDS and stores its maxima in parts, which k_plan reduces.  Few
+// workgroups add their histograms (some 50 bins) to the result at once; many
+// store them whole in phist, which k_hist_sum reduces: no address takes an
+// atomic from more than REACH_DIRECT workgroups.
 // BIN: the same pass also takes each sphere's cell and slot on the grid G with
 // split extent rho_c, exactly as k_cell_hist does (the binning of a step whose
 // grid is planned before its reach is known; the plan is checked against the
@@ -150,8 +151,8 @@ hipError_t launch_fill_f64(hipStream_t s, double *p, double v, int64_t n) {
 template <bool BIN>
 __global__ __launch_bounds__(256) void k_reach(Particles P, double L0, double L1, double L2,
                                                double dt, int hist_shift, ReachPart *parts,
-                                               unsigned int *phist, Grid G, double rho_c,
-                                               int *cid, int *slot, int *count) {
+                                               unsigned int *sum, unsigned int *phist, Grid G,
+                                               double rho_c, int *cid, int *slot, int *count) {
   __shared__ unsigned int hist[RHO_BINS];
   for (int k = threadIdx.x; k < RHO_BINS; k += 256) hist[k] = 0u;
   __syncthreads();
@@ -255,57 +256,113 @@ __global__ __launch_bounds__(256) void k_reach(Particles P, double L0, double L1
     for (int w = 1; w < 256 / WAVE; ++w) p = reach_merge(p, wpart[w]);
     parts[blockIdx.x] = p;
   }
-  for (int k = threadIdx.x; k < RHO_BINS; k += 256)
-    phist[(int64_t)blockIdx.x * RHO_BINS + k] = hist[k];
+  for (int k = threadIdx.x; k < RHO_BINS; k += 256) {
+    if (phist)
+      phist[(int64_t)blockIdx.x * RHO_BINS + k] = hist[k];
+    else if (hist[k])
+      atomicAdd(&sum[k], hist[k]);
+  }
 }
 
-// Reduction of k_reach's nblocks partial results into out: the maxima, the
-// smallest radius and the validity bits by one workgroup, the histogram by
-// REACH_FINAL_Y workgroups per 256 bins, each summing a share of the partial
-// histograms and adding its non-zero sums (REACH_FINAL_Y adds per bin at most).
+// Sum of k_reach's nblocks partial histograms: REACH_FINAL_Y workgroups per 256
+// bins, each summing a share of them and adding its non-zero sums.
 constexpr int REACH_FINAL_Y = 32;
+constexpr int REACH_DIRECT = 512;
 
-__global__ __launch_bounds__(256) void k_reach_final(int nblocks, const ReachPart *parts,
-                                                     const unsigned int *phist, ReachOut *out) {
+__global__ __launch_bounds__(256) void k_hist_sum(int nblocks, const unsigned int *phist,
+                                                  unsigned int *sum) {
   const int b = blockIdx.x * 256 + threadIdx.x;  // bin
   const int per = (nblocks + REACH_FINAL_Y - 1) / REACH_FINAL_Y;
   const int k0 = blockIdx.y * per, k1 = k0 + per < nblocks ? k0 + per : nblocks;
-  unsigned int s = 0u;
-  for (int k = k0; k < k1; ++k) s += phist[(int64_t)k * RHO_BINS + b];
-  if (s) atomicAdd(&out->hist[b], s);
-  if (blockIdx.x != 0 || blockIdx.y != 0) return;
-  __shared__ ReachPart red[256];
-  ReachPart p{0ull, 0ull, dbits(INFINITY), 0ull, 0u, 0u};
-  for (int k = threadIdx.x; k < nblocks; k += 256) p = reach_merge(p, parts[k]);
-  red[threadIdx.x] = p;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] = reach_merge(red[threadIdx.x], red[threadIdx.x + o]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    out->v2max = red[0].v2max;
-    out->rmax = red[0].rmax;
-    out->rhomax = red[0].rhomax;
-    out->rmin = red[0].rmin;
-    out->bad = red[0].bad;
-  }
+  unsigned int t = 0u;
+  for (int k = k0; k < k1; ++k) t += phist[(int64_t)k * RHO_BINS + b];
+  if (t) atomicAdd(&sum[b], t);
 }
 
-hipError_t launch_reach(hipStream_t s, const Particles &P, const double L[3], double dt,
-                        int hist_shift, ReachOut *out, ReachPart *parts, unsigned int *phist,
-                        const Grid *G, double rho_c, int *cid, int *slot, int *count) {
-  int64_t g = (P.n + 255) / 256;
+// The step's plan from the reach pass (make_plan: the checks, the split extent,
+// the grid and the tolerances that follow from them), by one workgroup, so that
+// the kernels behind it can be queued without the host in between: they read the
+// plan from device memory and do nothing when it says so (plan.err).  Written to
+// the host's memory too.  Leaves the histogram, the step's counters and the
+// scan's words zero.
+__global__ __launch_bounds__(256) void k_plan(PlanArgs A, int nparts, const ReachPart *parts,
+                                              unsigned int *hist, SweepCounters *ctr,
+                                              ScanState *scan, StepPlan *plan,
+                                              StepPlan *plan_host) {
+  const int t = threadIdx.x;
+  unsigned long long *w = (unsigned long long *)ctr;
+  for (int k = t; k < (int)(sizeof(SweepCounters) / 8); k += 256) w[k] = 0ull;
+  // the split quantile's bin: the first one whose running count reaches it
+  constexpr int PER = RHO_BINS / 256;
+  unsigned int h[PER], mine = 0u;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    h[k] = hist[t * PER + k];
+    mine += h[k];
+    hist[t * PER + k] = 0u;
+  }
+  ReachPart p{0ull, 0ull, dbits(INFINITY), 0ull, 0u, 0u};
+  for (int k = t; k < nparts; k += 256) p = reach_merge(p, parts[k]);
+  __shared__ unsigned int cum[256];
+  __shared__ ReachPart red[256];
+  __shared__ int bin;
+  cum[t] = mine;
+  red[t] = p;
+  if (t == 0) bin = RHO_BINS;
+  __syncthreads();
+  for (int o = 1; o < 256; o <<= 1) {
+    const unsigned int v = t >= o ? cum[t - o] : 0u;
+    __syncthreads();
+    cum[t] += v;
+    __syncthreads();
+  }
+  for (int o = 128; o > 0; o >>= 1) {
+    if (t < o) red[t] = reach_merge(red[t], red[t + o]);
+    __syncthreads();
+  }
+  const double target = ceil(A.quantile * (double)cum[255]);
+  unsigned int run = cum[t] - mine;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const bool before = (double)run < target;
+    run += h[k];
+    if (before && (double)run >= target) atomicMin(&bin, t * PER + k);
+  }
+  __syncthreads();
+  __shared__ StepPlan out;
+  if (t == 0) make_plan(A, red[0], bin < RHO_BINS - 1 ? bin : -1, out);
+  __syncthreads();
+  const unsigned long long *o = (const unsigned long long *)&out;
+  for (int k = t; k < (int)(sizeof(StepPlan) / 8); k += 256) {
+    ((unsigned long long *)plan)[k] = o[k];
+    ((unsigned long long *)plan_host)[k] = o[k];
+  }
+  if (out.err != 0u) return;  // (then there may be no room for the cells either)
+  for (int k = t; k <= (out.cells + SCAN_B - 1) / SCAN_B; k += 256) scan->word[k] = 0ull;
+  if (t == 0) scan->ticket = 0;
+}
+
+hipError_t launch_reach(hipStream_t s, const Particles &P, double dt, int hist_shift,
+                        const PlanArgs &A, const ReachScratch &R, SweepCounters *ctr,
+                        ScanState *scan, StepPlan *plan, StepPlan *plan_host, const Grid *G,
+                        double rho_c, int *cid, int *slot, int *count) {
+  const int64_t g4 = (P.n + 1023) / 1024, g1 = (P.n + 255) / 256;
+  int64_t g = std::max(g4, std::min(g1, (int64_t)128));
   if (g > REACH_BLOCKS) g = REACH_BLOCKS;
   if (g < 1) g = 1;
+  unsigned int *phist = g > REACH_DIRECT ? R.phist : nullptr;
   if (G)
-    hipLaunchKernelGGL(k_reach<true>, dim3((int)g), dim3(256), 0, s, P, L[0], L[1], L[2], dt,
-                       hist_shift, parts, phist, *G, rho_c, cid, slot, count);
+    hipLaunchKernelGGL(k_reach<true>, dim3((int)g), dim3(256), 0, s, P, A.L[0], A.L[1], A.L[2], dt,
+                       hist_shift, R.parts, R.hist, phist, *G, rho_c, cid, slot, count);
   else
-    hipLaunchKernelGGL(k_reach<false>, dim3((int)g), dim3(256), 0, s, P, L[0], L[1], L[2], dt,
-                       hist_shift, parts, phist, Grid{}, 0.0, nullptr, nullptr, nullptr);
-  hipLaunchKernelGGL(k_reach_final, dim3(RHO_BINS / 256, REACH_FINAL_Y), dim3(256), 0, s, (int)g,
-                     parts, phist, out);
+    hipLaunchKernelGGL(k_reach<false>, dim3((int)g), dim3(256), 0, s, P, A.L[0], A.L[1], A.L[2],
+                       dt, hist_shift, R.parts, R.hist, phist, Grid{}, 0.0, nullptr, nullptr,
+                       nullptr);
+  if (phist)
+    hipLaunchKernelGGL(k_hist_sum, dim3(RHO_BINS / 256, REACH_FINAL_Y), dim3(256), 0, s, (int)g,
+                       phist, R.hist);
+  hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, s, A, (int)g, R.parts, R.hist, ctr, scan, plan,
+                     plan_host);
   return hipGetLastError();
 }
 
@@ -316,8 +373,11 @@ hipError_t launch_reach(hipStream_t s, const Particles &P, const double L[3], do
 // Extent split: a sphere whose extent r + |v| dt exceeds rho_c goes to the
 // second layer of cells (number G.layer2 + c), searched separately; the first
 // layer then only needs cells of side 2 rho_c.  rho_c = +inf: one layer.
-__global__ __launch_bounds__(256) void k_cell_hist(Particles P, Grid G, double dt, double rho_c,
+// Not if the reach pass has counted on this very grid (plan.hit).
+__global__ __launch_bounds__(256) void k_cell_hist(Particles P, const StepPlan *plan, double dt,
                                                    int *cid, int *slot, int *count) {
+  if (plan->err || plan->hit) return;
+  const Grid &G = plan->G;
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   int c = -1;
   if (i < P.n) {
@@ -325,7 +385,7 @@ __global__ __launch_bounds__(256) void k_cell_hist(Particles P, Grid G, double d
     const int cy = cell_coord(P.y[i], G.inv_h[1], G.nc[1]);
     const int cz = cell_coord(P.z[i], G.inv_h[2], G.nc[2]);
     c = (cz * G.nc[1] + cy) * G.nc[0] + cx;
-    if (G.layer2 && !(extent(P.r[i], P.vx[i], P.vy[i], P.vz[i], dt) <= rho_c)) c += G.layer2;
+    if (G.layer2 && !(extent(P.r[i], P.vx[i], P.vy[i], P.vz[i], dt) <= plan->rho_c)) c += G.layer2;
   }
   const int sl = run_slot(c, count);
   if (c >= 0) {
@@ -334,19 +394,25 @@ __global__ __launch_bounds__(256) void k_cell_hist(Particles P, Grid G, double d
   }
 }
 
-hipError_t launch_cell_hist(hipStream_t s, const Particles &P, const Grid &G, double dt,
-                            double rho_c, int *cid, int *slot, int *count) {
+// The counts that the reach pass took on another grid than the plan's.
+__global__ __launch_bounds__(256) void k_clear_missed(const StepPlan *plan, int cells, int *count) {
+  if (plan->err || plan->hit) return;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < cells; i += gridDim.x * 256) count[i] = 0;
+}
+
+hipError_t launch_cell_hist(hipStream_t s, const Particles &P, const StepPlan *plan, double dt,
+                            int tried_cells, int *cid, int *slot, int *count) {
   if (P.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cell_hist, dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, s, P, G, dt,
-                     rho_c, cid, slot, count);
+  if (tried_cells > 0)
+    hipLaunchKernelGGL(k_clear_missed, dim3(fill_grid(tried_cells)), dim3(256), 0, s, plan,
+                       tried_cells, count);
+  hipLaunchKernelGGL(k_cell_hist, dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, s, P, plan, dt,
+                     cid, slot, count);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- a3: exclusive scan
 
-constexpr int SCAN_T = 1024;   // threads per scan block
-constexpr int SCAN_E = 4;      // elements per thread
-constexpr int SCAN_B = SCAN_T * SCAN_E;
 
 // block-wide exclusive scan of one int per thread
 __device__ void block_exclusive_scan(int v, int &excl) {
@@ -373,75 +439,100 @@ __device__ void block_exclusive_scan(int v, int &excl) {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(SCAN_T) void k_scan_blocks(const int *count, int n, int *start,
-                                                         int *blocksum, ReachOut *out) {
-  const int base = blockIdx.x * SCAN_B + threadIdx.x * SCAN_E;
-  int v[SCAN_E];
-  int sum = 0, mx = 0;
-#pragma unroll
-  for (int k = 0; k < SCAN_E; ++k) {
-    v[k] = base + k < n ? count[base + k] : 0;
-    sum += v[k];
-    mx = v[k] > mx ? v[k] : mx;
-  }
-  int excl;
-  block_exclusive_scan(sum, excl);
-  int run = excl;
-#pragma unroll
-  for (int k = 0; k < SCAN_E; ++k) {
-    if (base + k < n) start[base + k] = run;
-    run += v[k];
-  }
-  // block total: the last thread's running end
-  if (threadIdx.x == SCAN_T - 1) blocksum[blockIdx.x] = run;
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    const int t = __shfl_xor(mx, o);
-    mx = t > mx ? t : mx;
-  }
+// Exclusive scan of the cell counts into start (start[n] the total) in one pass:
+// workgroups take tiles of SCAN_B cells in order, publish a tile's sum as soon
+// as they have it and its running total once they have added those before it,
+// looked up 64 tiles at a time by one wave.  A tile only waits for tiles taken
+// before it, which are held by workgroups that run.  The sum and its state travel
+// in one 64-bit word, so no other ordering is needed.  The counts are left zero
+// for the next binning; the largest one goes to *maxcell.
+// Three launches (tile sums, their scan, the addition) did the same: 26 us at
+// 2.7M cells and 3 launches of about 2 us, and as many gaps, at a thousand.
+enum : unsigned int { SCAN_SUM = 1u, SCAN_TOTAL = 2u };
+
+__global__ __launch_bounds__(SCAN_T) void k_scan(int *count, int n_host, const StepPlan *plan,
+                                                 int *start, ScanState *st,
+                                                 unsigned int *maxcell) {
+  if (plan && plan->err) return;
+  const int n = plan ? plan->cells : n_host;
+  const int tiles = (n + SCAN_B - 1) / SCAN_B;
+  __shared__ int tile, before;
   __shared__ int wmax[SCAN_T / WAVE];
-  if (__lane_id() == 0) wmax[threadIdx.x / WAVE] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < SCAN_T / WAVE; ++k) mx = wmax[k] > mx ? wmax[k] : mx;
-    atomicMax(&out->maxcell, (unsigned int)mx);
-  }
-}
-
-// exclusive scan of the block sums in place (one block, chunks of SCAN_T)
-__global__ __launch_bounds__(SCAN_T) void k_scan_sums(int *blocksum, int nb) {
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int c0 = 0; c0 < nb; c0 += SCAN_T) {
-    const int i = c0 + threadIdx.x;
-    const int v = i < nb ? blocksum[i] : 0;
+  for (;;) {
+    if (threadIdx.x == 0) tile = atomicAdd(&st->ticket, 1);
+    __syncthreads();
+    const int t = tile;
+    if (t >= tiles) return;
+    const int base = t * SCAN_B + threadIdx.x * SCAN_E;
+    int v[SCAN_E], sum = 0, mx = 0;
+#pragma unroll
+    for (int k = 0; k < SCAN_E; ++k) {
+      v[k] = base + k < n ? count[base + k] : 0;
+      sum += v[k];
+      mx = v[k] > mx ? v[k] : mx;
+    }
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+      const int m = __shfl_xor(mx, o);
+      mx = m > mx ? m : mx;
+    }
+    if (__lane_id() == 0) wmax[threadIdx.x / WAVE] = mx;
     int excl;
-    block_exclusive_scan(v, excl);
-    const int c = carry;
-    if (i < nb) blocksum[i] = c + excl;
+    block_exclusive_scan(sum, excl);
+    __shared__ int total;
+    if (threadIdx.x == SCAN_T - 1) total = excl + sum;
     __syncthreads();
-    if (threadIdx.x == SCAN_T - 1) carry = c + excl + v;
+    if (threadIdx.x < WAVE) {
+      const int lane = threadIdx.x;
+      int run = 0;
+      if (t > 0) {
+        if (lane == 0)
+          __hip_atomic_store(&st->word[t],
+                             ((unsigned long long)SCAN_SUM << 32) | (unsigned int)total,
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int hi = t - 1;; hi -= WAVE) {  // lane l looks at tile hi - l
+          const int at = hi - lane;
+          unsigned long long w = (unsigned long long)SCAN_TOTAL << 32;  // before the first: 0
+          if (at >= 0)
+            do
+              w = __hip_atomic_load(&st->word[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            while (w == 0ull);
+          const unsigned long long totals =
+              __builtin_amdgcn_ballot_w64((unsigned int)(w >> 32) == SCAN_TOTAL);
+          // the nearest running total ends the walk; lanes beyond it do not count
+          const int last = totals ? __ffsll((long long)totals) - 1 : WAVE - 1;
+          run += wave_sum(lane <= last ? (int)(unsigned int)w : 0);
+          if (totals) break;
+        }
+      }
+      if (lane == 0) {
+        __hip_atomic_store(&st->word[t],
+                           ((unsigned long long)SCAN_TOTAL << 32) | (unsigned int)(run + total),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = run;
+        for (int k = 1; k < SCAN_T / WAVE; ++k) mx = wmax[k] > mx ? wmax[k] : mx;
+        if (maxcell) atomicMax(maxcell, (unsigned int)mx);
+        if (t == tiles - 1) start[n] = run + total;
+      }
+    }
     __syncthreads();
+    int run = before + excl;
+#pragma unroll
+    for (int k = 0; k < SCAN_E; ++k) {
+      if (base + k < n) {
+        start[base + k] = run;
+        count[base + k] = 0;
+      }
+      run += v[k];
+    }
+    __syncthreads();  // tile, before, wmax and total are free again
   }
 }
 
-__global__ __launch_bounds__(256) void k_scan_add(int *start, const int *count, int n,
-                                                  const int *blocksum) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int v = start[i] + blocksum[i / SCAN_B];
-  start[i] = v;
-  if (i == n - 1) start[n] = v + count[i];
-}
-
-hipError_t launch_scan(hipStream_t s, const int *count, int ncell, int *start, int *blocksum,
-                       ReachOut *out) {
-  const int nb = (ncell + SCAN_B - 1) / SCAN_B;
-  hipLaunchKernelGGL(k_scan_blocks, dim3(nb), dim3(SCAN_T), 0, s, count, ncell, start, blocksum,
-                     out);
-  hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_T), 0, s, blocksum, nb);
-  hipLaunchKernelGGL(k_scan_add, dim3((ncell + 255) / 256), dim3(256), 0, s, start, count, ncell,
-                     blocksum);
+hipError_t launch_scan(hipStream_t s, int *count, int ncell, const StepPlan *plan, int *start,
+                        ScanState *st, unsigned int *maxcell) {
+  const int tiles = (ncell + SCAN_B - 1) / SCAN_B;
+  hipLaunchKernelGGL(k_scan, dim3(std::max(1, std::min(tiles, 512))), dim3(SCAN_T), 0, s, count,
+                     ncell, plan, start, st, maxcell);
   return hipGetLastError();
 }
 
@@ -449,12 +540,13 @@ hipError_t launch_scan(hipStream_t s, const int *count, int ncell, int *start, i
 
 // cell-sorted 64-B records of the start-of-step state; reads the caller's SoA
 // arrays coalesced and writes one record per sphere (its caller index and box
-// inside, so no other array is written in sorted order).
+// inside, so no other array is written in sorted order).  Clears the contact
+// counts on the way.
 __global__ __launch_bounds__(256) void k_scatter(Particles P, const int *cid, const int *slot,
-                                                 const int *start, Rec *rec, int *rank,
-                                                 const int *box_of, const unsigned int *flags) {
+                                                 const int *start, Rec *rec, int *rank, int *cnt,
+                                                 const int *box_of, const unsigned int *err) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= P.n || (flags && flags[FLAG_ERR])) return;
+  if (i >= P.n || *err) return;
   const int c = cid[i];
   const int pos = start[c] + slot[i];
   Rec q;
@@ -469,14 +561,15 @@ __global__ __launch_bounds__(256) void k_scatter(Particles P, const int *cid, co
   q.box = box_of ? box_of[i] : 0;
   rec[pos] = q;
   rank[i] = pos;
+  cnt[i] = 0;
 }
 
 hipError_t launch_scatter(hipStream_t s, const Particles &P, const int *cid, const int *slot,
-                          const int *start, Rec *rec, int *rank, const BatchDev *B) {
+                          const int *start, Rec *rec, int *rank, int *cnt, const BatchDev *B,
+                          const unsigned int *err) {
   if (P.n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_scatter, dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, s, P, cid,
-                     slot, start, rec, rank, B ? B->box_of : nullptr,
-                     B ? (const unsigned int *)B->flags : nullptr);
+                     slot, start, rec, rank, cnt, B ? B->box_of : nullptr, err);
   return hipGetLastError();
 }
 
@@ -979,51 +1072,64 @@ __device__ __forceinline__ void detect_cell64(const DetectArgs &A, const Grid &G
   // or after later cells of the same grid
 }
 
-// The binary32 filter over A.cpw consecutive cells per workgroup (see
-// k_detect_half64).
-__global__ __launch_bounds__(WAVE) void k_detect_half32(DetectArgs A) {
-  __shared__ int2 survq[QCAP];
-  SurvivorQueue Q{survq, 0, 0u, QCAP, 0ull};
-  __shared__ Rec32 hl[HB32];
-  __shared__ RunT rt[MAXRUN];
-  const int c0 = xcd_remap(blockIdx.x, gridDim.x) * A.cpw;
-  const int c1 = c0 + A.cpw < A.G.ncell ? c0 + A.cpw : A.G.ncell;
-  for (int cell = c0; cell < c1; ++cell) {
-    detect_cell32(A, A.G, A.start, cell, Q, hl, rt);
-    if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, A.G, Q);
+// Both filters run over cpw consecutive cells per workgroup, so the survivor
+// queue carries over between them and is decided a wave at a time (a cell of 13
+// spheres leaves about 13 survivors, so deciding them per cell runs the rule's
+// square root and division on a fifth of the lanes).  The grid, the tolerances
+// and cpw are the plan's; the host's launch is sized for the last step's grid,
+// so a workgroup takes further groups of cells if this step has more.  One add
+// per workgroup to the counters, which the waves do not wait for.
+template <typename Cells>
+__device__ __forceinline__ void detect_groups(const DetectArgs &A, int ncell, int cpw,
+                                              SurvivorQueue &Q, Cells cells) {
+  const int groups = (ncell + cpw - 1) / cpw;
+  for (int g = blockIdx.x; g < groups; g += gridDim.x) {
+    const int c0 = xcd_remap(g, groups) * cpw;
+    cells(c0, c0 + cpw < ncell ? c0 + cpw : ncell);
   }
-  // the workgroup's counts, summed by launch_cell_counts (a counter atomic per
-  // wave would serialise over the million cells)
-  if (__lane_id() == 0) A.cellc[blockIdx.x] = CellCount{Q.tests, Q.pushed};
+  if (__lane_id() == 0 && Q.tests) {
+    atomicAdd(&my_shard(A.ctr).tests, Q.tests);
+    if (Q.pushed) atomicAdd(&my_shard(A.ctr).recheck, (unsigned long long)Q.pushed);
+  }
 }
 
-// The binary64 filter over A.cpw consecutive cells per workgroup: the survivor
-// queue carries over between them and is decided a wave at a time (a cell of
-// 13 spheres leaves about 13 survivors, so deciding them per cell runs the
-// rule's square root and division on a fifth of the lanes).
+__global__ __launch_bounds__(WAVE) void k_detect_half32(DetectArgs A) {
+  if (A.plan->err) return;
+  __shared__ int2 survq[QCAP];
+  __shared__ Rec32 hl[HB32];
+  __shared__ RunT rt[MAXRUN];
+  SurvivorQueue Q{survq, 0, 0u, QCAP, 0ull};
+  const Grid G = A.plan->G;
+  A.kband = A.plan->kband;
+  A.dt2f = A.plan->dt2f;
+  detect_groups(A, G.ncell, A.plan->cpw, Q, [&](int c0, int c1) {
+    for (int cell = c0; cell < c1; ++cell) {
+      detect_cell32(A, G, A.start, cell, Q, hl, rt);
+      if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
+    }
+  });
+}
+
 __global__ __launch_bounds__(WAVE, 5) void k_detect_half64(DetectArgs A) {
+  if (A.plan->err) return;
   __shared__ int2 survq[QCAP64];
   __shared__ double hbeta[WAVE];
   __shared__ RunT rt[MAXRUN];
   SurvivorQueue Q{survq, 0, 0u, QCAP64, 0ull};
-  const int c0 = xcd_remap(blockIdx.x, gridDim.x) * A.cpw;
-  const int c1 = c0 + A.cpw < A.G.ncell ? c0 + A.cpw : A.G.ncell;
-  // the next cell's starts are loaded while this cell is tested
-  int code = 0;
-  int v = c0 < c1 ? cell_starts(A.G, A.start, c0, code) : 0;
-  for (int cell = c0; cell < c1; ++cell) {
-    const int vc = v;
-    const int cc = code;
-    if (cell + 1 < c1) v = cell_starts(A.G, A.start, cell + 1, code);
-    detect_cell64(A, A.G, vc, cc, Q, hbeta, rt);
-    if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, A.G, Q);
-  }
-  if (__lane_id() == 0) A.cellc[blockIdx.x] = CellCount{Q.tests, 0ull};
-}
-
-// Workgroups of launch_detect_half (one wave each), each writing one CellCount.
-int detect_half_blocks(const DetectArgs &A) {
-  return (A.G.ncell + A.cpw - 1) / A.cpw;
+  const Grid G = A.plan->G;
+  A.tol64 = A.plan->tol64;
+  detect_groups(A, G.ncell, A.plan->cpw, Q, [&](int c0, int c1) {
+    // the next cell's starts are loaded while this cell is tested
+    int code = 0;
+    int v = cell_starts(G, A.start, c0, code);
+    for (int cell = c0; cell < c1; ++cell) {
+      const int vc = v;
+      const int cc = code;
+      if (cell + 1 < c1) v = cell_starts(G, A.start, cell + 1, code);
+      detect_cell64(A, G, vc, cc, Q, hbeta, rt);
+      if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
+    }
+  });
 }
 
 // Box of a global cell number: the last b with cell_base[b] <= c.
@@ -1073,37 +1179,15 @@ __global__ __launch_bounds__(WAVE) void k_detect_batched(DetectArgs A, BatchDev 
   }
 }
 
-// Sum of the per-cell counts of the k_detect_half kernels (a few cells per
-// thread, so the loads of a thread are few and in flight together; one atomic
-// per workgroup and counter, spread over the shards).
-__global__ __launch_bounds__(256) void k_cell_counts(const CellCount *c, int n,
-                                                     SweepCounters *ctr) {
-  unsigned long long t = 0ull, r = 0ull;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    t += c[i].tests;
-    r += c[i].recheck;
-  }
-  block_add(t, &my_shard(ctr).tests);
-  block_add(r, &my_shard(ctr).recheck);
-}
-
-hipError_t launch_cell_counts(hipStream_t s, const CellCount *c, int n, SweepCounters *ctr) {
-  if (n <= 0) return hipSuccess;
-  int g = (n + 255) / 256;
-  if (g > 2048) g = 2048;
-  hipLaunchKernelGGL(k_cell_counts, dim3(g), dim3(256), 0, s, c, n, ctr);
-  return hipGetLastError();
-}
-
-hipError_t launch_detect_half(hipStream_t s, const DetectArgs &A) {
-  if (A.G.ncell <= 0) return hipSuccess;
-  if (A.fp32)
-    hipLaunchKernelGGL(k_detect_half32, dim3(detect_half_blocks(A)), dim3(WAVE), 0, s, A);
+// groups: the workgroups that the host expects (any number will do)
+hipError_t launch_detect_half(hipStream_t s, const DetectArgs &A, bool fp32, int groups) {
+  groups = (std::max(groups, 1) + 7) / 8 * 8;  // whole rounds of the XCDs
+  if (fp32)
+    hipLaunchKernelGGL(k_detect_half32, dim3(groups), dim3(WAVE), 0, s, A);
   else
-    hipLaunchKernelGGL(k_detect_half64, dim3(detect_half_blocks(A)), dim3(WAVE), 0, s, A);
+    hipLaunchKernelGGL(k_detect_half64, dim3(groups), dim3(WAVE), 0, s, A);
   return hipGetLastError();
 }
-
 
 // ---------------------------------------------------------------- a5/a7: partner from contact slots
 
@@ -1170,8 +1254,11 @@ __global__ __launch_bounds__(256) void k_slot_min(int n, const int *cnt, const d
                                                   const int *slot_j, int K, const Rec *rec,
                                                   int *key_j, double *key_t, int *ovf_list,
                                                   SweepCounters *ctr, const unsigned int *err,
-                                                  Grid G, const unsigned long long *crank) {
-  if (err && *err) return;
+                                                  const Grid *Gp,
+                                                  const unsigned long long *crank) {
+  if (*err) return;
+  Grid G{};  // the walls are all that matters here (none in the batched form)
+  if (Gp) G = *Gp;
   const int i = blockIdx.x * 256 + threadIdx.x;
   bool ovf = false;
   unsigned long long nc = 0ull;
@@ -1196,9 +1283,8 @@ hipError_t launch_slot_min(hipStream_t s, int n, const int *cnt, const double *s
                            int *ovf_list, SweepCounters *ctr, const unsigned int *err,
                            const Grid *G, const unsigned long long *crank) {
   if (n <= 0) return hipSuccess;
-  const Grid none{};  // walls = 0: periodic
   hipLaunchKernelGGL(k_slot_min, dim3((n + 255) / 256), dim3(256), 0, s, n, cnt, slot_t, slot_j, K,
-                     rec, key_j, key_t, ovf_list, ctr, err, G ? *G : none, crank);
+                     rec, key_j, key_t, ovf_list, ctr, err, G, crank);
   return hipGetLastError();
 }
 
@@ -1224,10 +1310,11 @@ __device__ __forceinline__ unsigned long long morton3(unsigned int cx, unsigned 
 // (nc cells of side h per axis) above its caller index,
 // crank = code << 31 | o, in cell-sorted order.  A sphere's cell is
 // floor(x / h) in binary64, clamped to nc - 1.
-__global__ __launch_bounds__(256) void k_curve_rank(const Rec *rec, int n, CurveGrid C,
+__global__ __launch_bounds__(256) void k_curve_rank(const Rec *rec, int n, const StepPlan *plan,
                                                     unsigned long long *crank) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
+  if (i >= n || plan->err) return;
+  const CurveGrid &C = plan->C;
   const Rec a = rec[i];
   const double p[3] = {a.x, a.y, a.z};
   unsigned int c[3];
@@ -1241,10 +1328,10 @@ __global__ __launch_bounds__(256) void k_curve_rank(const Rec *rec, int n, Curve
   crank[i] = morton3(c[0], c[1], c[2]) << 31 | (unsigned long long)(unsigned int)a.o;
 }
 
-hipError_t launch_curve_rank(hipStream_t s, const Rec *rec, int n, const CurveGrid &C,
+hipError_t launch_curve_rank(hipStream_t s, const Rec *rec, int n, const StepPlan *plan,
                              unsigned long long *crank) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_curve_rank, dim3((n + 255) / 256), dim3(256), 0, s, rec, n, C, crank);
+  hipLaunchKernelGGL(k_curve_rank, dim3((n + 255) / 256), dim3(256), 0, s, rec, n, plan, crank);
   return hipGetLastError();
 }
 
@@ -1377,18 +1464,21 @@ __device__ __forceinline__ void wide_run(const Grid &G, const int *start, int r,
 // the scanned lengths held across the wave.  An FMA pre-filter (tolerance for
 // the full reach) keeps the exact rule for the few pairs that may touch;
 // survivors are decided at once (they are rare).
-__global__ __launch_bounds__(256) void k_detect_wide(DetectArgs A, const int *first_dev, int n) {
-  const int first = *first_dev, count = n - first;
+__global__ __launch_bounds__(256) void k_detect_wide(DetectArgs A) {
+  if (A.plan->err || !A.plan->G.layer2) return;
+  const Grid G = A.plan->G;
+  const double rho_c = A.plan->rho_c, tol_wide = A.plan->tol_wide;
+  const int n = A.n;
+  const int first = A.start[G.layer2], count = n - first;
   const int lane = __lane_id();
   const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
   const int nw = (gridDim.x * blockDim.x) / WAVE;
-  const Grid &G = A.G;
   unsigned long long tests = 0ull;
   for (int w = wid; w < count; w += nw) {
     const int p = first + w;
     const Rec a = A.rec[p];
     const double ea = extent(a.r, a.vx, a.vy, a.vz, A.dt);
-    const double R[2] = {(ea + A.rho_c) * (1.0 + 1e-9), (ea + G.rho_max) * (1.0 + 1e-9)};
+    const double R[2] = {(ea + rho_c) * (1.0 + 1e-9), (ea + G.rho_max) * (1.0 + 1e-9)};
     int k[3];
     for (int ax = 0; ax < 3; ++ax) k[ax] = (int)ceil(R[1] / G.h[ax]);
     const int cx = cell_coord(a.x, G.inv_h[0], G.nc[0]);
@@ -1437,7 +1527,7 @@ __global__ __launch_bounds__(256) void k_detect_wide(DetectArgs A, const int *fi
           const double cf =
               __builtin_fma(d0, d0, __builtin_fma(d1, d1, __builtin_fma(d2, d2, -(s * s))));
           double t;
-          if (__builtin_fma(bf, A.dt2, cf) <= A.tol_wide &&
+          if (__builtin_fma(bf, A.dt2, cf) <= tol_wide &&
               contact_time(d0, d1, d2, u0, u1, u2, s, A.dt, t))
             record_contact(A, p, j, t);
         }
@@ -1447,15 +1537,15 @@ __global__ __launch_bounds__(256) void k_detect_wide(DetectArgs A, const int *fi
   block_add(tests, &my_shard(A.ctr).tests);
 }
 
-hipError_t launch_detect_wide(hipStream_t s, const DetectArgs &A, const int *first_dev, int n) {
+hipError_t launch_detect_wide(hipStream_t s, const DetectArgs &A) {
+  const int n = A.n;
   if (n <= 0) return hipSuccess;
   // the range is on the device (no read-back before the launch): waves loop
   // over it; about one wave per 256 spheres (the split puts about 0.1% of them
   // in the second layer), 64 to 4096
   int64_t waves = n / 256;
   waves = waves < 64 ? 64 : (waves > 4096 ? 4096 : waves);
-  hipLaunchKernelGGL(k_detect_wide, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, A,
-                     first_dev, n);
+  hipLaunchKernelGGL(k_detect_wide, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, A);
   return hipGetLastError();
 }
 
@@ -1526,11 +1616,13 @@ __device__ __forceinline__ void exact_partner(int i, const Rec &a, const Grid &G
 // grids with fewer than 3 cells along some axis.
 __global__ __launch_bounds__(256) void k_gather_exact(const int *list, int nlist,
                                                       const unsigned int *nlist_dev, int select,
-                                                      const Rec *rec, const int *start, Grid G0,
-                                                      double dt, const uint8_t *status, int *key_j,
+                                                      const Rec *rec, const int *start,
+                                                      const Grid *Gp, double dt,
+                                                      const uint8_t *status, int *key_j,
                                                       double *key_t, BatchDev B,
+                                                      const unsigned int *err,
                                                       const unsigned long long *crank) {
-  if (B.flags && B.flags[FLAG_ERR]) return;
+  if (*err) return;
   const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
   const int nw = (gridDim.x * blockDim.x) / WAVE;
   const int count = nlist_dev ? (int)*nlist_dev : nlist;
@@ -1540,7 +1632,7 @@ __global__ __launch_bounds__(256) void k_gather_exact(const int *list, int nlist
     // the sphere's grid: the single one, or its box's in the batched form
     const Rec a = rec[i];
     const int bx = B.gtab ? a.box : 0;
-    const Grid G = B.gtab ? B.gtab[bx] : G0;
+    const Grid G = B.gtab ? B.gtab[bx] : *Gp;
     const int *st = B.gtab ? start + B.cell_base[bx] : start;
     int bj;
     double bt;
@@ -1554,9 +1646,10 @@ __global__ __launch_bounds__(256) void k_gather_exact(const int *list, int nlist
 }
 
 hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const unsigned int *nlist_dev,
-                               int select, const Rec *rec, const int *start, const Grid &G,
+                               int select, const Rec *rec, const int *start, const Grid *G,
                                double dt, const uint8_t *status, int *key_j, double *key_t,
-                               const BatchDev *B, const unsigned long long *crank) {
+                               const BatchDev *B, const unsigned int *err,
+                               const unsigned long long *crank) {
   // a list whose length is on the device is short: a wave for 64 of the nlist
   // spheres it could name at most, in 16 to 2048 workgroups
   int64_t waves = nlist_dev ? std::max((int64_t)64, (int64_t)nlist / 64) : nlist;
@@ -1565,7 +1658,7 @@ hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const 
   const int blocks = (int)((waves + 3) / 4);
   BatchDev none{};
   hipLaunchKernelGGL(k_gather_exact, dim3(blocks), dim3(256), 0, s, list, nlist, nlist_dev, select,
-                     rec, start, G, dt, status, key_j, key_t, B ? *B : none, crank);
+                     rec, start, G, dt, status, key_j, key_t, B ? *B : none, err, crank);
   return hipGetLastError();
 }
 
@@ -1588,12 +1681,12 @@ __device__ __forceinline__ unsigned long long resolve_pair(const SweepArgs &A, i
     const double wa[3] = {S.wx[a.o], S.wy[a.o], S.wz[a.o]};
     const double wb[3] = {S.wx[b.o], S.wy[b.o], S.wz[b.o]};
     double xo[3], vo[3], wo[3];
-    resolve_one_spin(a, b, ma, mb, wa, wb, A.G, t, A.dt, A.e, S.mu, xo, vo, wo);
+    resolve_one_spin(a, b, ma, mb, wa, wb, *A.G, t, A.dt, A.e, S.mu, xo, vo, wo);
     A.out[i] = OutRec{xo[0], xo[1], xo[2], vo[0], vo[1], vo[2], t, b.o, 0u};
     S.wx[a.o] = wo[0];
     S.wy[a.o] = wo[1];
     S.wz[a.o] = wo[2];
-    resolve_one_spin(b, a, mb, ma, wb, wa, A.G, t, A.dt, A.e, S.mu, xo, vo, wo);
+    resolve_one_spin(b, a, mb, ma, wb, wa, *A.G, t, A.dt, A.e, S.mu, xo, vo, wo);
     A.out[p] = OutRec{xo[0], xo[1], xo[2], vo[0], vo[1], vo[2], t, a.o, 0u};
     S.wx[b.o] = wo[0];
     S.wy[b.o] = wo[1];
@@ -1610,7 +1703,7 @@ __device__ __forceinline__ unsigned long long resolve_pair(const SweepArgs &A, i
     const Grid G = A.B.gtab[a.box];
     resolve_one(a, b, ma, mb, G, t, A.dt, A.e, xo, vo);
   } else {
-    resolve_one(a, b, ma, mb, A.G, t, A.dt, A.e, xo, vo);
+    resolve_one(a, b, ma, mb, *A.G, t, A.dt, A.e, xo, vo);
   }
   A.out[i] = OutRec{xo[0], xo[1], xo[2], vo[0], vo[1], vo[2], t, b.o, 0u};
   A.status[i] = ST_COLLIDED;
@@ -1662,7 +1755,7 @@ __device__ __forceinline__ void list_append(bool keep, int i, int *count, int *l
 // workgroups, and with them one address for most of the chip: 600 us at 16M).
 template <bool SPIN>
 __global__ __launch_bounds__(256) void k_sweep_first(SweepArgs A, const int *key) {
-  if ((A.err && *A.err) || (!A.exact && A.ctr->n_overflow != 0u)) return;
+  if (*A.err || (!A.exact && A.ctr->n_overflow != 0u)) return;
   const int i = blockIdx.x * 256 + threadIdx.x;
   unsigned long long npair = 0ull;
   bool keep = false;
@@ -1734,8 +1827,10 @@ __device__ __forceinline__ void new_partner(const SweepArgs &A, bool need, int i
   if (need) {
     const int c = EXACT && A.small ? 0 : A.cnt[i];
     search = EXACT && (A.small || c > A.K);
+    Grid G{};  // the walls are all that matters here (none in the batched form)
+    if (A.G) G = *A.G;
     if (!search)
-      slot_choice(i, c, (size_t)A.n, A.slot_t, A.slot_j, A.rec, A.G, A.crank, gone, bj, bt);
+      slot_choice(i, c, (size_t)A.n, A.slot_t, A.slot_j, A.rec, G, A.crank, gone, bj, bt);
   }
   if (!EXACT) return;
   unsigned long long todo = __builtin_amdgcn_ballot_w64(search);
@@ -1754,7 +1849,7 @@ __device__ __forceinline__ void new_partner(const SweepArgs &A, bool need, int i
       exact_partner(w, a, A.B.gtab[a.box], A.start + A.B.cell_base[a.box], A.rec, A.dt, A.crank,
                     is_gone, j, t);
     else
-      exact_partner(w, a, A.G, A.start, A.rec, A.dt, A.crank, is_gone, j, t);
+      exact_partner(w, a, *A.G, A.start, A.rec, A.dt, A.crank, is_gone, j, t);
     if ((int)__lane_id() == l) {
       bj = j;
       bt = t;
@@ -1768,7 +1863,7 @@ __device__ __forceinline__ void new_partner(const SweepArgs &A, bool need, int i
 // costs 30 registers, so steps without overflow go without.
 template <bool EXACT>
 __device__ __forceinline__ bool sweep_off(const SweepArgs &A) {
-  return (A.err && *A.err) || (!EXACT && A.ctr->n_overflow != 0u);
+  return *A.err || (!EXACT && A.ctr->n_overflow != 0u);
 }
 
 // The partners of the spheres that sweep 1 left DIRTY (in place: only DIRTY keys
@@ -1914,6 +2009,7 @@ __device__ __forceinline__ void write_report(const SweepCounters *ctr, int nswee
       rep->recheck = r;
       rep->tests = e;
       rep->n_overflow = ctr->n_overflow + ctr->ovf_later;
+      rep->maxcell = ctr->maxcell;
     }
   }
 }
@@ -1928,11 +2024,16 @@ __device__ __forceinline__ void write_report(const SweepCounters *ctr, int nswee
 // last-level cache).
 __global__ __launch_bounds__(256) void k_finish(Particles P, const int *rank,
                                                 const OutRec *out, const uint8_t *status,
-                                                int *partner, double *tcoll, double dt, Grid G0,
-                                                BatchDev B, const SweepCounters *ctr, int nsweep,
-                                                int exact, StepReport *rep) {
-  if (blockIdx.x == 0) write_report(ctr, nsweep, rep);
-  if ((B.flags && B.flags[FLAG_ERR]) || (!exact && ctr->n_overflow != 0u) ||
+                                                int *partner, double *tcoll, double dt,
+                                                const StepPlan *plan, const int *start, BatchDev B,
+                                                const SweepCounters *ctr, int nsweep, int exact,
+                                                const unsigned int *err, StepReport *rep) {
+  if (blockIdx.x == 0) {
+    write_report(ctr, nsweep, rep);
+    if (plan && threadIdx.x == 0)
+      rep->wide_first = !*err && plan->G.layer2 ? start[plan->G.layer2] : (int)P.n;
+  }
+  if (*err || (!exact && ctr->n_overflow != 0u) ||
       sweep_pairs(ctr, nsweep - 1) != 0ull)
     return;
   const int64_t o = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -1951,8 +2052,8 @@ __global__ __launch_bounds__(256) void k_finish(Particles P, const int *rank,
     t = r.t;
     pj = r.partner;
   } else {
-    const double *L = B.gtab ? B.gtab[B.box_of[o]].L : G0.L;
-    const int walls = B.gtab ? 0 : G0.walls;  // the batched form has periodic boxes only
+    const double *L = plan ? plan->G.L : B.gtab[B.box_of[o]].L;
+    const int walls = plan ? plan->G.walls : 0;  // the batched form has periodic boxes only
     vx = P.vx[o];
     vy = P.vy[o];
     vz = P.vz[o];
@@ -1974,12 +2075,14 @@ __global__ __launch_bounds__(256) void k_finish(Particles P, const int *rank,
 
 hipError_t launch_finish(hipStream_t s, const Particles &P, const int *rank, const OutRec *out,
                          const uint8_t *status, int *partner, double *tcoll, double dt,
-                         const Grid &G, const BatchDev *B, const SweepCounters *ctr, int nsweep,
-                         bool exact, StepReport *rep) {
+                         const StepPlan *plan, const int *start, const BatchDev *B,
+                         const SweepCounters *ctr, int nsweep, bool exact, const unsigned int *err,
+                         StepReport *rep) {
   if (P.n <= 0) return hipSuccess;
   BatchDev none{};
   hipLaunchKernelGGL(k_finish, dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, s, P, rank, out,
-                     status, partner, tcoll, dt, G, B ? *B : none, ctr, nsweep, (int)exact, rep);
+                     status, partner, tcoll, dt, plan, start, B ? *B : none, ctr, nsweep,
+                     (int)exact, err, rep);
   return hipGetLastError();
 }
 
