@@ -609,14 +609,17 @@ static pcol_status check_binned(pcol_ctx *ctx, const pcol_particles *p, const pc
 
 // sweep 1: keys of all spheres (all active) into ctx->key_j / key_t (sorted
 // order); crank given: the literal order's partners instead of rule 2's
-static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long *crank) {
+// status given: of the ACTIVE spheres only, and only if *err (the caller's word) is 0
+static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long *crank,
+                              const uint8_t *status = nullptr,
+                              const unsigned int *masked_err = nullptr) {
   hipStream_t s = ctx->stream;
   const int n = (int)ctx->binned_n;
   // sized by the last plan that the host has seen: this binning's, or for a step
   // that has not waited yet the one before it (which then had no small grid, and a
   // split grid if this one has)
   const StepPlan &pl = ctx->plan;
-  const unsigned int *err = &ctx->plan_d->err;
+  const unsigned int *err = status ? masked_err : &ctx->plan_d->err;
   const Grid *G = &ctx->plan_d->G;
   if (!pl.small) {
     DetectArgs A{};
@@ -629,6 +632,7 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     A.n = n;
     A.K = ctx->K;
     A.plan = ctx->plan_d;
+    A.err = err;
     A.dt = dt;
     A.dt2 = 2.0 * dt * (1.0 + 0x1.0p-20);
     if (ctx->opts.timing) PCOL_HIP(hipEventRecord(ctx->ev[5], s));
@@ -639,9 +643,9 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     if (ctx->opts.timing) PCOL_HIP(hipEventRecord(ctx->ev[6], s));
     ctx->detect_timed = true;
     PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
-                             ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err, G, crank));
+                             ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err, G, crank, status));
     PCOL_HIP(launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
-                                 G, dt, nullptr, ctx->key_j, ctx->key_t, nullptr, err, crank));
+                                 G, dt, status, ctx->key_j, ctx->key_t, nullptr, err, crank));
   } else {
     // fewer than 3 cells on some axis: exact search for every sphere
     PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, -1, ctx->rec, ctx->start, G, dt,
@@ -659,16 +663,20 @@ pcol_status pcol_detect(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *
   hipStream_t s = ctx->stream;
   const int n = (int)p->n;
   if (n == 0) return PCOL_OK;
+  PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
   if (!active) {
-    PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
     PCOL_HIP(launch_fill_i32(s, ctx->cnt, 0, n));
     if ((st = detect_all(ctx, dt, nullptr)) != PCOL_OK) return st;
   } else {
-    PCOL_HIP(launch_status_from_active(s, active, ctx->rec, n, ctx->status));
-    PCOL_HIP(launch_fill_i32(s, ctx->key_j, -1, n));
+    // the pair tests of all spheres if many of them are active, else (or on a small
+    // grid) the exact search of each active one; the device decides
+    PCOL_HIP(launch_status_from_active(s, active, ctx->rec, n, ctx->status, ctx->cnt, ctx->ctr_d));
+    const bool small = ctx->plan.small != 0;
+    if (!small && (st = detect_all(ctx, dt, nullptr, ctx->status, &ctx->ctr_d->pairs_off)) != PCOL_OK)
+      return st;
     PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, ST_ACTIVE, ctx->rec, ctx->start,
                                  &ctx->plan_d->G, dt, ctx->status, ctx->key_j, ctx->key_t, nullptr,
-                                 &ctx->plan_d->err));
+                                 small ? &ctx->plan_d->err : &ctx->ctr_d->sparse_off));
   }
   PCOL_HIP(launch_export_keys(s, n, ctx->rec, ctx->key_j, ctx->key_t,
                               active ? ctx->status : nullptr, key_out, tmin_out));

@@ -360,7 +360,8 @@ struct SweepCounters {
   unsigned int n_overflow;  // spheres with more contacts than slots (list length)
   unsigned int ovf_later;   // the same among those that took a new partner later
   unsigned int maxcell;     // largest cell occupancy
-  unsigned int pad[29];
+  unsigned int pairs_off, sparse_off;  // masked detect: the one of its two ways not taken
+  unsigned int pad[27];
   unsigned long long pairs[MAX_QUEUE][PAIR_SHARDS];  // pairs resolved by each later sweep
 };
 
@@ -657,6 +658,7 @@ struct DetectArgs {
   int n;              // spheres (slot arrays are k-major: slot[k * n + i])
   int K;
   const StepPlan *plan;  // one box: grid and tolerances (null in the batched form)
+  const unsigned int *err;  // one box: nonzero: do nothing
   double dt;
   double dt2;         // 2 dt (1 + 2^-20): step bound of the FP64 filter
   double tol64;       // binary64 Gram filter tolerance (see gram64_tolerance)
@@ -694,7 +696,8 @@ hipError_t launch_slot_min(hipStream_t s, int n, const int *cnt, const double *s
                            const int *slot_j, int K, const Rec *rec, int *key_j, double *key_t,
                            int *ovf_list, SweepCounters *ctr, const unsigned int *err,
                            const Grid *G = nullptr,  // device: walls of the box (none: periodic)
-                           const unsigned long long *crank = nullptr);  // literal order's ranks
+                           const unsigned long long *crank = nullptr,  // literal order's ranks
+                           const uint8_t *status = nullptr);  // only ACTIVE spheres take part
 hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const unsigned int *nlist_dev,
                                int select, const Rec *rec, const int *start, const Grid *G,
                                double dt, const uint8_t *status, int *key_j, double *key_t,
@@ -729,8 +732,9 @@ hipError_t launch_detect_batched(hipStream_t s, const DetectArgs &A, const Batch
                                  int total_cells, int cpw);
 hipError_t launch_advance(hipStream_t s, const Particles &P, const int *partner, double dt,
                           const double L[3]);
+// ctr zero on entry; sets its pairs_off and sparse_off
 hipError_t launch_status_from_active(hipStream_t s, const uint8_t *active, const Rec *rec, int n,
-                                     uint8_t *status);
+                                     uint8_t *status, int *cnt, SweepCounters *ctr);
 hipError_t launch_export_keys(hipStream_t s, int n, const Rec *rec, const int *key_j,
                               const double *key_t, const uint8_t *status, uint64_t *key_out,
                               double *tmin_out);
