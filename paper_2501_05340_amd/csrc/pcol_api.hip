@@ -259,39 +259,32 @@ pcol_status deposit_args(const double *x, const double *y, const double *z, int6
   return PCOL_OK;
 }
 
-// The deposition on stream s with its scratch at base (laid out by Lo): the
-// count checks every position and is read back (into flag_h, host memory)
-// before anything of the caller's is written; st receives PCOL_E_INVALID for a
-// bad position, else PCOL_OK.  Counts and the flag are cleared by fill kernels.
+// The deposition on stream s with its scratch at base (laid out by Lo).  The count
+// checks every position, and the kernels behind it do nothing if one is bad, so
+// all are queued at once and the flag is read at the end (into flag_h, host
+// memory; pinned: the last kernel writes it there itself); st receives
+// PCOL_E_INVALID for a bad position, else PCOL_OK.
 hipError_t deposit_run(DepositArgs &D, const DepositLayout &Lo, unsigned char *base, hipStream_t s,
-                       unsigned int *flag_h, pcol_status &st) {
+                       unsigned int *flag_h, bool pinned, pcol_status &st) {
   st = PCOL_OK;
   D.eid = (int *)(base + Lo.eid);
   D.slot = (int *)(base + Lo.slot);
   D.rec = base + Lo.rec;
   D.cnt = (int *)(base + Lo.cnt);
   D.start = (int *)(base + Lo.start);
-  unsigned int *flag = (unsigned int *)(base + Lo.flag);
-  ScanState *scan = (ScanState *)(base + Lo.scan);
-  hipError_t e = launch_fill_i32(s, D.cnt, 0, D.nnode);
-  if (e != hipSuccess) return e;
-  const int64_t words = 2 * ((D.nnode + SCAN_B - 1) / SCAN_B + 1);
-  if ((e = launch_fill_u32(s, (unsigned int *)scan, 0u, words + 2)) != hipSuccess) return e;
-  if (D.n > 0) {  // the count checks the positions; nothing of the caller's is written yet
-    if ((e = launch_fill_u32(s, flag, 0u, 1)) != hipSuccess) return e;
-    if ((e = launch_deposit_count(s, D, flag)) != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(flag_h, flag, sizeof(unsigned int), hipMemcpyDeviceToHost, s)) !=
-        hipSuccess)
-      return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    if (*flag_h) {
-      st = PCOL_E_INVALID;
-      return hipSuccess;
-    }
-  }
-  if ((e = launch_scan(s, D.cnt, (int)D.nnode, nullptr, D.start, scan, nullptr)) != hipSuccess)
-    return e;
-  return launch_deposit(s, D);
+  D.scan = (ScanState *)(base + Lo.scan);
+  D.flag = (unsigned int *)(base + Lo.flag);
+  D.flag_host = pinned ? flag_h : nullptr;
+  hipError_t e = launch_deposit_count(s, D);
+  if (e == hipSuccess)
+    e = launch_scan(s, D.cnt, (int)D.nnode, nullptr, D.start, D.scan, nullptr);
+  if (e == hipSuccess) e = launch_deposit(s, D);
+  if (e != hipSuccess || D.n == 0) return e;
+  if (!pinned)
+    e = hipMemcpyAsync(flag_h, D.flag, sizeof(unsigned int), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess && *flag_h) st = PCOL_E_INVALID;
+  return e;
 }
 
 }  // namespace
@@ -976,7 +969,7 @@ pcol_status pcol_deposit(pcol_ctx *ctx, const double *x, const double *y, const 
                   "deposition scratch allocation failed");
     }
   }
-  hipError_t e = deposit_run(D, Lo, ctx->dep_buf, s, ctx->dep_flag_h, st);
+  hipError_t e = deposit_run(D, Lo, ctx->dep_buf, s, ctx->dep_flag_h, true, st);
   if (e != hipSuccess) return hip_fail(ctx, e, "pcol_deposit");
   if (st != PCOL_OK) return fail(ctx, st, "position outside [0, L) or not finite");
   return PCOL_OK;
@@ -994,7 +987,7 @@ pcol_status pcol_deposit_noalloc(const double *x, const double *y, const double 
   unsigned char *base = nullptr;
   if (static_scratch(&base) != hipSuccess) return PCOL_E_HIP;
   unsigned int flag_h = 0u;  // pageable host word: no pinned allocation
-  if (deposit_run(D, Lo, base, (hipStream_t)hip_stream, &flag_h, st) != hipSuccess)
+  if (deposit_run(D, Lo, base, (hipStream_t)hip_stream, &flag_h, false, st) != hipSuccess)
     return PCOL_E_HIP;
   return st;
 }

@@ -745,8 +745,7 @@ hipError_t launch_step_backward(hipStream_t s, const Particles &P, const Grid &G
 // Deposition of per-sphere sources onto the corner nodes of a periodic
 // Cartesian grid: positions x, y, z (n), sources a[q * n + i] (comp <= 8),
 // nc cells of side h = L / nc per axis, out[node * comp + q] (nnode nodes,
-// one per element).  Scratch: eid, slot (n each), cnt (nnode, zeroed before the
-// count), start (nnode + 1), rec (n records of deposit_record_bytes(comp)).
+// one per element).  Scratch: eid, slot (n each), cnt (nnode), start (nnode + 1), rec (n records of deposit_record_bytes(comp)).
 struct DepositArgs {
   const double *x, *y, *z, *a;
   int64_t n;
@@ -757,11 +756,14 @@ struct DepositArgs {
   double *out;
   int *eid, *slot, *cnt, *start;
   void *rec;
+  ScanState *scan;
+  unsigned int *flag;       // a position is bad: nothing of the caller's is written
+  unsigned int *flag_host;  // nullable: host memory that receives the flag
 };
 int64_t deposit_record_bytes(int comp);
-// element and slot of every sphere (cnt must be zero); positions outside
-// [0, L) or not finite set bit 0 of *flag and are skipped
-hipError_t launch_deposit_count(hipStream_t s, const DepositArgs &D, unsigned int *flag);
+// element and slot of every sphere (clears cnt, scan and flag first); positions
+// outside [0, L) or not finite set bit 0 of *flag and are skipped
+hipError_t launch_deposit_count(hipStream_t s, const DepositArgs &D);
 // after the scan of cnt into start: scatter, then element corner sums and node
 // sums over tiles of nodes
 hipError_t launch_deposit(hipStream_t s, const DepositArgs &D);

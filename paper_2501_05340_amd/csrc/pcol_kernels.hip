@@ -2557,12 +2557,24 @@ __device__ __forceinline__ int dep_cell(double p, double h, int nc, double &f) {
   return c;
 }
 
+// Zero element counts, scan words and position flag.
+__global__ __launch_bounds__(256) void k_dep_clear(DepositArgs D, int words) {
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = t; i < D.nnode; i += step) D.cnt[i] = 0;
+  for (int64_t i = t; i < words; i += step) D.scan->word[i] = 0ull;
+  if (t == 0) {
+    D.scan->ticket = 0;
+    *D.flag = 0u;
+  }
+}
+
 // Element of every sphere and its slot among the element's spheres.  A
 // position outside [0, L) or not finite raises bit 0 of *flag and is not
-// counted (the host reads the flag before anything else runs).  Consecutive
+// counted (the kernels behind do nothing then).  Consecutive
 // lanes of one element (spheres stored in element order) take their slots with
 // one atomic per run.
-__global__ __launch_bounds__(256) void k_dep_count(DepositArgs D, unsigned int *flag) {
+__global__ __launch_bounds__(256) void k_dep_count(DepositArgs D) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int e = -1;  // -1: no element (past the end, or a bad position)
   bool bad = false;
@@ -2580,7 +2592,7 @@ __global__ __launch_bounds__(256) void k_dep_count(DepositArgs D, unsigned int *
   }
   const int lane = (int)__lane_id();
   const unsigned long long badm = __ballot(bad);
-  if (badm != 0ull && lane == __ffsll((long long)badm) - 1) atomicOr(flag, 1u);
+  if (badm != 0ull && lane == __ffsll((long long)badm) - 1) atomicOr(D.flag, 1u);
   const int sl = run_slot(e, D.cnt);
   if (e >= 0) {
     D.eid[i] = e;
@@ -2593,7 +2605,7 @@ __global__ __launch_bounds__(256) void k_dep_count(DepositArgs D, unsigned int *
 template <int COMP>
 __global__ __launch_bounds__(256) void k_dep_scatter(DepositArgs D) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= D.n) return;
+  if (i >= D.n || *D.flag) return;
   DepRec<COMP> r;
   r.p[0] = D.x[i];
   r.p[1] = D.y[i];
@@ -2679,6 +2691,8 @@ constexpr int DEP_TN = 7, DEP_TE = DEP_TN + 1, DEP_TILE_THREADS = DEP_TE * DEP_T
 
 template <int COMP>
 __global__ __launch_bounds__(DEP_TILE_THREADS) void k_dep_tile(DepositArgs D, int ntx, int nty) {
+  if (D.flag_host && blockIdx.x == 0 && threadIdx.x == 0) *D.flag_host = *D.flag;
+  if (*D.flag) return;
   __shared__ double nacc[DEP_TN * DEP_TN * DEP_TN * COMP];
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
   const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
@@ -2740,9 +2754,11 @@ hipError_t deposit_sorted(hipStream_t s, const DepositArgs &D) {
 
 int64_t deposit_record_bytes(int comp) { return ((int64_t)(4 + comp) * 8 + 15) / 16 * 16; }
 
-hipError_t launch_deposit_count(hipStream_t s, const DepositArgs &D, unsigned int *flag) {
-  if (D.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_dep_count, dim3((unsigned)((D.n + 255) / 256)), dim3(256), 0, s, D, flag);
+hipError_t launch_deposit_count(hipStream_t s, const DepositArgs &D) {
+  const int words = (int)((D.nnode + SCAN_B - 1) / SCAN_B) + 1;
+  hipLaunchKernelGGL(k_dep_clear, dim3(fill_grid(D.nnode)), dim3(256), 0, s, D, words);
+  if (D.n > 0)
+    hipLaunchKernelGGL(k_dep_count, dim3((unsigned)((D.n + 255) / 256)), dim3(256), 0, s, D);
   return hipGetLastError();
 }
 
