@@ -602,7 +602,8 @@ static pcol_status check_binned(pcol_ctx *ctx, const pcol_particles *p, const pc
 
 // sweep 1: keys of all spheres (all active) into ctx->key_j / key_t (sorted
 // order); crank given: the literal order's partners instead of rule 2's
-// status given: of the ACTIVE spheres only, and only if *err (the caller's word) is 0
+// status given: of the ACTIVE spheres only, and only if *masked_err is 0.  The
+// spheres whose contacts overflowed their slots get no key (overflow_search).
 static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long *crank,
                               const uint8_t *status = nullptr,
                               const unsigned int *masked_err = nullptr) {
@@ -637,13 +638,20 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     ctx->detect_timed = true;
     PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
                              ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err, G, crank, status));
-    PCOL_HIP(launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
-                                 G, dt, status, ctx->key_j, ctx->key_t, nullptr, err, crank));
   } else {
     // fewer than 3 cells on some axis: exact search for every sphere
     PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, -1, ctx->rec, ctx->start, G, dt,
                                  nullptr, ctx->key_j, ctx->key_t, nullptr, err, crank));
   }
+  return PCOL_OK;
+}
+
+// Keys, by the exact search, of the spheres that detect_all left out.
+static pcol_status overflow_search(pcol_ctx *ctx, double dt, const unsigned long long *crank,
+                                   const uint8_t *status, const unsigned int *err) {
+  PCOL_HIP(launch_gather_exact(ctx->stream, ctx->ovf, (int)ctx->binned_n, &ctx->ctr_d->n_overflow,
+                               -1, ctx->rec, ctx->start, &ctx->plan_d->G, dt, status, ctx->key_j,
+                               ctx->key_t, nullptr, err, crank));
   return PCOL_OK;
 }
 
@@ -660,12 +668,17 @@ pcol_status pcol_detect(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *
   if (!active) {
     PCOL_HIP(launch_fill_i32(s, ctx->cnt, 0, n));
     if ((st = detect_all(ctx, dt, nullptr)) != PCOL_OK) return st;
+    if (!ctx->plan.small &&
+        (st = overflow_search(ctx, dt, nullptr, nullptr, &ctx->plan_d->err)) != PCOL_OK)
+      return st;
   } else {
     // the pair tests of all spheres if many of them are active, else (or on a small
     // grid) the exact search of each active one; the device decides
     PCOL_HIP(launch_status_from_active(s, active, ctx->rec, n, ctx->status, ctx->cnt, ctx->ctr_d));
     const bool small = ctx->plan.small != 0;
-    if (!small && (st = detect_all(ctx, dt, nullptr, ctx->status, &ctx->ctr_d->pairs_off)) != PCOL_OK)
+    const unsigned int *off = &ctx->ctr_d->pairs_off;
+    if (!small && ((st = detect_all(ctx, dt, nullptr, ctx->status, off)) != PCOL_OK ||
+                   (st = overflow_search(ctx, dt, nullptr, ctx->status, off)) != PCOL_OK))
       return st;
     PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, ST_ACTIVE, ctx->rec, ctx->start,
                                  &ctx->plan_d->G, dt, ctx->status, ctx->key_j, ctx->key_t, nullptr,
@@ -786,6 +799,11 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
     SweepArgs W = sweep_args(ctx, P, dt, e);
     W.crank = crank;
     if (spin) W.spin = *spin;
+    // sweeps that cannot search stop at an overflow, so only the others need its keys
+    const unsigned int *err = &ctx->plan_d->err;
+    if (W.exact && !ctx->plan.small &&
+        (st = overflow_search(ctx, dt, crank, nullptr, err)) != PCOL_OK)
+      return st;
     // All the sweeps that the step is likely to take, and the free flight behind
     // them, are queued at once: a sweep runs if the one before it resolved a pair,
     // the free flight if the last one resolved none.  Steps that need more are
@@ -803,7 +821,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
       if (timing) PCOL_HIP(hipEventRecord(ctx->ev[3], s));
       PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, ctx->plan_d,
                              ctx->start, nullptr, ctx->ctr_d, end, W.exact != 0,
-                             &ctx->plan_d->err, ctx->rep));
+                             err, ctx->rep));
       PCOL_HIP(hipStreamSynchronize(s));
       if (ahead) {
         ahead = false;
@@ -813,6 +831,9 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
           W = sweep_args(ctx, P, dt, e);
           W.crank = crank;
           if (spin) W.spin = *spin;
+          if (W.exact && !ctx->plan.small &&
+              (st = overflow_search(ctx, dt, crank, nullptr, err)) != PCOL_OK)
+            return st;
           continue;
         }
         if ((st = take_plan(ctx)) != PCOL_OK) return st;
@@ -820,6 +841,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
       }
       if (!W.exact && ctx->rep->n_overflow) {  // nothing ran: again, with the exact search
         W.exact = ctx->exact_sweeps = 1;
+        if ((st = overflow_search(ctx, dt, crank, nullptr, err)) != PCOL_OK) return st;
         continue;
       }
       bool done = false;
@@ -1172,6 +1194,14 @@ static SweepArgs batch_sweep_args(const pcol_ctx *ctx, const Particles &P, doubl
   return W;
 }
 
+// Keys, by the exact search, of the spheres whose contacts overflowed their slots.
+static hipError_t batch_overflow_search(pcol_ctx *ctx, hipStream_t s, const BatchDev &B, int n,
+                                        double dt) {
+  return launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
+                             nullptr, dt, nullptr, ctx->key_j, ctx->key_t, &B,
+                             ctx->bp->flags + FLAG_ERR);
+}
+
 // Enqueue the whole batched step on stream s (captured into a graph).
 static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &P, int32_t *part,
                                  double *tc, double dt, double e, int kmax, int cpw) {
@@ -1220,10 +1250,8 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   PCOL_HIP(launch_detect_batched(s, A, B, bp->total_cells, cpw));
   PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec, ctx->key_j,
                            ctx->key_t, ctx->ovf, ctx->ctr_d, bp->flags + FLAG_ERR));
-  PCOL_HIP(launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
-                               nullptr, dt, nullptr, ctx->key_j, ctx->key_t, &B,
-                               bp->flags + FLAG_ERR));
   SweepArgs W = batch_sweep_args(ctx, P, dt, e);
+  if (W.exact) PCOL_HIP(batch_overflow_search(ctx, s, B, n, dt));
   PCOL_HIP(queue_sweeps(ctx, W, s, kmax, true));
   PCOL_HIP(launch_finish(s, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, nullptr,
                          nullptr, &B, ctx->ctr_d, kmax, W.exact != 0, bp->flags + FLAG_ERR,
@@ -1481,6 +1509,7 @@ extern "C" pcol_status pcol_step_batched(pcol_ctx *ctx, int32_t nbox, const int6
     bp->captured = false;
     SweepArgs W = batch_sweep_args(ctx, P, dt, e);
     const BatchDev B = batch_dev(bp);
+    PCOL_HIP(batch_overflow_search(ctx, ctx->stream, B, W.n, dt));
     PCOL_HIP(queue_sweeps(ctx, W, ctx->stream, bp->kmax, true));
     PCOL_HIP(launch_finish(ctx->stream, P, ctx->rank, ctx->out, ctx->status, part, tc, dt, nullptr,
                            nullptr, &B, ctx->ctr_d, bp->kmax, true, bp->flags + FLAG_ERR,
