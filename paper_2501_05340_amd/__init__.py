@@ -349,11 +349,15 @@ def pcol_step_batched(ctx: Context, p: Particles, box_off, Ls, dt: float, e: flo
     if nbox < 1 or len(Ls) != nbox:
         raise ValueError("box_off needs nbox + 1 entries and Ls nbox boxes")
     off_arr = (ctypes.c_int64 * (nbox + 1))(*off)
-    boxes = (pcol_box * nbox)()
-    for b, L in enumerate(Ls):
-        Lb = (L, L, L) if isinstance(L, (int, float)) else L
-        for a in range(3):
-            boxes[b].len[a] = float(Lb[a])
+    # the sides flat, one conversion for all boxes (one store per side took 0.6 ms for 512)
+    sides = []
+    for L in Ls:
+        if isinstance(L, (int, float)):
+            sides += (L, L, L)
+        else:
+            sides += (L[0], L[1], L[2])
+    flat = (ctypes.c_double * (3 * nbox))(*map(float, sides))
+    boxes = ctypes.cast(flat, ctypes.POINTER(pcol_box))
     st = pcol_batch_stats() if stats else None
     ctx.sync_stream()
     ps = p.struct()
