@@ -173,3 +173,27 @@ def test_restitution_gradient_sums_every_pair(n):
     pc.pcol_step_backward(pc.Context(n), p, L, dt, e, dev(partner), dev(t),
                           list(dev(np.concatenate([gx, gv]))), list(gin), ge)
     assert abs(ge.item() - 3.0 - float(want)) <= 128 * 2.0 ** -53 * (float(mag) + 3.0)
+
+
+def test_pair_recorded_on_one_side():
+    """A pair record whose other side says no collision: the recorded side gets the pair's gradient,
+    the other one free flight, and the recorded side's values equal those of the full record."""
+    rng = np.random.default_rng(3)
+    n = 4
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+    state = np.concatenate([rng.uniform(40, 60, (3, n)), rng.normal(size=(3, n))])
+    p = pc.Particles(*dev(state), dev(np.ones(n)), dev(np.ones(n)))
+    g = list(dev(rng.normal(size=(6, n))))
+    t = dev(np.full(n, 0.1))
+    ctx = pc.Context(n)
+
+    def run(partner):
+        gin, ge = torch.full((6, n), np.nan, dtype=torch.float64, device="cuda"), torch.zeros((), dtype=torch.float64, device="cuda")
+        pc.pcol_step_backward(ctx, p, (100.0,) * 3, 0.4, 0.8, dev(np.array(partner, dtype=np.int32)), t,
+                              g, list(gin), ge)
+        return gin.cpu().numpy()
+
+    full, none = run([2, 3, 0, 1]), run([-1, -1, -1, -1])
+    half = run([2, -1, -1, 1])
+    for i, want in ((0, full), (3, full), (1, none), (2, none)):
+        assert np.array_equal(half[:, i], want[:, i]), i
