@@ -72,6 +72,7 @@ struct pcol_ctx {
   // a step are sized by the last one, and if both gave one grid the reach pass of
   // a large step counts the spheres on it.
   bool shape_valid = false, steady = false;
+  bool split_seen = false;  // some plan of the shape split: the wide search is queued every time
   int64_t shape_n = -1;
   double shape_L[3] = {0, 0, 0}, shape_dt = 0.0;
   int shape_walls = 0;
@@ -480,6 +481,7 @@ static pcol_status take_plan(pcol_ctx *ctx) {
   ctx->steady = ctx->shape_valid && same_grid(ctx->plan, *ctx->plan_h);
   ctx->plan = *ctx->plan_h;
   ctx->shape_valid = true;
+  ctx->split_seen = ctx->split_seen || ctx->plan.split;
   ctx->binned = true;
   return PCOL_OK;
 }
@@ -512,7 +514,7 @@ static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_
   const bool shape = ctx->shape_valid && ctx->shape_n == p->n && ctx->shape_dt == dt &&
                      ctx->shape_walls == ctx->walls && ctx->shape_L[0] == box->len[0] &&
                      ctx->shape_L[1] == box->len[1] && ctx->shape_L[2] == box->len[2];
-  if (!shape) ctx->shape_valid = ctx->steady = false;
+  if (!shape) ctx->shape_valid = ctx->steady = ctx->split_seen = false;
   ahead = ahead && ctx->shape_valid && !ctx->plan.small && p->n > 0;
   ctx->shape_n = p->n;
   ctx->shape_dt = dt;
@@ -532,7 +534,7 @@ static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_
   A.fp32 = ctx->opts.filter == 1;
   A.walls = ctx->walls;
   A.allow_small = !ahead;
-  A.allow_split = !ahead || ctx->plan.split;
+  A.allow_split = !ahead || ctx->split_seen;
   A.tried_rho_c = INFINITY;
   // Counting in the reach pass saves reading the spheres once more (0.66 ms for both
   // at 16M spheres in random order, against 0.22 + 0.64 apart) but is thrown away
@@ -610,8 +612,8 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
   hipStream_t s = ctx->stream;
   const int n = (int)ctx->binned_n;
   // sized by the last plan that the host has seen: this binning's, or for a step
-  // that has not waited yet the one before it (which then had no small grid, and a
-  // split grid if this one has)
+  // that has not waited yet the one before it (which then had no small grid, and
+  // some plan of the shape a split one if this one has)
   const StepPlan &pl = ctx->plan;
   const unsigned int *err = status ? masked_err : &ctx->plan_d->err;
   const Grid *G = &ctx->plan_d->G;
@@ -633,7 +635,7 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     PCOL_HIP(launch_detect_half(s, A, ctx->opts.filter == 1,
                                 (pl.G.ncell + pl.cpw - 1) / (pl.cpw > 0 ? pl.cpw : 1)));
     // spheres of large extent: exact search of their wider neighbourhood
-    if (pl.split) PCOL_HIP(launch_detect_wide(s, A));
+    if (ctx->split_seen) PCOL_HIP(launch_detect_wide(s, A));
     if (ctx->opts.timing) PCOL_HIP(hipEventRecord(ctx->ev[6], s));
     ctx->detect_timed = true;
     PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
