@@ -1881,6 +1881,21 @@ __device__ __forceinline__ bool sweep_off(const SweepArgs &A) {
   return *A.err || (!EXACT && A.ctr->n_overflow != 0u);
 }
 
+// Entries of the list that a wave takes at a time: all its lanes one each, but
+// where they may have to search, the wave on one sphere after another, one or a
+// few (64 searches in a row took 0.4 ms a step in boxes of fewer than 3 cells on an
+// axis, where every new partner is a search).
+template <bool EXACT>
+__device__ __forceinline__ int wave_share(const SweepArgs &A) {
+  return !EXACT ? WAVE : (A.small ? 1 : 8);
+}
+
+// This lane's entry, count (none) past the end or its wave's share.
+__device__ __forceinline__ int list_entry(int t0, int share, int count) {
+  const int l = (int)threadIdx.x % WAVE, t = t0 + (int)threadIdx.x / WAVE * share + l;
+  return l < share && t < count ? t : count;
+}
+
 // The partners of the spheres that sweep 1 left DIRTY (in place: only DIRTY keys
 // change and no key is read).
 template <bool EXACT>
@@ -1889,8 +1904,9 @@ __global__ __launch_bounds__(256) void k_rekey(SweepArgs A, int *key) {
   const int sh = blockIdx.y, count = A.ctr->list[sh].n[0];
   const int *list = A.list[0] + (size_t)sh * A.shard_blocks * 256;
   const GoneCollided gone{A.status};
-  for (int t0 = blockIdx.x * 256; t0 < count; t0 += gridDim.x * 256) {
-    const int t = t0 + threadIdx.x;
+  const int share = wave_share<EXACT>(A), step = share * (256 / WAVE);
+  for (int t0 = blockIdx.x * step; t0 < count; t0 += gridDim.x * step) {
+    const int t = list_entry(t0, share, count);
     const int i = t < count ? list[t] : 0;
     const bool need = t < count && A.status[i] == ST_DIRTY;
     int bj;
@@ -1924,14 +1940,15 @@ __global__ __launch_bounds__(256) void k_sweep(SweepArgs A, const int *in, int *
   const int c1 = c == 2 ? 0 : c + 1, c2 = c1 == 2 ? 0 : c1 + 1;
   const int count = A.ctr->list[sh].n[c];
   if (blockIdx.x == 0 && threadIdx.x == 0) A.ctr->list[sh].n[c2] = 0;
-  if ((int)blockIdx.x * 256 >= count) return;
+  const int share = wave_share<EXACT>(A), step = share * (256 / WAVE);
+  if ((int)blockIdx.x * step >= count) return;
   const size_t at = (size_t)sh * A.shard_blocks * 256;
   const int *list = A.list[lin] + at;
   int *next = A.list[lin ^ 1] + at;
   const GoneInSweep gone{A.status, in};
   unsigned long long npair = 0ull;
-  for (int t0 = blockIdx.x * 256; t0 < count; t0 += gridDim.x * 256) {
-    const int t = t0 + threadIdx.x;
+  for (int t0 = blockIdx.x * step; t0 < count; t0 += gridDim.x * step) {
+    const int t = list_entry(t0, share, count);
     const int i = t < count ? list[t] : 0;
     bool need = false, keep = false;
     if (t < count && A.status[i] == ST_ACTIVE) {
@@ -1984,7 +2001,8 @@ hipError_t launch_sweep_first(hipStream_t s, const SweepArgs &A, const int *key)
 // Grid of a kernel over the list: one row of workgroups per shard, enough for
 // a quarter of the spheres at once (a tenth is usual; more take another turn).
 static dim3 list_grid(const SweepArgs &A) {
-  return dim3((A.shard_blocks + 3) / 4, A.shards);
+  const int per = A.exact ? (A.small ? WAVE : 8) : 1;  // workgroups for 256 entries
+  return dim3((unsigned)std::min((int64_t)8192, ((int64_t)A.shard_blocks * per + 3) / 4), A.shards);
 }
 
 hipError_t launch_rekey(hipStream_t s, const SweepArgs &A, int *key) {
