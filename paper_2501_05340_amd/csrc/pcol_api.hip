@@ -72,6 +72,7 @@ struct pcol_ctx {
   // a step are sized by the last one, and if both gave one grid the reach pass of
   // a large step counts the spheres on it.
   bool shape_valid = false, steady = false;
+  bool many_cells = false;  // some plan of the shape was not one for k_bin_small
   bool split_seen = false;  // some plan of the shape split: the wide search is queued every time
   int64_t shape_n = -1;
   double shape_L[3] = {0, 0, 0}, shape_dt = 0.0;
@@ -492,8 +493,9 @@ static pcol_status take_plan(pcol_ctx *ctx) {
 // have to be: the same shape and no small grid, whose kernels are others.
 // Otherwise (ahead then false) it waits for the plan, checks it and makes room for
 // its cells before it queues the rest.
+// few: let one workgroup bin the box if that can be done ahead (then still set).
 static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box, double dt,
-                             bool &ahead) {
+                             bool &ahead, bool &few) {
   ctx->binned = false;
   Particles P = to_dev(p);
   if (ctx->spin) {
@@ -514,7 +516,7 @@ static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_
   const bool shape = ctx->shape_valid && ctx->shape_n == p->n && ctx->shape_dt == dt &&
                      ctx->shape_walls == ctx->walls && ctx->shape_L[0] == box->len[0] &&
                      ctx->shape_L[1] == box->len[1] && ctx->shape_L[2] == box->len[2];
-  if (!shape) ctx->shape_valid = ctx->steady = ctx->split_seen = false;
+  if (!shape) ctx->shape_valid = ctx->steady = ctx->split_seen = ctx->many_cells = false;
   ahead = ahead && ctx->shape_valid && !ctx->plan.small && p->n > 0;
   ctx->shape_n = p->n;
   ctx->shape_dt = dt;
@@ -533,6 +535,7 @@ static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_
   A.home_cells = ctx->opts.home_cells;
   A.fp32 = ctx->opts.filter == 1;
   A.walls = ctx->walls;
+  A.curve = ctx->opts.order == 1;
   A.allow_small = !ahead;
   A.allow_split = !ahead || ctx->split_seen;
   A.tried_rho_c = INFINITY;
@@ -551,6 +554,13 @@ static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_
   // the extent histogram only picks the split extent: above 2^20 spheres it
   // samples one sphere in 16 (the quantile of a million samples is as good)
   const int hist_shift = p->n >= (1 << 20) ? 4 : 0;
+  few = few && ahead && !ctx->many_cells;
+  if (few) {  // counts in LDS: the context's stay clean
+    A.allow_split = 0;
+    PCOL_HIP(launch_bin_small(s, P, A, ctx->ctr_d, ctx->plan_d, ctx->plan_h, ctx->start, ctx->rec,
+                              ctx->rank, ctx->cnt, ctx->crank));
+    return PCOL_OK;
+  }
   ctx->counts_dirty = true;  // until the scan is queued behind a plan that stands
   if (tried)
     PCOL_HIP(launch_reach(s, P, dt, hist_shift, A, ctx->reach, ctx->ctr_d, ctx->scan, ctx->plan_d,
@@ -565,7 +575,7 @@ static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_
       const pcol_status st = grow_cells(ctx, ctx->plan_h->cells);
       if (st != PCOL_OK) return st;
       ctx->steady = false;
-      return bin_queue(ctx, p, box, dt, ahead);
+      return bin_queue(ctx, p, box, dt, ahead, few);
     }
     const pcol_status st = take_plan(ctx);
     if (st != PCOL_OK) return st;
@@ -587,8 +597,8 @@ static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_
 pcol_status pcol_bin(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box, double dt) {
   pcol_status st = check_common(ctx, p, box, dt);
   if (st != PCOL_OK) return st;
-  bool ahead = false;
-  return bin_queue(ctx, p, box, dt, ahead);
+  bool ahead = false, few = false;
+  return bin_queue(ctx, p, box, dt, ahead, few);
 }
 
 static pcol_status check_binned(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *box,
@@ -608,7 +618,8 @@ static pcol_status check_binned(pcol_ctx *ctx, const pcol_particles *p, const pc
 // spheres whose contacts overflowed their slots get no key (overflow_search).
 static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long *crank,
                               const uint8_t *status = nullptr,
-                              const unsigned int *masked_err = nullptr) {
+                              const unsigned int *masked_err = nullptr,
+                              bool contacts_only = false) {
   hipStream_t s = ctx->stream;
   const int n = (int)ctx->binned_n;
   // sized by the last plan that the host has seen: this binning's, or for a step
@@ -638,6 +649,7 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     if (ctx->split_seen) PCOL_HIP(launch_detect_wide(s, A));
     if (ctx->opts.timing) PCOL_HIP(hipEventRecord(ctx->ev[6], s));
     ctx->detect_timed = true;
+    if (contacts_only) return PCOL_OK;
     PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
                              ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err, G, crank, status));
   } else {
@@ -783,8 +795,10 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
   // The binning is queued ahead of its plan where that can be done.  If the plan
   // turns out not to fit, nothing has run, and the step is queued again behind a
   // wait.
-  bool ahead = true;
-  if ((st = bin_queue(ctx, p, box, dt, ahead)) != PCOL_OK) return st;
+  // Few spheres: one workgroup before the pair tests and, of fewer still, one after
+  // them, unless slots have overflowed.
+  bool ahead = true, few = p->n < SMALL_N;
+  if ((st = bin_queue(ctx, p, box, dt, ahead, few)) != PCOL_OK) return st;
   if (timing) PCOL_HIP(hipEventRecord(ctx->ev[1], s));
   const int n = (int)p->n;
   int32_t *part = partner ? partner : ctx->partner_tmp;
@@ -796,7 +810,9 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
   if (n > 0) {
     // sweep 1: every contact within dt, then the earliest partner of each sphere
     ctx->detect_timed = false;
-    if ((st = detect_all(ctx, dt, crank)) != PCOL_OK) return st;
+    // (the friction resolve needs the registers of a whole workgroup of 1024 twice)
+    bool one_tail = few && n <= SMALL_TAIL && !spin && !timing && !ctx->exact_sweeps;
+    if ((st = detect_all(ctx, dt, crank, nullptr, nullptr, one_tail)) != PCOL_OK) return st;
     if (timing) PCOL_HIP(hipEventRecord(ctx->ev[2], s));
     SweepArgs W = sweep_args(ctx, P, dt, e);
     W.crank = crank;
@@ -811,10 +827,39 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
     // the free flight if the last one resolved none.  Steps that need more are
     // continued below, one wait for each group.
     const int cap = ctx->opts.max_sweeps;
+    if (one_tail) {
+      PCOL_HIP(launch_sweeps_small(s, W, P, part, tc, cap, ctx->rep));
+      PCOL_HIP(hipStreamSynchronize(s));
+      ahead = false;
+      if (ctx->plan_h->err == PLAN_AGAIN) {  // too many cells, or a grid of another kind
+        ctx->many_cells = ctx->plan_h->cells > SMALL_CELLS;
+        few = one_tail = false;
+        if ((st = bin_queue(ctx, p, box, dt, ahead, few)) != PCOL_OK) return st;
+        if ((st = detect_all(ctx, dt, crank)) != PCOL_OK) return st;
+        W = sweep_args(ctx, P, dt, e);
+        W.crank = crank;
+        if (spin) W.spin = *spin;
+      } else {
+        if ((st = take_plan(ctx)) != PCOL_OK) return st;
+        if (ctx->rep->n_overflow) {  // nothing ran: sweeps that can search
+          one_tail = false;
+          W.exact = ctx->exact_sweeps = 1;
+          PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
+                                   ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err,
+                                   &ctx->plan_d->G, crank));
+          if ((st = overflow_search(ctx, dt, crank, nullptr, err)) != PCOL_OK) return st;
+        } else {
+          pairs = (int64_t)ctx->rep->small_pairs;
+          sweeps = ctx->rep->small_sweeps;
+          if (!ctx->rep->small_done)
+            return fail(ctx, PCOL_E_SWEEPS, "sweep cap reached with pairs still resolving");
+        }
+      }
+    }
     int group = ctx->sweep_guess + 1;
     if (group < 4) group = 4;
     bool first = true;
-    for (;;) {
+    while (!one_tail) {
       if (group > MAX_QUEUE - 1) group = MAX_QUEUE - 1;
       if (cap > 0 && group > cap - (int)sweeps) group = cap - (int)sweeps;
       if (!first) PCOL_HIP(hipMemsetAsync(ctx->ctr_d->pairs, 0, sizeof(ctx->ctr_d->pairs), s));
@@ -828,7 +873,9 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
       if (ahead) {
         ahead = false;
         if (ctx->plan_h->err == PLAN_AGAIN) {
-          if ((st = bin_queue(ctx, p, box, dt, ahead)) != PCOL_OK) return st;
+          ctx->many_cells = few && ctx->plan_h->cells > SMALL_CELLS;
+          few = false;
+          if ((st = bin_queue(ctx, p, box, dt, ahead, few)) != PCOL_OK) return st;
           if ((st = detect_all(ctx, dt, crank)) != PCOL_OK) return st;
           W = sweep_args(ctx, P, dt, e);
           W.crank = crank;
@@ -839,7 +886,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
           continue;
         }
         if ((st = take_plan(ctx)) != PCOL_OK) return st;
-        ctx->counts_dirty = false;
+        if (!few) ctx->counts_dirty = false;
       }
       if (!W.exact && ctx->rep->n_overflow) {  // nothing ran: again, with the exact search
         W.exact = ctx->exact_sweeps = 1;

@@ -141,7 +141,7 @@ enum : unsigned int {
 struct PlanArgs {
   int64_t n, cell_cap;
   double L[3], dt, cell_mult, band_rel, quantile;
-  int home_cells, fp32, walls;
+  int home_cells, fp32, walls, curve;
   int allow_split, allow_small;  // kernels for them are queued behind the plan
   // the grid that the reach pass has counted the spheres on (tried)
   int tried, tried_nc[3], tried_layer2;
@@ -328,7 +328,7 @@ __host__ __device__ inline void make_plan(const PlanArgs &A, const ReachPart &r,
   P.dt2f = (float)(2.0 * A.dt * (1.0 + 0x1.0p-12));
   // the literal order's curve grid: cell side >= the reach (whatever grid the pair
   // tests use), at most 2048 cells per axis
-  for (int a = 0; a < 3; ++a) {
+  for (int a = 0; a < 3 && A.curve; ++a) {
     double q = floor(A.L[a] / (reach * (1.0 + 1e-9)));
     if (!(q >= 1.0)) q = 1.0;
     if (q > 2048.0) q = 2048.0;
@@ -369,7 +369,9 @@ struct SweepCounters {
 struct StepReport {
   unsigned long long contacts, recheck, tests;
   unsigned int n_overflow, maxcell;
-  int wide_first, pad;  // sorted position of the first sphere above the split extent
+  int wide_first;  // sorted position of the first sphere above the split extent
+  int small_sweeps, small_done, pad;  // k_sweeps_small: sweeps run, and whether the last found none
+  unsigned long long small_pairs;     // and the pairs of them all
   unsigned long long pairs[MAX_QUEUE];
 };
 
@@ -589,6 +591,15 @@ struct Particles {
   const double *wx = nullptr, *wy = nullptr, *wz = nullptr;  // spins, validated when given
 };
 
+// Boxes that one workgroup bins (k_bin_small): fewer spheres than a plan needs to
+// split, and cells whose counts fit LDS.  And boxes that one workgroup sweeps
+// (k_sweeps_small): up to two spheres a thread; the queued kernels take the same
+// time up to 6,000 spheres, and both together a step of 93 us where this one
+// takes 78 at 2,000 spheres (phi 0.05), 94 at 3,000 and 111 at 4,000.
+constexpr int SMALL_N = 4096;
+constexpr int SMALL_CELLS = 8192;
+constexpr int SMALL_TAIL = 2048;
+
 // gradient with respect to a step's positions and velocities (SoA)
 struct StateGrad {
   double *x, *y, *z, *vx, *vy, *vz;
@@ -720,6 +731,13 @@ hipError_t launch_finish(hipStream_t s, const Particles &P, const int *rank, con
                          const StepPlan *plan, const int *start, const BatchDev *B,
                          const SweepCounters *ctr, int nsweep, bool exact, const unsigned int *err,
                          StepReport *rep);
+// P.n <= SMALL_N: the binning (reach, plan, sort, ranks), and everything after the
+// pair tests, by one workgroup each
+hipError_t launch_bin_small(hipStream_t s, const Particles &P, const PlanArgs &A,
+                            SweepCounters *ctr, StepPlan *plan, StepPlan *plan_host, int *start,
+                            Rec *rec, int *rank, int *cnt, unsigned long long *crank);
+hipError_t launch_sweeps_small(hipStream_t s, const SweepArgs &A, const Particles &P, int *partner,
+                               double *tcoll, int cap, StepReport *rep);
 hipError_t launch_fill_box_of(hipStream_t s, int nbox, const int64_t *box_off, int *box_of);
 // count given (zero on entry): the pass also takes every sphere's global cell
 // (box's first cell + local cell on its planned grid) and its slot in that cell

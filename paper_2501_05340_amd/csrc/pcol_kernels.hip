@@ -1335,13 +1335,9 @@ __device__ __forceinline__ unsigned long long morton3(unsigned int cx, unsigned 
 // (nc cells of side h per axis) above its caller index,
 // crank = code << 31 | o, in cell-sorted order.  A sphere's cell is
 // floor(x / h) in binary64, clamped to nc - 1.
-__global__ __launch_bounds__(256) void k_curve_rank(const Rec *rec, int n, const StepPlan *plan,
-                                                    unsigned long long *crank) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n || plan->err) return;
-  const CurveGrid &C = plan->C;
-  const Rec a = rec[i];
-  const double p[3] = {a.x, a.y, a.z};
+__device__ __forceinline__ unsigned long long curve_rank(const CurveGrid &C, double x, double y,
+                                                         double z, int o) {
+  const double p[3] = {x, y, z};
   unsigned int c[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -1350,7 +1346,15 @@ __global__ __launch_bounds__(256) void k_curve_rank(const Rec *rec, int n, const
     if (q > (double)(C.nc[k] - 1)) q = (double)(C.nc[k] - 1);
     c[k] = (unsigned int)q;
   }
-  crank[i] = morton3(c[0], c[1], c[2]) << 31 | (unsigned long long)(unsigned int)a.o;
+  return morton3(c[0], c[1], c[2]) << 31 | (unsigned long long)(unsigned int)o;
+}
+
+__global__ __launch_bounds__(256) void k_curve_rank(const Rec *rec, int n, const StepPlan *plan,
+                                                    unsigned long long *crank) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n || plan->err) return;
+  const Rec a = rec[i];
+  crank[i] = curve_rank(plan->C, a.x, a.y, a.z, a.o);
 }
 
 hipError_t launch_curve_rank(hipStream_t s, const Rec *rec, int n, const StepPlan *plan,
@@ -2116,6 +2120,264 @@ hipError_t launch_finish(hipStream_t s, const Particles &P, const int *rank, con
   hipLaunchKernelGGL(k_finish, dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, s, P, rank, out,
                      status, partner, tcoll, dt, plan, start, B ? *B : none, ctr, nsweep,
                      (int)exact, err, rep);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- few spheres
+
+// The kernels of a step of few spheres are a chain of launches of 2 to 7 us each,
+// most of it latency: 14 of them took 80 us at 2,000 spheres.  One workgroup does
+// what comes before the pair tests and, for fewer still, one what comes after,
+// with the cell counts, keys and statuses in LDS and a barrier where the chain had
+// a launch; the pair tests between them keep the whole chip.
+
+// Reach, checks, plan, counting sort (and the literal order's ranks) of
+// n <= SMALL_N spheres, as k_reach, k_plan, k_cell_hist, k_scan, k_scatter and
+// k_curve_rank do them.  No extent split (a plan of fewer than 4096 spheres has
+// none).  A grid of more than SMALL_CELLS cells is for the other kernels
+// (PLAN_AGAIN).
+__global__ __launch_bounds__(1024) void k_bin_small(Particles P, PlanArgs A, SweepCounters *ctr,
+                                                    StepPlan *plan, StepPlan *plan_host,
+                                                    int *start, Rec *rec, int *rank, int *cnt,
+                                                    unsigned long long *crank) {
+  const int t = threadIdx.x, n = (int)P.n;
+  constexpr int PER = SMALL_N / 1024;
+  __shared__ int count[SMALL_CELLS + 1];
+  __shared__ StepPlan S;
+  unsigned long long *w = (unsigned long long *)ctr;
+  for (int k = t; k < (int)(sizeof(SweepCounters) / 8); k += 1024) w[k] = 0ull;
+  double v2 = 0.0, rm = 0.0, rn = INFINITY, em = 0.0;
+  unsigned int bad = 0u;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = t + k * 1024;
+    if (i >= n) continue;
+    const double x = P.x[i], y = P.y[i], z = P.z[i], vx = P.vx[i], vy = P.vy[i], vz = P.vz[i];
+    const double r = P.r[i], m = P.m[i];
+    const double q = (vx * vx + vy * vy) + vz * vz;
+    const bool fin = isfinite(x) && isfinite(y) && isfinite(z) && isfinite(q) && isfinite(r) &&
+                     isfinite(m);
+    if (!fin || !(r > 0.0) || !(m > 0.0)) bad |= 1u;
+    if (P.wx && (!isfinite(P.wx[i]) || !isfinite(P.wy[i]) || !isfinite(P.wz[i]))) bad |= 1u;
+    if (!(x >= 0.0 && x < A.L[0]) || !(y >= 0.0 && y < A.L[1]) || !(z >= 0.0 && z < A.L[2]))
+      bad |= 2u;
+    if (fin) {
+      v2 = q > v2 ? q : v2;
+      rm = r > rm ? r : rm;
+      rn = r < rn ? r : rn;
+      if (r > 0.0) {
+        const double ex = extent(r, vx, vy, vz, A.dt);
+        em = ex > em ? ex : em;
+      }
+    }
+  }
+  ReachPart part{dbits(v2), dbits(rm), dbits(rn), dbits(em), bad, 0u};
+  __shared__ ReachPart wpart[1024 / WAVE];
+  for (int o = WAVE / 2; o > 0; o >>= 1) {
+    ReachPart q;
+    q.v2max = __shfl_xor(part.v2max, o);
+    q.rmax = __shfl_xor(part.rmax, o);
+    q.rmin = __shfl_xor(part.rmin, o);
+    q.rhomax = __shfl_xor(part.rhomax, o);
+    q.bad = __shfl_xor(part.bad, o);
+    part = reach_merge(part, q);
+  }
+  if (__lane_id() == 0) wpart[t / WAVE] = part;
+  __syncthreads();
+  if (t == 0) {
+    for (int k = 1; k < 1024 / WAVE; ++k) part = reach_merge(part, wpart[k]);
+    make_plan(A, part, -1, S);
+    if (!S.err && S.cells > SMALL_CELLS) S.err = PLAN_AGAIN;
+  }
+  for (int k = t; k <= SMALL_CELLS; k += 1024) count[k] = 0;
+  __syncthreads();
+  const unsigned long long *o = (const unsigned long long *)&S;
+  for (int k = t; k < (int)(sizeof(StepPlan) / 8); k += 1024) {
+    ((unsigned long long *)plan)[k] = o[k];
+    ((unsigned long long *)plan_host)[k] = o[k];
+  }
+  if (S.err) return;
+  const Grid &G = S.G;
+  int cell[PER], slot[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = t + k * 1024;
+    if (i >= n) continue;
+    const int cx = cell_coord(P.x[i], G.inv_h[0], G.nc[0]);
+    const int cy = cell_coord(P.y[i], G.inv_h[1], G.nc[1]);
+    const int cz = cell_coord(P.z[i], G.inv_h[2], G.nc[2]);
+    cell[k] = (cz * G.nc[1] + cy) * G.nc[0] + cx;
+    slot[k] = atomicAdd(&count[cell[k]], 1);
+  }
+  __syncthreads();
+  constexpr int CPT = SMALL_CELLS / 1024;
+  int c[CPT], sum = 0, mx = 0;
+#pragma unroll
+  for (int k = 0; k < CPT; ++k) {
+    c[k] = count[t * CPT + k];
+    sum += c[k];
+    mx = c[k] > mx ? c[k] : mx;
+  }
+  int run;
+  block_exclusive_scan(sum, run);
+#pragma unroll
+  for (int k = 0; k < CPT; ++k) {
+    count[t * CPT + k] = run;
+    run += c[k];
+  }
+  if (t == 1023) count[SMALL_CELLS] = run;
+  for (int q = WAVE / 2; q > 0; q >>= 1) {
+    const int m = __shfl_xor(mx, q);
+    mx = m > mx ? m : mx;
+  }
+  if (__lane_id() == 0) atomicMax(&ctr->maxcell, (unsigned int)mx);
+  __syncthreads();
+  for (int k = t; k <= S.cells; k += 1024) start[k] = count[k];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = t + k * 1024;
+    if (i >= n) continue;
+    const int pos = count[cell[k]] + slot[k];
+    const Rec q{P.x[i], P.y[i], P.z[i], P.r[i], P.vx[i], P.vy[i], P.vz[i], i, 0};
+    rec[pos] = q;
+    rank[i] = pos;
+    cnt[i] = 0;
+    if (crank) crank[pos] = curve_rank(S.C, q.x, q.y, q.z, i);
+  }
+}
+
+hipError_t launch_bin_small(hipStream_t s, const Particles &P, const PlanArgs &A,
+                            SweepCounters *ctr, StepPlan *plan, StepPlan *plan_host, int *start,
+                            Rec *rec, int *rank, int *cnt, unsigned long long *crank) {
+  if (P.n < 1 || P.n > SMALL_N) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(1024), 0, s, P, A, ctr, plan, plan_host, start, rec,
+                     rank, cnt, crank);
+  return hipGetLastError();
+}
+
+// Partners, every sweep, free flight and the report of n <= SMALL_TAIL spheres, as
+// k_slot_min, k_sweep_first, k_rekey, k_sweep and k_finish do them (keys in two
+// arrays in turn; status and keys in LDS).  cap > 0: the most sweeps; if the last
+// still resolved pairs, nothing of the caller's is written.  Contacts
+// that overflow their slots are for the other kernels: only the report is written.
+__global__ __launch_bounds__(1024) void k_sweeps_small(SweepArgs A, Particles P, int *partner,
+                                                       double *tcoll, int cap, StepReport *rep) {
+  if (*A.err) return;
+  const int t = threadIdx.x, n = A.n;
+  __shared__ int key[2][SMALL_TAIL];
+  __shared__ uint8_t status[SMALL_TAIL];
+  __shared__ unsigned long long total[3];  // contacts; pairs of the sweep, in two words in turn
+  __shared__ int overflow;
+  if (t < 3) total[t] = 0ull;
+  if (t == 3) overflow = 0;
+  __syncthreads();
+  const Grid G = *A.G;
+  unsigned long long nc = 0ull;
+  for (int i = t; i < n; i += 1024) {
+    const int c = A.cnt[i];
+    nc += (unsigned long long)c;
+    if (c > A.K) atomicAdd(&overflow, 1);
+    int bj;
+    double bt;
+    slot_choice(i, c > A.K ? 0 : c, (size_t)n, A.slot_t, A.slot_j, A.rec, G, A.crank, GoneNone{},
+                bj, bt);
+    key[0][i] = bj;
+    A.key_t[i] = bt;
+    status[i] = bj < 0 ? ST_FREE : ST_ACTIVE;
+  }
+  nc = wave_sum(nc);
+  if (__lane_id() == 0 && nc) atomicAdd(&total[0], nc);
+  __syncthreads();
+  A.status = status;
+  unsigned long long pairs = 0ull;
+  int sweeps = 0;
+  bool done = false;
+  while (!overflow && !done && (cap == 0 || sweeps < cap)) {
+    const int *in = key[sweeps & 1];
+    int *out = key[~sweeps & 1];
+    unsigned long long *now = &total[1 + (sweeps & 1)];
+    const GoneInSweep gone{status, in};
+    unsigned long long np = 0ull;
+    for (int i = t; i < n; i += 1024) {
+      if (status[i] != ST_ACTIVE) continue;
+      const int p = in[i];
+      if (p < 0) {
+        status[i] = ST_FREE;
+        continue;
+      }
+      const int q = in[p];
+      if (q == i) {
+        np += resolve_pair<false>(A, i, p);
+        continue;
+      }
+      int bj = p;
+      if (q >= 0 && in[q] == p) {
+        double bt;
+        slot_choice(i, A.cnt[i], (size_t)n, A.slot_t, A.slot_j, A.rec, G, A.crank, gone, bj, bt);
+        A.key_t[i] = bt;
+      }
+      out[i] = bj;
+    }
+    np = wave_sum(np);
+    if (__lane_id() == 0 && np) atomicAdd(now, np);
+    __syncthreads();
+    const unsigned long long got = *now;
+    if (t == 0) total[1 + (~sweeps & 1)] = 0ull;
+    pairs += got;
+    done = got == 0ull;
+    ++sweeps;
+    __syncthreads();
+  }
+  if (t == 0) {
+    rep->contacts = total[0];
+    rep->recheck = 0ull;
+    rep->tests = 0ull;
+    rep->n_overflow = (unsigned int)overflow;
+    rep->maxcell = A.ctr->maxcell;
+    rep->wide_first = n;
+    rep->small_pairs = pairs;
+    rep->small_sweeps = sweeps;
+    rep->small_done = done;
+  }
+  if (t < NSHARD) {
+    const unsigned long long r = wave_sum(A.ctr->shard[t].recheck),
+                             e = wave_sum(A.ctr->shard[t].tests);
+    if (t == 0) {
+      rep->recheck = r;
+      rep->tests = e;
+    }
+  }
+  if (!done) return;
+  for (int i = t; i < n; i += 1024) {
+    const Rec a = A.rec[i];
+    OutRec r;
+    if (status[i] == ST_COLLIDED) {
+      r = A.out[i];
+    } else {
+      r.vx = a.vx;
+      r.vy = a.vy;
+      r.vz = a.vz;
+      r.x = fly_axis(a.x + A.dt * a.vx, G.L[0], G.walls & 1, r.vx);
+      r.y = fly_axis(a.y + A.dt * a.vy, G.L[1], G.walls & 2, r.vy);
+      r.z = fly_axis(a.z + A.dt * a.vz, G.L[2], G.walls & 4, r.vz);
+      r.t = __longlong_as_double(0x7ff8000000000000LL);  // NaN: no collision
+      r.partner = -1;
+    }
+    P.x[a.o] = r.x;
+    P.y[a.o] = r.y;
+    P.z[a.o] = r.z;
+    P.vx[a.o] = r.vx;
+    P.vy[a.o] = r.vy;
+    P.vz[a.o] = r.vz;
+    partner[a.o] = r.partner;
+    tcoll[a.o] = r.t;
+  }
+}
+
+hipError_t launch_sweeps_small(hipStream_t s, const SweepArgs &A, const Particles &P, int *partner,
+                               double *tcoll, int cap, StepReport *rep) {
+  if (A.n < 1 || A.n > SMALL_TAIL || A.spin.wx) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_sweeps_small, dim3(1), dim3(1024), 0, s, A, P, partner, tcoll, cap, rep);
   return hipGetLastError();
 }
 
