@@ -735,30 +735,38 @@ __device__ __forceinline__ void detect_chunk32(const DetectArgs &A, const Grid &
   }
 }
 
-// Pair tests of one home cell (see k_detect_half).  `start` points at the first
-// cell of the box whose grid is G (cell numbers below are local to that box;
-// sphere positions in start[] are global).
 // Runs of consecutive cell-sorted records that make the half stencil of one
 // home cell: run 0 the own cell (pairs with j after i), run 1 the next cell
 // along x, runs 2..9 the 4 rows of 3 cells, each row as two runs (the second
 // empty unless the row wraps along x); each with its periodic image code.
-// Run k's bounds are the starts of two cells, held in lanes 2k and 2k + 1 of
-// the wave, so that one vector load fetches all 20 and the runs are formed
-// lane by lane rather than in scalar code.
+// A wave forms the runs of GROUP home cells at once, one run to a lane and one
+// cell to each 16 lanes: of some 160 vector instructions a cell, 125 went into
+// its runs when a cell had the wave to itself.
+constexpr int GROUP = 4;
 
-// Lane j < 20 of a home cell's stencil: the cell whose start it loads (lane
-// 2k the first cell of run k, lane 2k + 1 the cell one past its last) and run
-// k's image code (run_code).  Lanes from 20 on load nothing.
-__device__ __forceinline__ int cell_starts(const Grid &G, const int *start, int cell, int &code) {
+// The runs of a group, lane 16 q + k holding run k of cell q: its first sorted
+// position and length, and its first slot in the cell's candidate list (an empty
+// run starts where the next does).
+struct GroupRuns {
+  int first, len, slot;
+};
+
+// The runs of cells cell0 .. cell0 + ncells - 1 (ncells <= GROUP) of the box whose
+// grid is G (`start` points at its first cell; positions in start[] are global):
+// the lanes' own R, and in LDS the run tables rt (MAXRUN entries a cell): each
+// run's offset from list slot to sorted index, its code and its image shift.
+__device__ __forceinline__ void group_runs(const Grid &G, const int *start, int cell0, int ncells,
+                                           RunT *rt, GroupRuns &R) {
   const int nc0 = G.nc[0], nc1 = G.nc[1], nc2 = G.nc[2];
-  int cx, cy, cz;
-  cell_xyz(G, cell, cx, cy, cz);
-  // the lane index made opaque per call, so that the lane-constant selections
-  // below are recomputed per cell rather than hoisted out of a cell loop
-  // (held across it they cost registers and, in the grouped kernel, spills)
+  // the lane index opaque, so that what follows from it is formed here per group
+  // and not held across the cells (registers)
   int ln = (int)__lane_id();
   asm volatile("" : "+v"(ln));
-  const int k = ln >> 1, end = ln & 1;
+  const int q = ln >> 4, k = ln & 15;
+  const bool mine = q < ncells && k < MAXRUN;
+  const int cell = cell0 + (q < ncells ? q : 0);
+  int cx, cy, cz;
+  cell_xyz(G, cell, cx, cy, cz);
   const bool lw = cx - 1 < 0, rw = cx + 1 >= nc0;  // the row wraps left / right
   // rows (runs 2..9): offsets (dy, dz) = (1, 0), (-1, 1), (0, 1), (1, 1)
   const int row = (k - 2) >> 1, second = (k - 2) & 1;
@@ -768,70 +776,58 @@ __device__ __forceinline__ int cell_starts(const Grid &G, const int *start, int 
   z -= sz * nc2;
   // a row's two runs, as cells [a0, a1) and [a2, a3) of the row: the wrapped
   // left cell then cells 0..1; cells cx-1..cx then the wrapped right cell 0;
-  // or cells cx-1..cx+1 and an empty second run.  The four bounds are uniform
-  // and each lane selects one (simple selects, no divergent branches).
+  // or cells cx-1..cx+1 and an empty second run
   const int a0 = lw ? nc0 - 1 : cx - 1, a1 = lw ? nc0 : (rw ? cx + 1 : cx + 2);
   const int a2 = lw || rw ? 0 : cx + 2, a3 = lw ? 2 : (rw ? 1 : cx + 2);
-  const int o01 = end ? a1 : a0, o23 = end ? a3 : a2;
-  const int o = second ? o23 : o01;
   // image along x of a row's first / second run
   const int sx0 = lw ? -1 : 0, sx1 = !lw && rw ? 1 : 0;
-  const int sx_row = second ? sx1 : sx0;
   // run 1: the next cell along x, cell 0 of the own row where x wraps
   const int c01 = k == 0 ? cell : (rw ? cell - cx : cell + 1);
-  const int idx = k < 2 ? c01 + end : (z * nc1 + y) * nc0 + o;
+  const int base = (z * nc1 + y) * nc0;
+  const int i0 = k < 2 ? c01 : base + (second ? a2 : a0);
+  const int i1 = k < 2 ? c01 + 1 : base + (second ? a3 : a1);
   const int code01 = k == 0 ? run_code(0, 0, 0, 1) : run_code(rw ? 1 : 0, 0, 0, 0);
-  code = k < 2 ? code01 : run_code(sx_row, sy, sz, 0);
-  int v = 0;
-  if (ln < 20) v = start[idx];
-  return v;
+  const int code = k < 2 ? code01 : run_code(second ? sx1 : sx0, sy, sz, 0);
+  R.first = R.len = 0;
+  if (mine) {
+    R.first = start[i0];
+    R.len = start[i1] - R.first;
+  }
+  // running lengths within 16 lanes (row_shr:1, 2, 4, 8)
+  int inc = R.len;
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, true);
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, true);
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, true);
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, true);
+  R.slot = inc - R.len;
+  if (mine)  // one wave owns rt: its LDS operations stay in order
+    rt[q * MAXRUN + k] = RunT{R.first - R.slot, code, code_shift(code & 3, G.sL[0]),
+                              code_shift((code >> 2) & 3, G.sL[1]),
+                              code_shift((code >> 4) & 3, G.sL[2])};
 }
 
 // A home cell's runs as the candidate search needs them: its spheres [h0, h1),
-// the candidate list length, and the first list slot of each run (pre[0] = 0;
-// an empty run starts where the next does).
+// the candidate list length, the first list slot of each run (pre[0] = 0) and the
+// run table.
 struct CellSet {
   int h0, h1, total;
   int pre[MAXRUN];
+  const RunT *rt;
 };
 
-// The runs of a home cell from its lanes' starts v and codes (cell_starts):
-// run lengths and their prefix sums formed across lanes 0..19 (DPP shifts
-// within rows of 16 lanes, then the carry of the first row), and the run table
-// rt (the wave's own room in LDS; its LDS operations stay in order) written by
-// lanes 2k: run k's offset from list slot to sorted index, its code and its
-// image shift on the grid G.  Returns false for an empty home cell.
-__device__ __forceinline__ bool cell_setup(const Grid &G, int v, int code, RunT *rt, CellSet &S) {
-  const int h0 = __builtin_amdgcn_readlane(v, 0), h1 = __builtin_amdgcn_readlane(v, 1);
-  S.h0 = h0;
-  S.h1 = h1;
-  if (h1 <= h0) return false;
-  // the lane index opaque, so that the table addresses are formed here per
-  // cell and not held across the cell loop (registers)
-  int ln = (int)__lane_id();
-  asm volatile("" : "+v"(ln));
-  const bool first = ln < 20 && (ln & 1) == 0;
-  // lane 2k + 1's start beside lane 2k's (row_shl:1; a pair never straddles a row)
-  const int vn = __builtin_amdgcn_update_dpp(0, v, 0x101, 0xf, 0xf, true);
-  const int rl = first ? vn - v : 0;
-  int inc = rl;
-  inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, true);  // row_shr:1
-  inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, true);  // row_shr:2
-  inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, true);  // row_shr:4
-  inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, true);  // row_shr:8
-  const int carry = __builtin_amdgcn_readlane(inc, 15);
-  if (ln >= 16) inc += carry;
-  const int excl = inc - rl;
-  if (first)
-    rt[ln >> 1] = RunT{v - excl, code, code_shift(code & 3, G.sL[0]),
-                       code_shift((code >> 2) & 3, G.sL[1]), code_shift((code >> 4) & 3, G.sL[2])};
-  S.total = __builtin_amdgcn_readlane(inc, 19);
+// Cell q of a group; false if it is empty.
+__device__ __forceinline__ bool group_cell(const GroupRuns &R, int q, const RunT *rt, CellSet &S) {
+  const int l = 16 * q;
+  S.h0 = __builtin_amdgcn_readlane(R.first, l);
+  S.h1 = S.h0 + __builtin_amdgcn_readlane(R.len, l);
+  if (S.h1 <= S.h0) return false;
   S.pre[0] = 0;
 #pragma unroll
-  for (int k = 1; k < MAXRUN; ++k) S.pre[k] = __builtin_amdgcn_readlane(excl, 2 * k);
+  for (int k = 1; k < MAXRUN; ++k) S.pre[k] = __builtin_amdgcn_readlane(R.slot, l + k);
+  S.total = __builtin_amdgcn_readlane(R.slot, l + MAXRUN);  // (no run there: the end of the last)
+  S.rt = rt + q * MAXRUN;
   return true;
 }
-
 
 // Home spheres of the binary32 filter staged in LDS per batch.
 constexpr int HB32 = WAVE;
@@ -839,14 +835,9 @@ constexpr int HB32 = WAVE;
 // Pair tests of one home cell with the binary32 filter.  The home spheres are
 // staged in LDS (hl) HB32 at a time as binary32 records relative to the home
 // cell centre, converted from the binary64 records; candidates in chunks of 64
-// lanes, converted likewise with their run's image shift.  rt: the wave's room
-// in LDS for the cell's run table (MAXRUN entries).
-__device__ __forceinline__ void detect_cell32(const DetectArgs &A, const Grid &G, const int *start,
-                                              int cell, SurvivorQueue &Q, Rec32 *hl, RunT *rt) {
-  int code;
-  const int vs = cell_starts(G, start, cell, code);
-  CellSet S;
-  if (!cell_setup(G, vs, code, rt, S)) return;
+// lanes, converted likewise with their run's image shift.
+__device__ __forceinline__ void detect_cell32(const DetectArgs &A, const Grid &G, int cell,
+                                              const CellSet &S, SurvivorQueue &Q, Rec32 *hl) {
   const int h0 = S.h0, h1 = S.h1, total = S.total;
   const int *pre = S.pre;
   const int lane = __lane_id();
@@ -874,11 +865,11 @@ __device__ __forceinline__ void detect_cell32(const DetectArgs &A, const Grid &G
     __syncthreads();  // the workgroup is this one wave
     for (int base = 0; base < total; base += WAVE) {
       const int v = base + lane;
-      int r = 0;  // the run of list slot v (see detect_cell64)
+      int r = 0;  // the run of list slot v (see detect_chunks)
 #pragma unroll
       for (int k = 1; k < MAXRUN; ++k) r += v >= pre[k] ? 1 : 0;
       asm volatile("" : "+v"(r));  // the count apart from the table address
-      const RunT run = rt[r];
+      const RunT run = S.rt[r];
       const int g = run.off + v;
       const bool ok = v < total;
       const bool own = (run.code >> 6) & 1;
@@ -917,11 +908,10 @@ __device__ __forceinline__ void detect_cell32(const DetectArgs &A, const Grid &G
 typedef double d8 __attribute__((ext_vector_type(8)));
 typedef const d8 __attribute__((address_space(4))) *ScalarRec;
 
-__device__ __forceinline__ double gram_beta(double x, double y, double z, double vx, double vy,
-                                            double vz, double r, double dt2) {
-  const double xx = __builtin_fma(z, z, __builtin_fma(y, y, x * x));
-  const double xv = __builtin_fma(z, vz, __builtin_fma(y, vy, x * vx));
-  return __builtin_fma(-r, r, __builtin_fma(dt2, xv, xx));
+// beta of a sphere at x with w = x + dt2 v
+__device__ __forceinline__ double gram_beta(double x, double y, double z, double wx, double wy,
+                                            double wz, double r) {
+  return __builtin_fma(-r, r, __builtin_fma(z, wz, __builtin_fma(y, wy, x * wx)));
 }
 
 // Queue the survivors of home i (the lanes of m) against the lane's candidate
@@ -950,7 +940,7 @@ __device__ __forceinline__ void push_home(unsigned long long m, int i, int g, in
 template <int NC>
 __device__ __forceinline__ int detect_chunks(const DetectArgs &A, const CellSet &S, int base,
                                              int i0, int k, int nb, const double *hbeta,
-                                             const RunT *rt, SurvivorQueue &Q) {
+                                             SurvivorQueue &Q) {
   const int *pre = S.pre;
   const double dt2 = A.dt2;
   double q[NC][7], thr[NC];
@@ -966,21 +956,24 @@ __device__ __forceinline__ int detect_chunks(const DetectArgs &A, const CellSet 
 #pragma unroll
     for (int k = 1; k < MAXRUN; ++k) r += v >= pre[k] ? 1 : 0;
     asm volatile("" : "+v"(r));  // the count apart from the table address
-    const RunT run = rt[r];
+    const RunT run = S.rt[r];
     const bool ok = v < S.total;
     // past the end of the list: some record, and a threshold nothing meets
     g[c] = ok ? run.off + v : i0;
     last[c] = ((run.code >> 6) & 1) ? g[c] : 0x7fffffff;
     const Rec b = A.rec[g[c]];
     const double x = b.x + run.sx, y = b.y + run.sy, z = b.z + run.sz;
-    q[c][0] = __builtin_fma(-2.0, x, -dt2 * b.vx);
-    q[c][1] = __builtin_fma(-2.0, y, -dt2 * b.vy);
-    q[c][2] = __builtin_fma(-2.0, z, -dt2 * b.vz);
+    // w = x + dt2 v: Q = -(x + w), and beta = x . w - r^2
+    const double wx = __builtin_fma(dt2, b.vx, x), wy = __builtin_fma(dt2, b.vy, y),
+                 wz = __builtin_fma(dt2, b.vz, z);
+    q[c][0] = -(x + wx);
+    q[c][1] = -(y + wy);
+    q[c][2] = -(z + wz);
     q[c][3] = -2.0 * b.r;
     q[c][4] = -dt2 * x;
     q[c][5] = -dt2 * y;
     q[c][6] = -dt2 * z;
-    const double th = A.tol64 - gram_beta(x, y, z, b.vx, b.vy, b.vz, b.r, dt2);
+    const double th = A.tol64 - gram_beta(x, y, z, wx, wy, wz, b.r);
     thr[c] = ok ? th : -INFINITY;
   }
   const auto test = [&](d8 p, double beta, int c) {
@@ -1031,14 +1024,8 @@ __device__ __forceinline__ int detect_chunks(const DetectArgs &A, const CellSet 
 // Pair tests of one home cell with the binary64 Gram filter; homes in batches
 // of 64 (hbeta holds one batch's beta), candidates in chunks of 64 lanes, three
 // chunks a pass (a cell of 13 has about 180 candidates).
-// vs, code: the cell's 20 starts and run codes (cell_starts), loaded ahead by
-// the caller; rt: the wave's room in LDS for the cell's run table (MAXRUN
-// entries).
-__device__ __forceinline__ void detect_cell64(const DetectArgs &A, const Grid &G, int vs,
-                                              int code, SurvivorQueue &Q, double *hbeta,
-                                              RunT *rt) {
-  CellSet S;
-  if (!cell_setup(G, vs, code, rt, S)) return;
+__device__ __forceinline__ void detect_cell64(const DetectArgs &A, const Grid &G, const CellSet &S,
+                                              SurvivorQueue &Q, double *hbeta) {
   const int h0 = S.h0, nh = S.h1 - S.h0;
   Q.tests += (unsigned long long)nh * (unsigned long long)(S.total - nh) +
              (unsigned long long)nh * (unsigned long long)(nh - 1) / 2ull;
@@ -1047,17 +1034,19 @@ __device__ __forceinline__ void detect_cell64(const DetectArgs &A, const Grid &G
     const int i0 = h0 + hb;
     if ((int)__lane_id() < nb) {  // one wave owns hbeta: its LDS operations stay in order
       const Rec a = A.rec[i0 + (int)__lane_id()];
-      hbeta[__lane_id()] = gram_beta(a.x, a.y, a.z, a.vx, a.vy, a.vz, a.r, A.dt2);
+      hbeta[__lane_id()] =
+          gram_beta(a.x, a.y, a.z, __builtin_fma(A.dt2, a.vx, a.x), __builtin_fma(A.dt2, a.vy, a.y),
+                    __builtin_fma(A.dt2, a.vz, a.z), a.r);
     }
     for (int base = 0, k = 0; base < S.total;) {
       const int left = S.total - base;
       int step = 3 * WAVE;
       if (left > 2 * WAVE) {
-        k = detect_chunks<3>(A, S, base, i0, k, nb, hbeta, rt, Q);
+        k = detect_chunks<3>(A, S, base, i0, k, nb, hbeta, Q);
       } else if (left > WAVE) {
-        k = detect_chunks<2>(A, S, base, i0, k, nb, hbeta, rt, Q);
+        k = detect_chunks<2>(A, S, base, i0, k, nb, hbeta, Q);
       } else {
-        k = detect_chunks<1>(A, S, base, i0, k, nb, hbeta, rt, Q);
+        k = detect_chunks<1>(A, S, base, i0, k, nb, hbeta, Q);
       }
       if (k < nb) {  // the queue is full (rare): decide it, then the rest of these homes
         flush_survivors(A, G, Q);
@@ -1093,41 +1082,47 @@ __device__ __forceinline__ void detect_groups(const DetectArgs &A, int ncell, in
   }
 }
 
-__global__ __launch_bounds__(WAVE) void k_detect_half32(DetectArgs A) {
+__global__ __launch_bounds__(WAVE, 6) void k_detect_half32(DetectArgs A) {
   if (*A.err) return;
   __shared__ int2 survq[QCAP];
   __shared__ Rec32 hl[HB32];
-  __shared__ RunT rt[MAXRUN];
+  __shared__ RunT rt[GROUP * MAXRUN];
   SurvivorQueue Q{survq, 0, 0u, QCAP, 0ull};
   const Grid G = A.plan->G;
   A.kband = A.plan->kband;
   A.dt2f = A.plan->dt2f;
   detect_groups(A, G.ncell, A.plan->cpw, Q, [&](int c0, int c1) {
-    for (int cell = c0; cell < c1; ++cell) {
-      detect_cell32(A, G, A.start, cell, Q, hl, rt);
-      if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
+    for (int b = c0; b < c1; b += GROUP) {
+      const int nc = c1 - b < GROUP ? c1 - b : GROUP;
+      GroupRuns R;
+      group_runs(G, A.start, b, nc, rt, R);
+      for (int q = 0; q < nc; ++q) {
+        CellSet S;
+        if (group_cell(R, q, rt, S)) detect_cell32(A, G, b + q, S, Q, hl);
+        if (b + q + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
+      }
     }
   });
 }
 
-__global__ __launch_bounds__(WAVE, 5) void k_detect_half64(DetectArgs A) {
+__global__ __launch_bounds__(WAVE, 6) void k_detect_half64(DetectArgs A) {
   if (*A.err) return;
   __shared__ int2 survq[QCAP64];
   __shared__ double hbeta[WAVE];
-  __shared__ RunT rt[MAXRUN];
+  __shared__ RunT rt[GROUP * MAXRUN];
   SurvivorQueue Q{survq, 0, 0u, QCAP64, 0ull};
   const Grid G = A.plan->G;
   A.tol64 = A.plan->tol64;
   detect_groups(A, G.ncell, A.plan->cpw, Q, [&](int c0, int c1) {
-    // the next cell's starts are loaded while this cell is tested
-    int code = 0;
-    int v = cell_starts(G, A.start, c0, code);
-    for (int cell = c0; cell < c1; ++cell) {
-      const int vc = v;
-      const int cc = code;
-      if (cell + 1 < c1) v = cell_starts(G, A.start, cell + 1, code);
-      detect_cell64(A, G, vc, cc, Q, hbeta, rt);
-      if (cell + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
+    for (int b = c0; b < c1; b += GROUP) {
+      const int nc = c1 - b < GROUP ? c1 - b : GROUP;
+      GroupRuns R;
+      group_runs(G, A.start, b, nc, rt, R);
+      for (int q = 0; q < nc; ++q) {
+        CellSet S;
+        if (group_cell(R, q, rt, S)) detect_cell64(A, G, S, Q, hbeta);
+        if (b + q + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
+      }
     }
   });
 }
@@ -1152,11 +1147,11 @@ __device__ __forceinline__ int box_of_cell(const int *cell_base, int nbox, int c
 // queue carries over the cells, decided with the grid of the box its survivors
 // came from whenever the next cell lies in another box, when it holds a wave's
 // worth, and at the end.
-__global__ __launch_bounds__(WAVE) void k_detect_batched(DetectArgs A, BatchDev B, int cpw) {
+__global__ __launch_bounds__(WAVE, 5) void k_detect_batched(DetectArgs A, BatchDev B, int cpw) {
   if (B.flags[FLAG_ERR]) return;
   __shared__ int2 survq[QCAP64];
   __shared__ double hbeta[WAVE];
-  __shared__ RunT rt[MAXRUN];
+  __shared__ RunT rt[GROUP * MAXRUN];
   SurvivorQueue Q{survq, 0, 0u, QCAP64, 0ull};
   const int total = B.cell_base[B.nbox];
   const int c0 = xcd_remap(blockIdx.x, gridDim.x) * cpw;
@@ -1164,7 +1159,7 @@ __global__ __launch_bounds__(WAVE) void k_detect_batched(DetectArgs A, BatchDev 
   if (c0 >= c1) return;
   int b = box_of_cell(B.cell_base, B.nbox, c0);
   int qb = b;  // the box of the queued survivors
-  for (int item = c0; item < c1; ++item) {
+  for (int item = c0; item < c1;) {
     while (item >= B.cell_base[b + 1]) ++b;  // boxes of no cells are passed over
     if (b != qb) {
       if (Q.n > 0) flush_survivors(A, B.gtab[qb], Q);
@@ -1172,10 +1167,15 @@ __global__ __launch_bounds__(WAVE) void k_detect_batched(DetectArgs A, BatchDev 
     }
     const Grid G = B.gtab[b];
     const int base = B.cell_base[b];
-    int code;
-    const int vs = cell_starts(G, A.start + base, item - base, code);
-    detect_cell64(A, G, vs, code, Q, hbeta, rt);
-    if (item + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
+    const int end = c1 < B.cell_base[b + 1] ? c1 : B.cell_base[b + 1];  // a group is of one box
+    const int nc = end - item < GROUP ? end - item : GROUP;
+    GroupRuns R;
+    group_runs(G, A.start + base, item - base, nc, rt, R);
+    for (int q = 0; q < nc; ++q, ++item) {
+      CellSet S;
+      if (group_cell(R, q, rt, S)) detect_cell64(A, G, S, Q, hbeta);
+      if (item + 1 == c1 || Q.n >= WAVE) flush_survivors(A, G, Q);
+    }
   }
 }
 
