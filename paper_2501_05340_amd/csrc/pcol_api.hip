@@ -356,7 +356,7 @@ void pcol_destroy(pcol_ctx *ctx) {
                  ctx->slot_j, ctx->key_j,  ctx->key_t,  ctx->status,      ctx->out,
                  ctx->ovf,    ctx->partner_tmp, ctx->tcoll_tmp, ctx->list_a,
                  ctx->ctr_d, ctx->dep_buf, ctx->crank, ctx->reach.parts, ctx->reach.hist,
-                 ctx->reach.phist, ctx->plan_d};
+                 ctx->plan_d};
   for (void *p : dev)
     if (p) (void)hipFree(p);
   if (ctx->plan_h) (void)hipHostFree(ctx->plan_h);
@@ -423,7 +423,6 @@ pcol_status pcol_create(pcol_ctx **out, int64_t n_max, void *hip_stream, const p
   A(dalloc(&ctx->plan_d, 1));
   A(dalloc(&ctx->reach.parts, REACH_BLOCKS));
   A(dalloc(&ctx->reach.hist, RHO_BINS));
-  A(dalloc(&ctx->reach.phist, (int64_t)REACH_BLOCKS * RHO_BINS));
   if (e == hipSuccess)
     e = hipMemsetAsync(ctx->reach.hist, 0, RHO_BINS * sizeof(unsigned int), ctx->stream);
   A(dalloc(&ctx->ctr_d, 1));

@@ -114,11 +114,11 @@ struct CurveGrid {
   double h[3];
 };
 
-// Scratch of the reach pass: REACH_BLOCKS partial results, the extent histogram
-// (RHO_BINS bins, zero between passes) and REACH_BLOCKS partial ones.
+// Scratch of the reach pass: REACH_BLOCKS partial results and the extent histogram
+// (RHO_BINS bins, zero between passes).
 struct ReachScratch {
   ReachPart *parts;
-  unsigned int *hist, *phist;
+  unsigned int *hist;
 };
 
 // Exclusive scan: SCAN_T threads of SCAN_E cells per tile; the words (zero before
@@ -678,8 +678,6 @@ struct DetectArgs {
 };
 
 hipError_t launch_fill_u32(hipStream_t s, unsigned int *p, unsigned int v, int64_t n);
-hipError_t launch_fill_u8(hipStream_t s, uint8_t *p, uint8_t v, int64_t n);
-hipError_t launch_fill_f64(hipStream_t s, double *p, double v, int64_t n);
 hipError_t launch_fill_i32(hipStream_t s, int *p, int v, int64_t n);
 // The reach pass and the plan.  hist_shift: the extent histogram covers the
 // spheres whose index is a multiple of 2^hist_shift.  G given: the pass also bins

@@ -131,16 +131,6 @@ __global__ void k_fill_u32(unsigned int *p, unsigned int v, int64_t n) {
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
 }
-__global__ void k_fill_u8(uint8_t *p, uint8_t v, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-__global__ void k_fill_f64(double *p, double v, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
 
 static int fill_grid(int64_t n) {
   int64_t g = (n + 255) / 256;
@@ -156,16 +146,6 @@ hipError_t launch_fill_u32(hipStream_t s, unsigned int *p, unsigned int v, int64
 hipError_t launch_fill_i32(hipStream_t s, int *p, int v, int64_t n) {
   return launch_fill_u32(s, (unsigned int *)p, (unsigned int)v, n);
 }
-hipError_t launch_fill_u8(hipStream_t s, uint8_t *p, uint8_t v, int64_t n) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_u8, dim3(fill_grid(n)), dim3(256), 0, s, p, v, n);
-  return hipGetLastError();
-}
-hipError_t launch_fill_f64(hipStream_t s, double *p, double v, int64_t n) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_f64, dim3(fill_grid(n)), dim3(256), 0, s, p, v, n);
-  return hipGetLastError();
-}
 
 // ---------------------------------------------------------------- a1: reach + validation
 
@@ -175,10 +155,10 @@ hipError_t launch_fill_f64(hipStream_t s, double *p, double v, int64_t n) {
 // validity cover every sphere; the histogram, which only picks the split
 // extent (a performance choice), covers the spheres whose index is a multiple
 // of 2^hist_shift.  Grid-stride over at most REACH_BLOCKS workgroups; each
-// histograms in LDS and stores its maxima in parts, which k_plan reduces.  Few
-// workgroups add their histograms (some 50 bins) to the result at once; many
-// store them whole in phist, which k_hist_sum reduces: no address takes an
-// atomic from more than REACH_DIRECT workgroups.
+// histograms in LDS, adds the bins it has (some 50) to the result, and stores its
+// maxima in parts, which k_plan reduces.  (Partial histograms and a kernel to add
+// them up, 9 us at 1M spheres and 12 at 16M, cost more than up to 1024 adds to an
+// address, 3 us at 1M and none at 16M, that end while others still read.)
 // BIN: the same pass also takes each sphere's cell and slot on the grid G with
 // split extent rho_c, exactly as k_cell_hist does (the binning of a step whose
 // grid is planned before its reach is known; the plan is checked against the
@@ -187,8 +167,8 @@ hipError_t launch_fill_f64(hipStream_t s, double *p, double v, int64_t n) {
 template <bool BIN>
 __global__ __launch_bounds__(256) void k_reach(Particles P, double L0, double L1, double L2,
                                                double dt, int hist_shift, ReachPart *parts,
-                                               unsigned int *sum, unsigned int *phist, Grid G,
-                                               double rho_c, int *cid, int *slot, int *count) {
+                                               unsigned int *sum, Grid G, double rho_c, int *cid,
+                                               int *slot, int *count) {
   __shared__ unsigned int hist[RHO_BINS];
   for (int k = threadIdx.x; k < RHO_BINS; k += 256) hist[k] = 0u;
   __syncthreads();
@@ -292,27 +272,8 @@ __global__ __launch_bounds__(256) void k_reach(Particles P, double L0, double L1
     for (int w = 1; w < 256 / WAVE; ++w) p = reach_merge(p, wpart[w]);
     parts[blockIdx.x] = p;
   }
-  for (int k = threadIdx.x; k < RHO_BINS; k += 256) {
-    if (phist)
-      phist[(int64_t)blockIdx.x * RHO_BINS + k] = hist[k];
-    else if (hist[k])
-      atomicAdd(&sum[k], hist[k]);
-  }
-}
-
-// Sum of k_reach's nblocks partial histograms: REACH_FINAL_Y workgroups per 256
-// bins, each summing a share of them and adding its non-zero sums.
-constexpr int REACH_FINAL_Y = 32;
-constexpr int REACH_DIRECT = 512;
-
-__global__ __launch_bounds__(256) void k_hist_sum(int nblocks, const unsigned int *phist,
-                                                  unsigned int *sum) {
-  const int b = blockIdx.x * 256 + threadIdx.x;  // bin
-  const int per = (nblocks + REACH_FINAL_Y - 1) / REACH_FINAL_Y;
-  const int k0 = blockIdx.y * per, k1 = k0 + per < nblocks ? k0 + per : nblocks;
-  unsigned int t = 0u;
-  for (int k = k0; k < k1; ++k) t += phist[(int64_t)k * RHO_BINS + b];
-  if (t) atomicAdd(&sum[b], t);
+  for (int k = threadIdx.x; k < RHO_BINS; k += 256)
+    if (hist[k]) atomicAdd(&sum[k], hist[k]);
 }
 
 // The step's plan from the reach pass (make_plan: the checks, the split extent,
@@ -386,17 +347,12 @@ hipError_t launch_reach(hipStream_t s, const Particles &P, double dt, int hist_s
   int64_t g = std::max(g4, std::min(g1, (int64_t)128));
   if (g > REACH_BLOCKS) g = REACH_BLOCKS;
   if (g < 1) g = 1;
-  unsigned int *phist = g > REACH_DIRECT ? R.phist : nullptr;
   if (G)
     hipLaunchKernelGGL(k_reach<true>, dim3((int)g), dim3(256), 0, s, P, A.L[0], A.L[1], A.L[2], dt,
-                       hist_shift, R.parts, R.hist, phist, *G, rho_c, cid, slot, count);
+                       hist_shift, R.parts, R.hist, *G, rho_c, cid, slot, count);
   else
     hipLaunchKernelGGL(k_reach<false>, dim3((int)g), dim3(256), 0, s, P, A.L[0], A.L[1], A.L[2],
-                       dt, hist_shift, R.parts, R.hist, phist, Grid{}, 0.0, nullptr, nullptr,
-                       nullptr);
-  if (phist)
-    hipLaunchKernelGGL(k_hist_sum, dim3(RHO_BINS / 256, REACH_FINAL_Y), dim3(256), 0, s, (int)g,
-                       phist, R.hist);
+                       dt, hist_shift, R.parts, R.hist, Grid{}, 0.0, nullptr, nullptr, nullptr);
   hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, s, A, (int)g, R.parts, R.hist, ctr, scan, plan,
                      plan_host);
   return hipGetLastError();
@@ -642,10 +598,6 @@ struct alignas(16) RunT {
   int off, code;
   double sx, sy, sz;
 };
-
-// Candidate slots past the end of the list hold this far-away sphere: its
-// separation squares to +inf and b stays finite, so it never passes the reject.
-constexpr double FAR_AWAY = 1e300;
 
 // Append contact (i, j, t) to both spheres' slots.
 __device__ __forceinline__ void record_contact(const DetectArgs &A, int i, int g, double t) {
@@ -1519,7 +1471,7 @@ __device__ __forceinline__ void wide_run(const Grid &G, const int *start, int r,
 // rho_c (their extents are at most rho_c); of the second layer, those after p
 // within p's extent plus the largest extent, so each pair of large-extent
 // spheres is tested once.  Pairs of two first-layer spheres belong to
-// k_detect_half.  The lanes first fetch up to 64 row runs of the ball-pruned
+// k_detect_half64.  The lanes first fetch up to 64 row runs of the ball-pruned
 // search box at once and scan their lengths; then each lane takes every 64th
 // candidate of the concatenated runs, finding its run by a binary search over
 // the scanned lengths held across the wave.  An FMA pre-filter (tolerance for
