@@ -1663,9 +1663,10 @@ hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const 
                                double dt, const uint8_t *status, int *key_j, double *key_t,
                                const BatchDev *B, const unsigned int *err,
                                const unsigned long long *crank) {
-  // a list whose length is on the device is short: a wave for 64 of the nlist
-  // spheres it could name at most, in 16 to 2048 workgroups
-  int64_t waves = nlist_dev ? std::max((int64_t)64, (int64_t)nlist / 64) : nlist;
+  // a list whose length is on the device is mostly short: a wave for 8 of the nlist
+  // spheres it could name at most, in 16 to 2048 workgroups (for 64, one contact
+  // slot and 100k spheres, a third of them listed, the search took 220 us, not 130)
+  int64_t waves = nlist_dev ? std::max((int64_t)64, (int64_t)nlist / 8) : nlist;
   if (nlist <= 0) return hipSuccess;
   if (waves > 8192) waves = 8192;
   const int blocks = (int)((waves + 3) / 4);
@@ -1881,10 +1882,12 @@ __device__ __forceinline__ bool sweep_off(const SweepArgs &A) {
 // Entries of the list that a wave takes at a time: all its lanes one each, but
 // where they may have to search, the wave on one sphere after another, one or a
 // few (64 searches in a row took 0.4 ms a step in boxes of fewer than 3 cells on an
-// axis, where every new partner is a search).
+// axis, where every new partner is a search; with one contact slot, two steps of
+// 100k spheres take 1277, 1303 and 1387 us for 2, 4 and 8 entries, of 1M 8346,
+// 8098 and 8007).
 template <bool EXACT>
 __device__ __forceinline__ int wave_share(const SweepArgs &A) {
-  return !EXACT ? WAVE : (A.small ? 1 : 8);
+  return !EXACT ? WAVE : (A.small ? 1 : 4);
 }
 
 // This lane's entry, count (none) past the end or its wave's share.
@@ -2000,7 +2003,7 @@ hipError_t launch_sweep_first(hipStream_t s, const SweepArgs &A, const int *key)
 // Grid of a kernel over the list: one row of workgroups per shard, enough for
 // a quarter of the spheres at once (a tenth is usual; more take another turn).
 static dim3 list_grid(const SweepArgs &A) {
-  const int per = A.exact ? (A.small ? WAVE : 8) : 1;  // workgroups for 256 entries
+  const int per = A.exact ? (A.small ? WAVE : 16) : 1;  // workgroups for 256 entries
   return dim3((unsigned)std::min((int64_t)8192, ((int64_t)A.shard_blocks * per + 3) / 4), A.shards);
 }
 
