@@ -423,14 +423,11 @@ pcol_status pcol_create(pcol_ctx **out, int64_t n_max, void *hip_stream, const p
   A(dalloc(&ctx->plan_d, 1));
   A(dalloc(&ctx->reach.parts, REACH_BLOCKS));
   A(dalloc(&ctx->reach.hist, RHO_BINS));
-  if (e == hipSuccess)
-    e = hipMemsetAsync(ctx->reach.hist, 0, RHO_BINS * sizeof(unsigned int), ctx->stream);
   A(dalloc(&ctx->ctr_d, 1));
   if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->plan_h, sizeof(StepPlan));
   if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->rep, sizeof(StepReport));
   for (hipEvent_t &ev : ctx->ev)
     if (e == hipSuccess) e = hipEventCreate(&ev);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) {
     pcol_destroy(ctx);
     return e == hipErrorOutOfMemory ? PCOL_E_NOMEM : PCOL_E_HIP;
@@ -440,9 +437,12 @@ pcol_status pcol_create(pcol_ctx **out, int64_t n_max, void *hip_stream, const p
 }
 
 // The cell arrays for `cells` cells (of both layers), with room for a grid a
-// little finer; the counts start at zero.
+// little finer; the counts start at zero, and so does the extent histogram with
+// the first ones (a context that only deposits needs none of them: clearing the
+// histogram in pcol_create, and waiting for that, took 50 us).
 static pcol_status grow_cells(pcol_ctx *ctx, int64_t cells) {
   if (cells + 2 <= ctx->cell_cap) return PCOL_OK;
+  const bool first = ctx->cell_cap == 0;
   PCOL_HIP(hipStreamSynchronize(ctx->stream));
   if (ctx->count) (void)hipFree(ctx->count);
   if (ctx->start) (void)hipFree(ctx->start);
@@ -460,6 +460,8 @@ static pcol_status grow_cells(pcol_ctx *ctx, int64_t cells) {
   if (e == hipSuccess)
     e = hipMemsetAsync(ctx->scan, 0, sizeof(ScanState) + (size_t)(cap / SCAN_B + 2) * 8,
                        ctx->stream);
+  if (e == hipSuccess && first)
+    e = hipMemsetAsync(ctx->reach.hist, 0, RHO_BINS * sizeof(unsigned int), ctx->stream);
   if (e != hipSuccess) return fail(ctx, PCOL_E_NOMEM, "cell arrays");
   ctx->cell_cap = cap;
   ctx->counts_dirty = false;
