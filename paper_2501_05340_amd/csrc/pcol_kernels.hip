@@ -2113,9 +2113,10 @@ hipError_t launch_finish(hipStream_t s, const Particles &P, const int *rank, con
                          const StepPlan *plan, const int *start, const BatchDev *B,
                          const SweepCounters *ctr, int nsweep, bool exact, const unsigned int *err,
                          StepReport *rep) {
-  if (P.n <= 0) return hipSuccess;
+  // one workgroup also where there are no spheres: the host reads the report
   BatchDev none{};
-  hipLaunchKernelGGL(k_finish, dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, s, P, rank, out,
+  const unsigned blocks = P.n > 0 ? (unsigned)((P.n + 255) / 256) : 1u;
+  hipLaunchKernelGGL(k_finish, dim3(blocks), dim3(256), 0, s, P, rank, out,
                      status, partner, tcoll, dt, plan, start, B ? *B : none, ctr, nsweep,
                      (int)exact, err, rep);
   return hipGetLastError();
