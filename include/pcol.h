@@ -81,8 +81,9 @@ typedef enum {
   PCOL_E_NOMEM = 3,   /* device allocation failed */
   PCOL_E_HIP = 4,     /* a HIP runtime call failed; see pcol_last_error */
   PCOL_E_SWEEPS = 5,  /* opts.max_sweeps sweeps ran and the last still resolved pairs */
-  PCOL_E_STATE = 6,   /* call order: pcol_detect / pcol_resolve before pcol_bin, or for a
-                         different particle count than the last pcol_bin */
+  PCOL_E_STATE = 6,   /* call order: pcol_detect / pcol_resolve before pcol_bin, after a
+                         pcol_step_batched, or for a different particle count than the
+                         last pcol_bin */
   PCOL_E_SCRATCH = 7  /* pcol_deposit_noalloc: the input needs more than the library's
                          fixed device scratch (PCOL_NOALLOC_SCRATCH_BYTES) */
 } pcol_status;
@@ -295,7 +296,9 @@ typedef struct {
  * per workgroup on scratch copies of the input and keeps the fastest; choices are
  * cached in the text file named by the environment variable PCOL_TUNE_CACHE
  * (default $HOME/.cache/pcol_tune.txt), keyed by GPU and batch shape.
- * Synchronises once per call (plus planning and tuning calls). */
+ * Synchronises once per call (plus planning and tuning calls).  Its scratch is the
+ * last binning's: pcol_detect and pcol_resolve return PCOL_E_STATE after it until
+ * pcol_bin runs again. */
 pcol_status pcol_step_batched(pcol_ctx *ctx, int32_t nbox, const int64_t *box_off,
                               const pcol_box *boxes, pcol_particles *p, double dt, double e,
                               int32_t *partner, double *tcoll, pcol_batch_stats *stats);

@@ -1483,6 +1483,7 @@ extern "C" pcol_status pcol_step_batched(pcol_ctx *ctx, int32_t nbox, const int6
     for (int a = 0; a < 3; ++a)
       if (!finite_pos(boxes[b].len[a])) return fail(ctx, PCOL_E_INVALID, "box side not finite positive");
   }
+  ctx->binned = false;  // the batch's spheres and cells take the place of the last binning's
   if (!ctx->bp) {
     ctx->bp = new (std::nothrow) BatchPlan();
     if (!ctx->bp) return PCOL_E_NOMEM;
