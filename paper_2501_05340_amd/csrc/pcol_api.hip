@@ -1265,7 +1265,7 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   // discarded with everything else if the check fails)
   PCOL_HIP(launch_fill_i32(s, ctx->count, 0, ncell));
   PCOL_HIP(launch_fill_u32(s, (unsigned int *)ctx->scan, 0u,
-                           2 + 2 * (int64_t)((ncell + SCAN_B - 1) / SCAN_B + 1)));
+                           2 + 2 * ((int64_t)scan_tiles(ncell) + 1)));
   PCOL_HIP(launch_breach(s, P, B, dt, 1, ctx->cid, ctx->slot, ctx->count));
   PCOL_HIP(launch_scan(s, ctx->count, ncell, nullptr, ctx->start, ctx->scan, nullptr));
   PCOL_HIP(launch_scatter(s, P, ctx->cid, ctx->slot, ctx->start, ctx->rec, ctx->rank, ctx->cnt, &B,

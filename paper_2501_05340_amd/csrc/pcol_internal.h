@@ -126,6 +126,10 @@ struct ReachScratch {
 constexpr int SCAN_T = 1024;
 constexpr int SCAN_E = 4;
 constexpr int SCAN_B = SCAN_T * SCAN_E;
+// Tiles of a scan of n cells (n up to 2^31 - 1: rounding up must not leave int).
+__host__ __device__ constexpr int scan_tiles(int64_t n) {
+  return (int)((n + (SCAN_B - 1)) / SCAN_B);
+}
 struct ScanState {
   int ticket, pad;
   unsigned long long word[1];  // one per tile, and one more

@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void k_plan(PlanArgs A, int nparts, const Reac
     ((unsigned long long *)plan_host)[k] = o[k];
   }
   if (out.err != 0u) return;  // (then there may be no room for the cells either)
-  for (int k = t; k <= (out.cells + SCAN_B - 1) / SCAN_B; k += 256) scan->word[k] = 0ull;
+  for (int k = t; k <= scan_tiles(out.cells); k += 256) scan->word[k] = 0ull;
   if (t == 0) scan->ticket = 0;
 }
 
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(SCAN_T) void k_scan(int *count, int n_host, const S
                                                  unsigned int *maxcell) {
   if (plan && plan->err) return;
   const int n = plan ? plan->cells : n_host;
-  const int tiles = (n + SCAN_B - 1) / SCAN_B;
+  const int tiles = scan_tiles(n);
   __shared__ int tile, before;
   __shared__ int wmax[SCAN_T / WAVE];
   for (;;) {
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(SCAN_T) void k_scan(int *count, int n_host, const S
 
 hipError_t launch_scan(hipStream_t s, int *count, int ncell, const StepPlan *plan, int *start,
                         ScanState *st, unsigned int *maxcell) {
-  const int tiles = (ncell + SCAN_B - 1) / SCAN_B;
+  const int tiles = scan_tiles(ncell);
   hipLaunchKernelGGL(k_scan, dim3(std::max(1, std::min(tiles, 512))), dim3(SCAN_T), 0, s, count,
                      ncell, plan, start, st, maxcell);
   return hipGetLastError();
@@ -3051,7 +3051,7 @@ hipError_t deposit_sorted(hipStream_t s, const DepositArgs &D) {
 int64_t deposit_record_bytes(int comp) { return ((int64_t)(4 + comp) * 8 + 15) / 16 * 16; }
 
 hipError_t launch_deposit_count(hipStream_t s, const DepositArgs &D) {
-  const int words = (int)((D.nnode + SCAN_B - 1) / SCAN_B) + 1;
+  const int words = scan_tiles(D.nnode) + 1;
   hipLaunchKernelGGL(k_dep_clear, dim3(fill_grid(D.nnode)), dim3(256), 0, s, D, words);
   if (D.n > 0)
     hipLaunchKernelGGL(k_dep_count, dim3((unsigned)((D.n + 255) / 256)), dim3(256), 0, s, D);
