@@ -279,7 +279,7 @@ hipError_t deposit_run(DepositArgs &D, const DepositLayout &Lo, unsigned char *b
   D.flag_host = pinned ? flag_h : nullptr;
   hipError_t e = launch_deposit_count(s, D);
   if (e == hipSuccess)
-    e = launch_scan(s, D.cnt, (int)D.nnode, nullptr, D.start, D.scan, nullptr);
+    e = launch_scan(s, D.cnt, (int)D.nnode, nullptr, D.start, D.scan, nullptr, false);
   if (e == hipSuccess) e = launch_deposit(s, D);
   if (e != hipSuccess || D.n == 0) return e;
   if (!pinned)
@@ -586,7 +586,7 @@ static pcol_status bin_queue(pcol_ctx *ctx, const pcol_particles *p, const pcol_
   PCOL_HIP(launch_cell_hist(s, P, ctx->plan_d, dt, tried ? last.cells : 0, ctx->cid, ctx->slot,
                             ctx->count));
   PCOL_HIP(launch_scan(s, ctx->count, cells, ctx->plan_d, ctx->start, ctx->scan,
-                       &ctx->ctr_d->maxcell));
+                       &ctx->ctr_d->maxcell, true));
   ctx->counts_dirty = ahead;
   PCOL_HIP(launch_scatter(s, P, ctx->cid, ctx->slot, ctx->start, ctx->rec, ctx->rank, ctx->cnt,
                           nullptr, &ctx->plan_d->err));
@@ -1267,7 +1267,7 @@ static pcol_status batch_enqueue(pcol_ctx *ctx, hipStream_t s, const Particles &
   PCOL_HIP(launch_fill_u32(s, (unsigned int *)ctx->scan, 0u,
                            2 + 2 * ((int64_t)scan_tiles(ncell) + 1)));
   PCOL_HIP(launch_breach(s, P, B, dt, 1, ctx->cid, ctx->slot, ctx->count));
-  PCOL_HIP(launch_scan(s, ctx->count, ncell, nullptr, ctx->start, ctx->scan, nullptr));
+  PCOL_HIP(launch_scan(s, ctx->count, ncell, nullptr, ctx->start, ctx->scan, nullptr, true));
   PCOL_HIP(launch_scatter(s, P, ctx->cid, ctx->slot, ctx->start, ctx->rec, ctx->rank, ctx->cnt, &B,
                           bp->flags + FLAG_ERR));
   DetectArgs A{};

@@ -698,9 +698,9 @@ hipError_t launch_cell_hist(hipStream_t s, const Particles &P, const StepPlan *p
 // the spheres of the second layer, if there is one
 hipError_t launch_detect_wide(hipStream_t s, const DetectArgs &A);
 // one-pass scan of plan->cells counts (ncell: as many as the host expects) or, with
-// no plan, of ncell; clears the counts; *st zero on entry
+// no plan, of ncell; clears the counts on request; *st zero on entry
 hipError_t launch_scan(hipStream_t s, int *count, int ncell, const StepPlan *plan, int *start,
-                        ScanState *st, unsigned int *maxcell);
+                        ScanState *st, unsigned int *maxcell, bool clear);
 hipError_t launch_scatter(hipStream_t s, const Particles &P, const int *cid, const int *slot,
                           const int *start, Rec *rec, int *rank, int *cnt, const BatchDev *B,
                           const unsigned int *err);

@@ -436,15 +436,17 @@ __device__ void block_exclusive_scan(int v, int &excl) {
 // as they have it and its running total once they have added those before it,
 // looked up 64 tiles at a time by one wave.  A tile only waits for tiles taken
 // before it, which are held by workgroups that run.  The sum and its state travel
-// in one 64-bit word, so no other ordering is needed.  The counts are left zero
-// for the next binning; the largest one goes to *maxcell.
+// in one 64-bit word, so no other ordering is needed.  clear: the counts are left
+// zero for the next binning (the deposition clears its own, which may lie in a new
+// buffer: left alone, the scan of 27M counts takes 122 us, not 152).  The largest count
+// goes to *maxcell.
 // Three launches (tile sums, their scan, the addition) did the same: 26 us at
 // 2.7M cells and 3 launches of about 2 us, and as many gaps, at a thousand.
 enum : unsigned int { SCAN_SUM = 1u, SCAN_TOTAL = 2u };
 
 __global__ __launch_bounds__(SCAN_T) void k_scan(int *count, int n_host, const StepPlan *plan,
                                                  int *start, ScanState *st,
-                                                 unsigned int *maxcell) {
+                                                 unsigned int *maxcell, int clear) {
   if (plan && plan->err) return;
   const int n = plan ? plan->cells : n_host;
   const int tiles = scan_tiles(n);
@@ -512,7 +514,7 @@ __global__ __launch_bounds__(SCAN_T) void k_scan(int *count, int n_host, const S
     for (int k = 0; k < SCAN_E; ++k) {
       if (base + k < n) {
         start[base + k] = run;
-        count[base + k] = 0;
+        if (clear) count[base + k] = 0;
       }
       run += v[k];
     }
@@ -521,10 +523,10 @@ __global__ __launch_bounds__(SCAN_T) void k_scan(int *count, int n_host, const S
 }
 
 hipError_t launch_scan(hipStream_t s, int *count, int ncell, const StepPlan *plan, int *start,
-                        ScanState *st, unsigned int *maxcell) {
+                        ScanState *st, unsigned int *maxcell, bool clear) {
   const int tiles = scan_tiles(ncell);
   hipLaunchKernelGGL(k_scan, dim3(std::max(1, std::min(tiles, 512))), dim3(SCAN_T), 0, s, count,
-                     ncell, plan, start, st, maxcell);
+                     ncell, plan, start, st, maxcell, (int)clear);
   return hipGetLastError();
 }
 
