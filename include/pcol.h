@@ -390,9 +390,10 @@ pcol_status pcol_step_backward(pcol_ctx *ctx, const pcol_particles *start, const
  * b = 0..7.  Repeated calls on the same input therefore agree bit for bit (up
  * to 64 spheres per element); against a sum in caller-index order each node is
  * within 2 (k - 1) 2^-53 sum|w a| (k its number of terms), and a node with one
- * term is exact.  Positions are checked on the device first (the verdict is read
- * back at the end, so the call synchronises with the stream); on PCOL_E_INVALID
- * out is unchanged.
+ * term is exact.  Positions are checked on the device first: the call waits for the
+ * verdict, not for the node sums queued behind it, so out is complete once the
+ * stream has been waited for (a later call on another stream waits for the device
+ * first); on PCOL_E_INVALID out is unchanged.
  * n = 0 gives zeros.  Scratch: 8 + 16 ceil((4 + comp) / 2) bytes per sphere
  * (72 for comp = 4) and 8 bytes per element, held by the context and grown on
  * demand (independent of n_max); growing it synchronises with the stream. */

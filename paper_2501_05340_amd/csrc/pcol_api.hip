@@ -66,6 +66,8 @@ struct pcol_ctx {
   int walls = 0;                   // set by pcol_step_walls for the step: bit k = walls on axis k
   // pcol_deposit: position check flag, and the element sort's scratch with its capacities
   unsigned int *dep_flag_h = nullptr;
+  hipEvent_t dep_known = nullptr;      // the flag has been written
+  hipStream_t dep_stream = nullptr;    // of the last deposition, whose node sums may still run
   unsigned char *dep_buf = nullptr;  // carved by deposit_layout
   int64_t dep_cap = 0;
   // The last two plans of a shape (sphere count, box, step, walls): the kernels of
@@ -263,11 +265,14 @@ pcol_status deposit_args(const double *x, const double *y, const double *z, int6
 
 // The deposition on stream s with its scratch at base (laid out by Lo).  The count
 // checks every position, and the kernels behind it do nothing if one is bad, so
-// all are queued at once and the flag is read at the end (into flag_h, host
-// memory; pinned: the last kernel writes it there itself); st receives
-// PCOL_E_INVALID for a bad position, else PCOL_OK.
+// all are queued at once and the flag is read behind them (into flag_h, host
+// memory); st receives PCOL_E_INVALID for a bad position, else PCOL_OK.  known
+// given: flag_h is page-locked, the scatter writes it, and the host waits for this
+// event behind the scatter only, not for the node sums (waiting for them too, 300,000
+// spheres onto 32^3 elements took 174 us a call among others, now 156, and a caller
+// could do nothing meanwhile).
 hipError_t deposit_run(DepositArgs &D, const DepositLayout &Lo, unsigned char *base, hipStream_t s,
-                       unsigned int *flag_h, bool pinned, pcol_status &st) {
+                       unsigned int *flag_h, hipEvent_t known, pcol_status &st) {
   st = PCOL_OK;
   D.eid = (int *)(base + Lo.eid);
   D.slot = (int *)(base + Lo.slot);
@@ -276,15 +281,18 @@ hipError_t deposit_run(DepositArgs &D, const DepositLayout &Lo, unsigned char *b
   D.start = (int *)(base + Lo.start);
   D.scan = (ScanState *)(base + Lo.scan);
   D.flag = (unsigned int *)(base + Lo.flag);
-  D.flag_host = pinned ? flag_h : nullptr;
+  D.flag_host = known ? flag_h : nullptr;
   hipError_t e = launch_deposit_count(s, D);
   if (e == hipSuccess)
     e = launch_scan(s, D.cnt, (int)D.nnode, nullptr, D.start, D.scan, nullptr, false);
-  if (e == hipSuccess) e = launch_deposit(s, D);
+  if (e == hipSuccess) e = launch_deposit(s, D, D.n > 0 ? known : nullptr);
   if (e != hipSuccess || D.n == 0) return e;
-  if (!pinned)
+  if (known) {
+    e = hipEventSynchronize(known);
+  } else {
     e = hipMemcpyAsync(flag_h, D.flag, sizeof(unsigned int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+  }
   if (e == hipSuccess && *flag_h) st = PCOL_E_INVALID;
   return e;
 }
@@ -362,6 +370,7 @@ void pcol_destroy(pcol_ctx *ctx) {
   if (ctx->plan_h) (void)hipHostFree(ctx->plan_h);
   if (ctx->rep) (void)hipHostFree(ctx->rep);
   if (ctx->dep_flag_h) (void)hipHostFree(ctx->dep_flag_h);
+  if (ctx->dep_known) (void)hipEventDestroy(ctx->dep_known);
   for (hipEvent_t &e : ctx->ev)
     if (e) (void)hipEventDestroy(e);
   if (BatchPlan *bp = ctx->bp) {
@@ -1030,18 +1039,23 @@ pcol_status pcol_deposit(pcol_ctx *ctx, const double *x, const double *y, const 
   if (st != PCOL_OK) return fail(ctx, st, why);
   hipStream_t s = ctx->stream;
   const DepositLayout Lo = deposit_layout(D.n, D.nnode, comp);
-  if (ctx->dep_cap < Lo.bytes || !ctx->dep_flag_h) {
+  // the last deposition's node sums read the scratch on another stream
+  if (ctx->dep_flag_h && ctx->dep_stream != s) PCOL_HIP(hipDeviceSynchronize());
+  ctx->dep_stream = s;
+  if (ctx->dep_cap < Lo.bytes || !ctx->dep_known) {
     PCOL_HIP(hipStreamSynchronize(s));  // the free below waits for nothing queued
     hipError_t e = grow(&ctx->dep_buf, ctx->dep_cap, Lo.bytes);
     if (e == hipSuccess && !ctx->dep_flag_h)
       e = hipHostMalloc((void **)&ctx->dep_flag_h, sizeof(unsigned int));
+    if (e == hipSuccess && !ctx->dep_known)
+      e = hipEventCreateWithFlags(&ctx->dep_known, hipEventDisableTiming);
     if (e != hipSuccess) {
       (void)hipGetLastError();
       return fail(ctx, e == hipErrorOutOfMemory ? PCOL_E_NOMEM : PCOL_E_HIP,
                   "deposition scratch allocation failed");
     }
   }
-  hipError_t e = deposit_run(D, Lo, ctx->dep_buf, s, ctx->dep_flag_h, true, st);
+  hipError_t e = deposit_run(D, Lo, ctx->dep_buf, s, ctx->dep_flag_h, ctx->dep_known, st);
   if (e != hipSuccess) return hip_fail(ctx, e, "pcol_deposit");
   if (st != PCOL_OK) return fail(ctx, st, "position outside [0, L) or not finite");
   return PCOL_OK;
@@ -1059,7 +1073,7 @@ pcol_status pcol_deposit_noalloc(const double *x, const double *y, const double 
   unsigned char *base = nullptr;
   if (static_scratch(&base) != hipSuccess) return PCOL_E_HIP;
   unsigned int flag_h = 0u;  // pageable host word: no pinned allocation
-  if (deposit_run(D, Lo, base, (hipStream_t)hip_stream, &flag_h, false, st) != hipSuccess)
+  if (deposit_run(D, Lo, base, (hipStream_t)hip_stream, &flag_h, nullptr, st) != hipSuccess)
     return PCOL_E_HIP;
   return st;
 }

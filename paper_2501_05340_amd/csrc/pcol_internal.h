@@ -778,15 +778,16 @@ struct DepositArgs {
   void *rec;
   ScanState *scan;
   unsigned int *flag;       // a position is bad: nothing of the caller's is written
-  unsigned int *flag_host;  // nullable: host memory that receives the flag
+  unsigned int *flag_host;  // nullable: host memory that receives the flag (n > 0)
 };
 int64_t deposit_record_bytes(int comp);
 // element and slot of every sphere (clears cnt, scan and flag first); positions
 // outside [0, L) or not finite set bit 0 of *flag and are skipped
 hipError_t launch_deposit_count(hipStream_t s, const DepositArgs &D);
 // after the scan of cnt into start: scatter, then element corner sums and node
-// sums over tiles of nodes
-hipError_t launch_deposit(hipStream_t s, const DepositArgs &D);
+// sums over tiles of nodes; known (nullable) is recorded behind the scatter, which
+// writes *flag_host
+hipError_t launch_deposit(hipStream_t s, const DepositArgs &D, hipEvent_t known);
 hipError_t launch_resolve_public(hipStream_t s, int n, const Rec *rec, const int *rank,
                                  const Grid &G, double dt, double e, const uint64_t *key,
                                  const Particles &P, uint8_t *active, int *partner, double *tcoll,

@@ -438,8 +438,8 @@ __device__ void block_exclusive_scan(int v, int &excl) {
 // before it, which are held by workgroups that run.  The sum and its state travel
 // in one 64-bit word, so no other ordering is needed.  clear: the counts are left
 // zero for the next binning (the deposition clears its own, which may lie in a new
-// buffer: left alone, the scan of 27M counts takes 122 us, not 152).  The largest count
-// goes to *maxcell.
+// buffer: left alone, the scan of 27M counts takes 122 us, not 152).  The largest
+// count goes to *maxcell.
 // Three launches (tile sums, their scan, the addition) did the same: 26 us at
 // 2.7M cells and 3 launches of about 2 us, and as many gaps, at a thousand.
 enum : unsigned int { SCAN_SUM = 1u, SCAN_TOTAL = 2u };
@@ -2898,6 +2898,7 @@ __global__ __launch_bounds__(256) void k_dep_count(DepositArgs D) {
 template <int COMP>
 __global__ __launch_bounds__(256) void k_dep_scatter(DepositArgs D) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (D.flag_host && i == 0) *D.flag_host = *D.flag;
   if (*D.flag) return;
   __shared__ Stage<sizeof(DepRec<COMP>) / 16> stage[256 / WAVE];
   DepRec<COMP> r{};
@@ -2989,7 +2990,6 @@ constexpr int DEP_TN = 7, DEP_TE = DEP_TN + 1, DEP_TILE_THREADS = DEP_TE * DEP_T
 
 template <int COMP>
 __global__ __launch_bounds__(DEP_TILE_THREADS) void k_dep_tile(DepositArgs D, int ntx, int nty) {
-  if (D.flag_host && blockIdx.x == 0 && threadIdx.x == 0) *D.flag_host = *D.flag;
   if (*D.flag) return;
   __shared__ double nacc[DEP_TN * DEP_TN * DEP_TN * COMP];
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
@@ -3038,9 +3038,13 @@ __global__ __launch_bounds__(DEP_TILE_THREADS) void k_dep_tile(DepositArgs D, in
 }
 
 template <int COMP>
-hipError_t deposit_sorted(hipStream_t s, const DepositArgs &D) {
+hipError_t deposit_sorted(hipStream_t s, const DepositArgs &D, hipEvent_t known) {
   const unsigned gn = (unsigned)((D.n + 255) / 256);
   if (D.n > 0) hipLaunchKernelGGL(k_dep_scatter<COMP>, dim3(gn), dim3(256), 0, s, D);
+  if (known) {
+    const hipError_t e = hipEventRecord(known, s);
+    if (e != hipSuccess) return e;
+  }
   const int ntx = (D.nc[0] + DEP_TN - 1) / DEP_TN, nty = (D.nc[1] + DEP_TN - 1) / DEP_TN,
             ntz = (D.nc[2] + DEP_TN - 1) / DEP_TN;
   hipLaunchKernelGGL(k_dep_tile<COMP>, dim3((unsigned)(ntx * nty * ntz)), dim3(DEP_TILE_THREADS),
@@ -3060,16 +3064,16 @@ hipError_t launch_deposit_count(hipStream_t s, const DepositArgs &D) {
   return hipGetLastError();
 }
 
-hipError_t launch_deposit(hipStream_t s, const DepositArgs &D) {
+hipError_t launch_deposit(hipStream_t s, const DepositArgs &D, hipEvent_t known) {
   switch (D.comp) {
-    case 1: return deposit_sorted<1>(s, D);
-    case 2: return deposit_sorted<2>(s, D);
-    case 3: return deposit_sorted<3>(s, D);
-    case 4: return deposit_sorted<4>(s, D);
-    case 5: return deposit_sorted<5>(s, D);
-    case 6: return deposit_sorted<6>(s, D);
-    case 7: return deposit_sorted<7>(s, D);
-    case 8: return deposit_sorted<8>(s, D);
+    case 1: return deposit_sorted<1>(s, D, known);
+    case 2: return deposit_sorted<2>(s, D, known);
+    case 3: return deposit_sorted<3>(s, D, known);
+    case 4: return deposit_sorted<4>(s, D, known);
+    case 5: return deposit_sorted<5>(s, D, known);
+    case 6: return deposit_sorted<6>(s, D, known);
+    case 7: return deposit_sorted<7>(s, D, known);
+    case 8: return deposit_sorted<8>(s, D, known);
     default: return hipErrorInvalidValue;
   }
 }
