@@ -624,19 +624,17 @@ static pcol_status check_binned(pcol_ctx *ctx, const pcol_particles *p, const pc
 
 // sweep 1: keys of all spheres (all active) into ctx->key_j / key_t (sorted
 // order); crank given: the literal order's partners instead of rule 2's
-// status given: of the ACTIVE spheres only, and only if *masked_err is 0.  The
-// spheres whose contacts overflowed their slots get no key (overflow_search).
+// The spheres whose contacts overflowed their slots get no key (overflow_search).
+// contacts_only: the pair tests alone; masked: if a masked detect takes them.
 static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long *crank,
-                              const uint8_t *status = nullptr,
-                              const unsigned int *masked_err = nullptr,
-                              bool contacts_only = false) {
+                              bool contacts_only = false, bool masked = false) {
   hipStream_t s = ctx->stream;
   const int n = (int)ctx->binned_n;
   // sized by the last plan that the host has seen: this binning's, or for a step
   // that has not waited yet the one before it (which then had no small grid, and
   // some plan of the shape a split one if this one has)
   const StepPlan &pl = ctx->plan;
-  const unsigned int *err = status ? masked_err : &ctx->plan_d->err;
+  const unsigned int *err = &ctx->plan_d->err;
   const Grid *G = &ctx->plan_d->G;
   if (!pl.small) {
     DetectArgs A{};
@@ -650,6 +648,7 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     A.K = ctx->K;
     A.plan = ctx->plan_d;
     A.err = err;
+    A.masked = masked;
     A.dt = dt;
     A.dt2 = 2.0 * dt * (1.0 + 0x1.0p-20);
     if (ctx->opts.timing) PCOL_HIP(hipEventRecord(ctx->ev[5], s));
@@ -661,21 +660,20 @@ static pcol_status detect_all(pcol_ctx *ctx, double dt, const unsigned long long
     ctx->detect_timed = true;
     if (contacts_only) return PCOL_OK;
     PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
-                             ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err, G, crank, status));
+                             ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err, G, crank));
   } else {
     // fewer than 3 cells on some axis: exact search for every sphere
-    PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, -1, ctx->rec, ctx->start, G, dt,
-                                 nullptr, ctx->key_j, ctx->key_t, nullptr, err, crank));
+    PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, ctx->rec, ctx->start, G, dt, ctx->key_j,
+                                 ctx->key_t, nullptr, err, crank));
   }
   return PCOL_OK;
 }
 
 // Keys, by the exact search, of the spheres that detect_all left out.
-static pcol_status overflow_search(pcol_ctx *ctx, double dt, const unsigned long long *crank,
-                                   const uint8_t *status, const unsigned int *err) {
+static pcol_status overflow_search(pcol_ctx *ctx, double dt, const unsigned long long *crank) {
   PCOL_HIP(launch_gather_exact(ctx->stream, ctx->ovf, (int)ctx->binned_n, &ctx->ctr_d->n_overflow,
-                               -1, ctx->rec, ctx->start, &ctx->plan_d->G, dt, status, ctx->key_j,
-                               ctx->key_t, nullptr, err, crank));
+                               ctx->rec, ctx->start, &ctx->plan_d->G, dt, ctx->key_j, ctx->key_t,
+                               nullptr, &ctx->plan_d->err, crank));
   return PCOL_OK;
 }
 
@@ -688,28 +686,26 @@ pcol_status pcol_detect(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *
   hipStream_t s = ctx->stream;
   const int n = (int)p->n;
   if (n == 0) return PCOL_OK;
-  PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
   if (!active) {
+    PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
     PCOL_HIP(launch_fill_i32(s, ctx->cnt, 0, n));
     if ((st = detect_all(ctx, dt, nullptr)) != PCOL_OK) return st;
-    if (!ctx->plan.small &&
-        (st = overflow_search(ctx, dt, nullptr, nullptr, &ctx->plan_d->err)) != PCOL_OK)
-      return st;
+    if (!ctx->plan.small && (st = overflow_search(ctx, dt, nullptr)) != PCOL_OK) return st;
   } else {
-    // the pair tests of all spheres if many of them are active, else (or on a small
-    // grid) the exact search of each active one; the device decides
+    // the pair tests of all spheres if many of them are active, else the exact search
+    // of each active one: the device decides.  The search alone on a small grid, and
+    // below SMALL_N spheres, where the launches count: 19 us at 3,000 spheres with few
+    // active and 25 with all, against 21 for either with the pair tests queued before it
+    // (10,000: 19 and 49, against 21 and 22).
+    const bool pairs = !ctx->plan.small && n >= SMALL_N;
     PCOL_HIP(launch_status_from_active(s, active, ctx->rec, n, ctx->status, ctx->cnt, ctx->ctr_d));
-    const bool small = ctx->plan.small != 0;
-    const unsigned int *off = &ctx->ctr_d->pairs_off;
-    if (!small && ((st = detect_all(ctx, dt, nullptr, ctx->status, off)) != PCOL_OK ||
-                   (st = overflow_search(ctx, dt, nullptr, ctx->status, off)) != PCOL_OK))
-      return st;
-    PCOL_HIP(launch_gather_exact(s, nullptr, n, nullptr, ST_ACTIVE, ctx->rec, ctx->start,
-                                 &ctx->plan_d->G, dt, ctx->status, ctx->key_j, ctx->key_t, nullptr,
-                                 small ? &ctx->plan_d->err : &ctx->ctr_d->sparse_off));
+    if (pairs && (st = detect_all(ctx, dt, nullptr, true, true)) != PCOL_OK) return st;
+    PCOL_HIP(launch_masked_keys(s, ctx->ctr_d, n, pairs, ctx->K, ctx->cnt, ctx->slot_t, ctx->slot_j,
+                                ctx->rec, ctx->start, &ctx->plan_d->G, dt, ctx->status, ctx->key_j,
+                                ctx->key_t));
   }
   PCOL_HIP(launch_export_keys(s, n, ctx->rec, ctx->key_j, ctx->key_t,
-                              active ? ctx->status : nullptr, key_out, tmin_out));
+                              active ? ctx->status : nullptr, ctx->ctr_d, key_out, tmin_out));
   return PCOL_OK;
 }
 
@@ -822,7 +818,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
     ctx->detect_timed = false;
     // (the friction resolve needs the registers of a whole workgroup of 1024 twice)
     bool one_tail = few && n <= SMALL_TAIL && !spin && !timing && !ctx->exact_sweeps;
-    if ((st = detect_all(ctx, dt, crank, nullptr, nullptr, one_tail)) != PCOL_OK) return st;
+    if ((st = detect_all(ctx, dt, crank, one_tail)) != PCOL_OK) return st;
     if (timing) PCOL_HIP(hipEventRecord(ctx->ev[2], s));
     SweepArgs W = sweep_args(ctx, P, dt, e);
     W.crank = crank;
@@ -830,7 +826,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
     // sweeps that cannot search stop at an overflow, so only the others need its keys
     const unsigned int *err = &ctx->plan_d->err;
     if (W.exact && !ctx->plan.small &&
-        (st = overflow_search(ctx, dt, crank, nullptr, err)) != PCOL_OK)
+        (st = overflow_search(ctx, dt, crank)) != PCOL_OK)
       return st;
     // All the sweeps that the step is likely to take, and the free flight behind
     // them, are queued at once: a sweep runs if the one before it resolved a pair,
@@ -857,7 +853,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
           PCOL_HIP(launch_slot_min(s, n, ctx->cnt, ctx->slot_t, ctx->slot_j, ctx->K, ctx->rec,
                                    ctx->key_j, ctx->key_t, ctx->ovf, ctx->ctr_d, err,
                                    &ctx->plan_d->G, crank));
-          if ((st = overflow_search(ctx, dt, crank, nullptr, err)) != PCOL_OK) return st;
+          if ((st = overflow_search(ctx, dt, crank)) != PCOL_OK) return st;
         } else {
           pairs = (int64_t)ctx->rep->small_pairs;
           sweeps = ctx->rep->small_sweeps;
@@ -891,7 +887,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
           W.crank = crank;
           if (spin) W.spin = *spin;
           if (W.exact && !ctx->plan.small &&
-              (st = overflow_search(ctx, dt, crank, nullptr, err)) != PCOL_OK)
+              (st = overflow_search(ctx, dt, crank)) != PCOL_OK)
             return st;
           continue;
         }
@@ -900,7 +896,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
       }
       if (!W.exact && ctx->rep->n_overflow) {  // nothing ran: again, with the exact search
         W.exact = ctx->exact_sweeps = 1;
-        if ((st = overflow_search(ctx, dt, crank, nullptr, err)) != PCOL_OK) return st;
+        if ((st = overflow_search(ctx, dt, crank)) != PCOL_OK) return st;
         continue;
       }
       bool done = false;
@@ -1261,9 +1257,8 @@ static SweepArgs batch_sweep_args(const pcol_ctx *ctx, const Particles &P, doubl
 // Keys, by the exact search, of the spheres whose contacts overflowed their slots.
 static hipError_t batch_overflow_search(pcol_ctx *ctx, hipStream_t s, const BatchDev &B, int n,
                                         double dt) {
-  return launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, -1, ctx->rec, ctx->start,
-                             nullptr, dt, nullptr, ctx->key_j, ctx->key_t, &B,
-                             ctx->bp->flags + FLAG_ERR);
+  return launch_gather_exact(s, ctx->ovf, n, &ctx->ctr_d->n_overflow, ctx->rec, ctx->start, nullptr,
+                             dt, ctx->key_j, ctx->key_t, &B, ctx->bp->flags + FLAG_ERR);
 }
 
 // Enqueue the whole batched step on stream s (captured into a graph).

@@ -346,13 +346,15 @@ __host__ __device__ inline void make_plan(const PlanArgs &A, const ReachPart &r,
 // no single address takes an atomic per wave; the pairs of a sweep over four.
 constexpr int NSHARD = 64;
 constexpr int PAIR_SHARDS = 4;
+constexpr int ACTIVE_SHARDS = 8;  // of a masked detect's active spheres
 constexpr int MAX_QUEUE = 256;  // sweeps queued without the host looking at them
 struct alignas(128) CounterShard {
   unsigned long long contacts;  // contacts found (each counted from both spheres)
   unsigned long long recheck;   // FP32 filter survivors rechecked in FP64 (counted per wave)
   unsigned long long tests;     // pair tests
   unsigned long long pairs;     // pairs resolved by the first sweep
-  unsigned long long pad[12];
+  unsigned long long active;    // masked detect: its active spheres (zero between calls)
+  unsigned long long pad[11];
 };
 struct alignas(128) ListShard {
   int n[3];  // spheres in this shard of the list of the later sweeps, three sweeps in turn
@@ -364,8 +366,7 @@ struct SweepCounters {
   unsigned int n_overflow;  // spheres with more contacts than slots (list length)
   unsigned int ovf_later;   // the same among those that took a new partner later
   unsigned int maxcell;     // largest cell occupancy
-  unsigned int pairs_off, sparse_off;  // masked detect: the one of its two ways not taken
-  unsigned int pad[27];
+  unsigned int pad[29];
   unsigned long long pairs[MAX_QUEUE][PAIR_SHARDS];  // pairs resolved by each later sweep
 };
 
@@ -604,6 +605,19 @@ constexpr int SMALL_N = 4096;
 constexpr int SMALL_CELLS = 8192;
 constexpr int SMALL_TAIL = 2048;
 
+// How a masked detect goes on: by the pair tests of all spheres and a choice among
+// the slots of the active ones if more than one in 24 are active, else by the exact
+// search of each active sphere.  Either leaves the same keys.  A call for 50,000,
+// 300,000 and 2M spheres takes 30, 107 and 602 us with the pair tests whatever the
+// mask, with the search 28, 69 and 309 us for one active in 64, 41, 145 and 728 us
+// for one in 17 and 188, 1224 and 7970 us for all.
+__device__ __forceinline__ bool masked_dense(const SweepCounters *ctr, int n) {
+  unsigned long long active = 0ull;
+#pragma unroll
+  for (int k = 0; k < ACTIVE_SHARDS; ++k) active += ctr->shard[k].active;
+  return active * 24ull > (unsigned long long)n;
+}
+
 // gradient with respect to a step's positions and velocities (SoA)
 struct StateGrad {
   double *x, *y, *z, *vx, *vy, *vz;
@@ -674,6 +688,7 @@ struct DetectArgs {
   int K;
   const StepPlan *plan;  // one box: grid and tolerances (null in the batched form)
   const unsigned int *err;  // one box: nonzero: do nothing
+  int masked;         // only if a masked detect takes the pair tests (masked_dense)
   double dt;
   double dt2;         // 2 dt (1 + 2^-20): step bound of the FP64 filter
   double tol64;       // binary64 Gram filter tolerance (see gram64_tolerance)
@@ -709,13 +724,15 @@ hipError_t launch_slot_min(hipStream_t s, int n, const int *cnt, const double *s
                            const int *slot_j, int K, const Rec *rec, int *key_j, double *key_t,
                            int *ovf_list, SweepCounters *ctr, const unsigned int *err,
                            const Grid *G = nullptr,  // device: walls of the box (none: periodic)
-                           const unsigned long long *crank = nullptr,  // literal order's ranks
-                           const uint8_t *status = nullptr);  // only ACTIVE spheres take part
+                           const unsigned long long *crank = nullptr);  // literal order's ranks
 hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const unsigned int *nlist_dev,
-                               int select, const Rec *rec, const int *start, const Grid *G,
-                               double dt, const uint8_t *status, int *key_j, double *key_t,
-                               const BatchDev *B, const unsigned int *err,
+                               const Rec *rec, const int *start, const Grid *G, double dt, int *key_j,
+                               double *key_t, const BatchDev *B, const unsigned int *err,
                                const unsigned long long *crank = nullptr);
+hipError_t launch_masked_keys(hipStream_t s, const SweepCounters *ctr, int n, bool pairs, int K,
+                              const int *cnt, const double *slot_t, const int *slot_j,
+                              const Rec *rec, const int *start, const Grid *G, double dt,
+                              const uint8_t *status, int *key_j, double *key_t);
 hipError_t launch_curve_rank(hipStream_t s, const Rec *rec, int n, const StepPlan *plan,
                              unsigned long long *crank);
 // The sweeps of a step (sweep_shards sets the list's shards).  first: every sphere;
@@ -752,12 +769,13 @@ hipError_t launch_detect_batched(hipStream_t s, const DetectArgs &A, const Batch
                                  int total_cells, int cpw);
 hipError_t launch_advance(hipStream_t s, const Particles &P, const int *partner, double dt,
                           const double L[3]);
-// ctr zero on entry; sets its pairs_off and sparse_off
+// counts the active spheres into ctr's shards (zero on entry)
 hipError_t launch_status_from_active(hipStream_t s, const uint8_t *active, const Rec *rec, int n,
                                      uint8_t *status, int *cnt, SweepCounters *ctr);
+// status given: a masked detect ends (the counts of its active spheres are cleared)
 hipError_t launch_export_keys(hipStream_t s, int n, const Rec *rec, const int *key_j,
-                              const double *key_t, const uint8_t *status, uint64_t *key_out,
-                              double *tmin_out);
+                              const double *key_t, const uint8_t *status, SweepCounters *ctr,
+                              uint64_t *key_out, double *tmin_out);
 hipError_t launch_step_backward(hipStream_t s, const Particles &P, const Grid &G, double dt,
                                 double e, const int *partner, const double *tcoll,
                                 const StateGrad &gout, const StateGrad &gin, double *epart,

@@ -1069,7 +1069,7 @@ __device__ __forceinline__ void detect_groups(const DetectArgs &A, int ncell, in
 }
 
 __global__ __launch_bounds__(WAVE, 6) void k_detect_half32(DetectArgs A) {
-  if (*A.err) return;
+  if (*A.err || (A.masked && !masked_dense(A.ctr, A.n))) return;
   __shared__ int2 survq[QCAP];
   __shared__ Rec32 hl[HB32];
   __shared__ RunT rt[GROUP * MAXRUN];
@@ -1092,7 +1092,7 @@ __global__ __launch_bounds__(WAVE, 6) void k_detect_half32(DetectArgs A) {
 }
 
 __global__ __launch_bounds__(WAVE, 6) void k_detect_half64(DetectArgs A) {
-  if (*A.err) return;
+  if (*A.err || (A.masked && !masked_dense(A.ctr, A.n))) return;
   __shared__ int2 survq[QCAP64];
   __shared__ double hbeta[WAVE];
   __shared__ RunT rt[GROUP * MAXRUN];
@@ -1252,15 +1252,12 @@ struct GoneNone {
 
 // Sweep 1's partner of every sphere.  Spheres with more contacts than slots are
 // queued for the exact search (rare; one atomic per wave that has one).
-// MASK: only the spheres whose status is ACTIVE take part.
-template <bool MASK>
 __global__ __launch_bounds__(256) void k_slot_min(int n, const int *cnt, const double *slot_t,
                                                   const int *slot_j, int K, const Rec *rec,
                                                   int *key_j, double *key_t, int *ovf_list,
                                                   SweepCounters *ctr, const unsigned int *err,
                                                   const Grid *Gp,
-                                                  const unsigned long long *crank,
-                                                  const uint8_t *status) {
+                                                  const unsigned long long *crank) {
   if (*err) return;
   Grid G{};  // the walls are all that matters here (none in the batched form)
   if (Gp) G = *Gp;
@@ -1268,16 +1265,12 @@ __global__ __launch_bounds__(256) void k_slot_min(int n, const int *cnt, const d
   bool ovf = false;
   unsigned long long nc = 0ull;
   if (i < n) {
-    const int c = MASK && status[i] != ST_ACTIVE ? 0 : cnt[i];
+    const int c = cnt[i];
     nc = (unsigned long long)c;
     ovf = c > K;
     int bj;
     double bt;
-    if (MASK)
-      slot_choice(i, ovf ? 0 : c, (size_t)n, slot_t, slot_j, rec, G, crank, GoneCollided{status},
-                  bj, bt);
-    else
-      slot_choice(i, ovf ? 0 : c, (size_t)n, slot_t, slot_j, rec, G, crank, GoneNone{}, bj, bt);
+    slot_choice(i, ovf ? 0 : c, (size_t)n, slot_t, slot_j, rec, G, crank, GoneNone{}, bj, bt);
     key_j[i] = bj;
     key_t[i] = bt;
   }
@@ -1289,13 +1282,10 @@ __global__ __launch_bounds__(256) void k_slot_min(int n, const int *cnt, const d
 hipError_t launch_slot_min(hipStream_t s, int n, const int *cnt, const double *slot_t,
                            const int *slot_j, int K, const Rec *rec, int *key_j, double *key_t,
                            int *ovf_list, SweepCounters *ctr, const unsigned int *err,
-                           const Grid *G, const unsigned long long *crank, const uint8_t *status) {
+                           const Grid *G, const unsigned long long *crank) {
   if (n <= 0) return hipSuccess;
-  const auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, cnt, slot_t, slot_j, K,
-                       rec, key_j, key_t, ovf_list, ctr, err, G, crank, status);
-  };
-  status ? go(k_slot_min<true>) : go(k_slot_min<false>);
+  hipLaunchKernelGGL(k_slot_min, dim3((n + 255) / 256), dim3(256), 0, s, n, cnt, slot_t, slot_j, K,
+                     rec, key_j, key_t, ovf_list, ctr, err, G, crank);
   return hipGetLastError();
 }
 
@@ -1480,7 +1470,7 @@ __device__ __forceinline__ void wide_run(const Grid &G, const int *start, int r,
 // the full reach) keeps the exact rule for the few pairs that may touch;
 // survivors are decided at once (they are rare).
 __global__ __launch_bounds__(256) void k_detect_wide(DetectArgs A) {
-  if (*A.err || !A.plan->G.layer2) return;
+  if (*A.err || !A.plan->G.layer2 || (A.masked && !masked_dense(A.ctr, A.n))) return;
   const Grid G = A.plan->G;
   const double rho_c = A.plan->rho_c, tol_wide = A.plan->tol_wide;
   const int n = A.n;
@@ -1623,17 +1613,33 @@ __device__ __forceinline__ void exact_partner(int i, const Rec &a, const Grid &G
   }
 }
 
-// Exact partners of a list of spheres, one wave per sphere (exact_partner):
-// `list` of length nlist, or *nlist_dev when given, or, with list NULL, all
-// i < nlist whose status is `select` (select < 0: all).  status (nullable: none
-// has) tells the collided spheres, never candidates.  Used for spheres whose
-// contacts overflowed the slots, for pcol_detect with an active mask, and for
-// grids with fewer than 3 cells along some axis.
+// Exact partner of sphere i by the whole wave (exact_partner) into its key; on the
+// single grid Gp, or on its box's in the batched form.
+__device__ __forceinline__ void gather_one(int i, const Rec *rec, const int *start, const Grid *Gp,
+                                           double dt, const uint8_t *status, int *key_j,
+                                           double *key_t, const BatchDev &B,
+                                           const unsigned long long *crank) {
+  const Rec a = rec[i];
+  const int bx = B.gtab ? a.box : 0;
+  const Grid G = B.gtab ? B.gtab[bx] : *Gp;
+  const int *st = B.gtab ? start + B.cell_base[bx] : start;
+  int bj;
+  double bt;
+  exact_partner(i, a, G, st, rec, dt, crank,
+                [&](int j) { return status && status[j] == ST_COLLIDED; }, bj, bt);
+  if (__lane_id() == 0) {
+    key_j[i] = bj;
+    key_t[i] = bt;
+  }
+}
+
+// Exact partners of a list of spheres, one wave per sphere: `list` of length nlist,
+// or *nlist_dev when given, or, with list NULL, all i < nlist.  For spheres whose
+// contacts overflowed the slots and grids with fewer than 3 cells along some axis.
 __global__ __launch_bounds__(256) void k_gather_exact(const int *list, int nlist,
-                                                      const unsigned int *nlist_dev, int select,
+                                                      const unsigned int *nlist_dev,
                                                       const Rec *rec, const int *start,
-                                                      const Grid *Gp, double dt,
-                                                      const uint8_t *status, int *key_j,
+                                                      const Grid *Gp, double dt, int *key_j,
                                                       double *key_t, BatchDev B,
                                                       const unsigned int *err,
                                                       const unsigned long long *crank) {
@@ -1641,29 +1647,57 @@ __global__ __launch_bounds__(256) void k_gather_exact(const int *list, int nlist
   const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
   const int nw = (gridDim.x * blockDim.x) / WAVE;
   const int count = nlist_dev ? (int)*nlist_dev : nlist;
-  for (int w = wid; w < count; w += nw) {
-    const int i = list ? list[w] : w;
-    if (select >= 0 && status[i] != (uint8_t)select) continue;
-    // the sphere's grid: the single one, or its box's in the batched form
-    const Rec a = rec[i];
-    const int bx = B.gtab ? a.box : 0;
-    const Grid G = B.gtab ? B.gtab[bx] : *Gp;
-    const int *st = B.gtab ? start + B.cell_base[bx] : start;
-    int bj;
-    double bt;
-    exact_partner(i, a, G, st, rec, dt, crank,
-                  [&](int j) { return status && status[j] == ST_COLLIDED; }, bj, bt);
-    if (__lane_id() == 0) {
-      key_j[i] = bj;
-      key_t[i] = bt;
+  for (int w = wid; w < count; w += nw)
+    gather_one(list ? list[w] : w, rec, start, Gp, dt, nullptr, key_j, key_t, B, crank);
+}
+
+// Keys of a masked detect's ACTIVE spheres.  Behind the pair tests (pairs: they
+// were queued, and taken) from their slots, a lane to a sphere, or where they
+// overflowed by the exact search; else all by the search.  There a wave looks at
+// every nw-th sphere, so neighbours, which may be active together, go to different
+// waves; 64 statuses at a time (one after another, 2M spheres of which none was
+// active took 257 us, now 154).
+__global__ __launch_bounds__(256) void k_masked_keys(const SweepCounters *ctr, int n, int pairs,
+                                                     int K, const int *cnt, const double *slot_t,
+                                                     const int *slot_j, const Rec *rec,
+                                                     const int *start, const Grid *Gp, double dt,
+                                                     const uint8_t *status, int *key_j,
+                                                     double *key_t) {
+  const BatchDev B{};
+  const bool dense = pairs && masked_dense(ctr, n);
+  const int nw = (gridDim.x * blockDim.x) / WAVE;
+  const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
+  // a wave's first sphere and the distance between its lanes' spheres
+  const int64_t first = dense ? (int64_t)wid * WAVE : wid;
+  const int stride = dense ? 1 : nw;
+  for (int64_t w0 = first; w0 < n; w0 += (int64_t)nw * WAVE) {
+    const int64_t i = w0 + (int64_t)__lane_id() * stride;
+    bool search = i < n && status[i] == ST_ACTIVE;
+    if (dense && search) {
+      const int c = cnt[i];
+      search = c > K;
+      if (!search) {
+        int bj;
+        double bt;
+        slot_choice((int)i, c, (size_t)n, slot_t, slot_j, rec, Grid{}, nullptr,
+                    GoneCollided{status}, bj, bt);
+        key_j[i] = bj;
+        key_t[i] = bt;
+      }
+    }
+    unsigned long long todo = __builtin_amdgcn_ballot_w64(search);
+    while (todo) {
+      const int l = __ffsll((long long)todo) - 1;
+      todo &= todo - 1ull;
+      gather_one((int)(w0 + (int64_t)l * stride), rec, start, Gp, dt, status, key_j, key_t, B,
+                 nullptr);
     }
   }
 }
 
 hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const unsigned int *nlist_dev,
-                               int select, const Rec *rec, const int *start, const Grid *G,
-                               double dt, const uint8_t *status, int *key_j, double *key_t,
-                               const BatchDev *B, const unsigned int *err,
+                               const Rec *rec, const int *start, const Grid *G, double dt, int *key_j,
+                               double *key_t, const BatchDev *B, const unsigned int *err,
                                const unsigned long long *crank) {
   // a list whose length is on the device is mostly short: a wave for 8 of the nlist
   // spheres it could name at most, in 16 to 2048 workgroups (for 64, one contact
@@ -1673,8 +1707,21 @@ hipError_t launch_gather_exact(hipStream_t s, const int *list, int nlist, const 
   if (waves > 8192) waves = 8192;
   const int blocks = (int)((waves + 3) / 4);
   BatchDev none{};
-  hipLaunchKernelGGL(k_gather_exact, dim3(blocks), dim3(256), 0, s, list, nlist, nlist_dev, select,
-                     rec, start, G, dt, status, key_j, key_t, B ? *B : none, err, crank);
+  hipLaunchKernelGGL(k_gather_exact, dim3(blocks), dim3(256), 0, s, list, nlist, nlist_dev, rec,
+                     start, G, dt, key_j, key_t, B ? *B : none, err, crank);
+  return hipGetLastError();
+}
+
+// Workgroups: a lane to a sphere, and for few spheres, where they search, up to
+// 8192 waves for them.
+hipError_t launch_masked_keys(hipStream_t s, const SweepCounters *ctr, int n, bool pairs, int K,
+                              const int *cnt, const double *slot_t, const int *slot_j,
+                              const Rec *rec, const int *start, const Grid *G, double dt,
+                              const uint8_t *status, int *key_j, double *key_t) {
+  if (n <= 0) return hipSuccess;
+  const int blocks = (int)std::max(((int64_t)n + 255) / 256, (int64_t)(std::min(n, 8192) + 3) / 4);
+  hipLaunchKernelGGL(k_masked_keys, dim3(blocks), dim3(256), 0, s, ctr, n, (int)pairs, K, cnt,
+                     slot_t, slot_j, rec, start, G, dt, status, key_j, key_t);
   return hipGetLastError();
 }
 
@@ -2408,7 +2455,8 @@ hipError_t launch_advance(hipStream_t s, const Particles &P, const int *partner,
 // ---------------------------------------------------------------- public single-sweep API
 
 // caller active mask -> sorted status (inactive spheres are excluded like
-// collided ones); clears the contact counts and counts the active spheres
+// collided ones); clears the contact counts and counts the active spheres (on one
+// address, the 1172 adds for 300,000 spheres took 12 us)
 __global__ __launch_bounds__(256) void k_status_from_active(const uint8_t *active,
                                                             const Rec *rec, int n,
                                                             uint8_t *status, int *cnt,
@@ -2420,20 +2468,7 @@ __global__ __launch_bounds__(256) void k_status_from_active(const uint8_t *activ
     status[i] = act ? ST_ACTIVE : ST_COLLIDED;
     cnt[i] = 0;
   }
-  block_add(act ? 1ull : 0ull, &my_shard(ctr).pairs);
-}
-
-// How a masked detect goes on: the pair tests of all spheres and a choice among
-// the slots of the active ones (sparse_off), or the exact search of each active
-// sphere (pairs_off).  The pair tests take about 0.17 ns a sphere whatever the
-// mask, the search 3 ns an active sphere (150 us for 50,000, against 45 us).
-__global__ __launch_bounds__(NSHARD) void k_masked_choice(SweepCounters *ctr, int n) {
-  const unsigned long long active = wave_sum(ctr->shard[threadIdx.x].pairs);
-  if (threadIdx.x == 0) {
-    const bool dense = active * 16ull > (unsigned long long)n;
-    ctr->pairs_off = dense ? 0u : 1u;
-    ctr->sparse_off = dense ? 1u : 0u;
-  }
+  block_add(act ? 1ull : 0ull, &ctr->shard[blockIdx.x % ACTIVE_SHARDS].active);
 }
 
 hipError_t launch_status_from_active(hipStream_t s, const uint8_t *active, const Rec *rec, int n,
@@ -2441,15 +2476,16 @@ hipError_t launch_status_from_active(hipStream_t s, const uint8_t *active, const
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_status_from_active, dim3((n + 255) / 256), dim3(256), 0, s, active, rec,
                      n, status, cnt, ctr);
-  hipLaunchKernelGGL(k_masked_choice, dim3(1), dim3(NSHARD), 0, s, ctr, n);
   return hipGetLastError();
 }
 
 // keys in the caller's order: (bits of (float)t) << 32 | caller index of the partner
 __global__ __launch_bounds__(256) void k_export_keys(int n, const Rec *rec, const int *key_j,
                                                      const double *key_t, const uint8_t *status,
-                                                     uint64_t *key_out, double *tmin_out) {
+                                                     SweepCounters *ctr, uint64_t *key_out,
+                                                     double *tmin_out) {
   const int i = blockIdx.x * 256 + threadIdx.x;
+  if (status && i < ACTIVE_SHARDS) ctr->shard[i].active = 0ull;
   if (i >= n) return;
   const int o = rec[i].o;
   const int j = key_j[i];
@@ -2466,11 +2502,11 @@ __global__ __launch_bounds__(256) void k_export_keys(int n, const Rec *rec, cons
 }
 
 hipError_t launch_export_keys(hipStream_t s, int n, const Rec *rec, const int *key_j,
-                              const double *key_t, const uint8_t *status, uint64_t *key_out,
-                              double *tmin_out) {
+                              const double *key_t, const uint8_t *status, SweepCounters *ctr,
+                              uint64_t *key_out, double *tmin_out) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_export_keys, dim3((n + 255) / 256), dim3(256), 0, s, n, rec, key_j, key_t,
-                     status, key_out, tmin_out);
+                     status, ctr, key_out, tmin_out);
   return hipGetLastError();
 }
 
