@@ -13,6 +13,9 @@ namespace {
 
 constexpr int WAVE = 64;
 
+// Any object read or written by words: these may alias every type.
+typedef unsigned long long __attribute__((may_alias)) Word64;
+
 __device__ __forceinline__ unsigned long long dbits(double v) {
   return (unsigned long long)__double_as_longlong(v);
 }
@@ -104,16 +107,22 @@ template <typename R, int PARTS = sizeof(R) / 16>
 __device__ __forceinline__ void store_records(const R &r, int pos, R *dst, Stage<PARTS> &S) {
   constexpr int STRIDE = PARTS | 1;
   const int lane = __lane_id();
-  const Part16 *src = reinterpret_cast<const Part16 *>(&r);
+  Part16 mine[PARTS];  // copied as bytes: the records are objects of other types
+  static_assert(sizeof(R) == sizeof(mine), "whole parts");
+  __builtin_memcpy(mine, &r, sizeof(R));
 #pragma unroll
-  for (int p = 0; p < PARTS; ++p) S.part[lane * STRIDE + p] = src[p];
+  for (int p = 0; p < PARTS; ++p) S.part[lane * STRIDE + p] = mine[p];
   S.pos[lane] = pos;
   __builtin_amdgcn_wave_barrier();  // (a wave's LDS operations stay in order)
 #pragma unroll
   for (int q = 0; q < PARTS; ++q) {
     const int at = q * WAVE + lane, who = at / PARTS, p = at % PARTS;
     const int to = S.pos[who];
-    if (to >= 0) reinterpret_cast<Part16 *>(dst + to)[p] = S.part[who * STRIDE + p];
+    if (to >= 0) {
+      char *part = reinterpret_cast<char *>(dst + to) + p * sizeof(Part16);
+      __builtin_memcpy(__builtin_assume_aligned(part, 16), &S.part[who * STRIDE + p],
+                       sizeof(Part16));
+    }
   }
   __builtin_amdgcn_wave_barrier();
 }
@@ -287,7 +296,7 @@ __global__ __launch_bounds__(256) void k_plan(PlanArgs A, int nparts, const Reac
                                               ScanState *scan, StepPlan *plan,
                                               StepPlan *plan_host) {
   const int t = threadIdx.x;
-  unsigned long long *w = (unsigned long long *)ctr;
+  Word64 *w = (Word64 *)ctr;
   for (int k = t; k < (int)(sizeof(SweepCounters) / 8); k += 256) w[k] = 0ull;
   // the split quantile's bin: the first one whose running count reaches it
   constexpr int PER = RHO_BINS / 256;
@@ -329,10 +338,10 @@ __global__ __launch_bounds__(256) void k_plan(PlanArgs A, int nparts, const Reac
   __shared__ StepPlan out;
   if (t == 0) make_plan(A, red[0], bin < RHO_BINS - 1 ? bin : -1, out);
   __syncthreads();
-  const unsigned long long *o = (const unsigned long long *)&out;
+  const Word64 *o = (const Word64 *)&out;
   for (int k = t; k < (int)(sizeof(StepPlan) / 8); k += 256) {
-    ((unsigned long long *)plan)[k] = o[k];
-    ((unsigned long long *)plan_host)[k] = o[k];
+    ((Word64 *)plan)[k] = o[k];
+    ((Word64 *)plan_host)[k] = o[k];
   }
   if (out.err != 0u) return;  // (then there may be no room for the cells either)
   for (int k = t; k <= scan_tiles(out.cells); k += 256) scan->word[k] = 0ull;
@@ -2192,7 +2201,7 @@ __global__ __launch_bounds__(1024) void k_bin_small(Particles P, PlanArgs A, Swe
   constexpr int PER = SMALL_N / 1024;
   __shared__ int count[SMALL_CELLS + 1];
   __shared__ StepPlan S;
-  unsigned long long *w = (unsigned long long *)ctr;
+  Word64 *w = (Word64 *)ctr;
   for (int k = t; k < (int)(sizeof(SweepCounters) / 8); k += 1024) w[k] = 0ull;
   double v2 = 0.0, rm = 0.0, rn = INFINITY, em = 0.0;
   unsigned int bad = 0u;
@@ -2239,10 +2248,10 @@ __global__ __launch_bounds__(1024) void k_bin_small(Particles P, PlanArgs A, Swe
   }
   for (int k = t; k <= SMALL_CELLS; k += 1024) count[k] = 0;
   __syncthreads();
-  const unsigned long long *o = (const unsigned long long *)&S;
+  const Word64 *o = (const Word64 *)&S;
   for (int k = t; k < (int)(sizeof(StepPlan) / 8); k += 1024) {
-    ((unsigned long long *)plan)[k] = o[k];
-    ((unsigned long long *)plan_host)[k] = o[k];
+    ((Word64 *)plan)[k] = o[k];
+    ((Word64 *)plan_host)[k] = o[k];
   }
   if (S.err) return;
   const Grid &G = S.G;
