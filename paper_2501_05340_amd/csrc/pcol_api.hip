@@ -828,6 +828,21 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
     if (W.exact && !ctx->plan.small &&
         (st = overflow_search(ctx, dt, crank)) != PCOL_OK)
       return st;
+    // The plan did not fit what was queued behind it, and nothing has run: once more,
+    // behind a wait.  The events of the binning and the pair tests are taken again.
+    const auto start_over = [&]() -> pcol_status {
+      few = one_tail = false;
+      pcol_status again = bin_queue(ctx, p, box, dt, ahead, few);
+      if (again != PCOL_OK) return again;
+      if (timing) PCOL_HIP(hipEventRecord(ctx->ev[1], s));
+      ctx->detect_timed = false;
+      if ((again = detect_all(ctx, dt, crank)) != PCOL_OK) return again;
+      if (timing) PCOL_HIP(hipEventRecord(ctx->ev[2], s));
+      W = sweep_args(ctx, P, dt, e);
+      W.crank = crank;
+      if (spin) W.spin = *spin;
+      return W.exact && !ctx->plan.small ? overflow_search(ctx, dt, crank) : PCOL_OK;
+    };
     // All the sweeps that the step is likely to take, and the free flight behind
     // them, are queued at once: a sweep runs if the one before it resolved a pair,
     // the free flight if the last one resolved none.  Steps that need more are
@@ -839,12 +854,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
       ahead = false;
       if (ctx->plan_h->err == PLAN_AGAIN) {  // too many cells, or a grid of another kind
         ctx->many_cells = ctx->plan_h->cells > SMALL_CELLS;
-        few = one_tail = false;
-        if ((st = bin_queue(ctx, p, box, dt, ahead, few)) != PCOL_OK) return st;
-        if ((st = detect_all(ctx, dt, crank)) != PCOL_OK) return st;
-        W = sweep_args(ctx, P, dt, e);
-        W.crank = crank;
-        if (spin) W.spin = *spin;
+        if ((st = start_over()) != PCOL_OK) return st;
       } else {
         if ((st = take_plan(ctx)) != PCOL_OK) return st;
         if (ctx->rep->n_overflow) {  // nothing ran: sweeps that can search
@@ -880,15 +890,7 @@ static pcol_status step_impl(pcol_ctx *ctx, pcol_particles *p, const pcol_box *b
         ahead = false;
         if (ctx->plan_h->err == PLAN_AGAIN) {
           ctx->many_cells = few && ctx->plan_h->cells > SMALL_CELLS;
-          few = false;
-          if ((st = bin_queue(ctx, p, box, dt, ahead, few)) != PCOL_OK) return st;
-          if ((st = detect_all(ctx, dt, crank)) != PCOL_OK) return st;
-          W = sweep_args(ctx, P, dt, e);
-          W.crank = crank;
-          if (spin) W.spin = *spin;
-          if (W.exact && !ctx->plan.small &&
-              (st = overflow_search(ctx, dt, crank)) != PCOL_OK)
-            return st;
+          if ((st = start_over()) != PCOL_OK) return st;
           continue;
         }
         if ((st = take_plan(ctx)) != PCOL_OK) return st;
