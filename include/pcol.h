@@ -229,12 +229,18 @@ pcol_status pcol_advance(pcol_ctx *ctx, pcol_particles *p, const pcol_box *box, 
  * flight and wrap; p is updated in place.  partner (device int32[n], nullable):
  * the caller index of the sphere i collided with, or -1.  tcoll (device
  * double[n], nullable): contact time within the step, NaN if none.
- * stats (host, nullable).  Synchronises at its end, once for every further group
- * of sweeps when the step takes more of them than were queued, and once before
- * the pair tests in the first call of a shape (sphere count, box, dt, walls), for
- * grids with fewer than 3 cells on an axis, and when the grid outgrows the
- * context's cell arrays or gains the extent split.  On PCOL_E_SWEEPS p is left as it was (the end-of-step state is written
- * only once the sweeps are done). */
+ * stats (host, nullable).  Synchronises at its end, and once more
+ * - for every further group of sweeps when the step takes more of them than were
+ *   queued;
+ * - before the pair tests in the first call of a shape (sphere count, box, dt,
+ *   walls) and for grids with fewer than 3 cells on an axis;
+ * - when the grid of a later call of the shape outgrows the context's cell arrays,
+ *   first has the extent split, falls below 3 cells on an axis or, under 4096
+ *   spheres, exceeds 8192 cells: the step then starts over;
+ * - the first time that a sphere of the context has more contacts than slots: the
+ *   sweeps are queued again.
+ * On PCOL_E_SWEEPS p is left as it was (the end-of-step state is written only once
+ * the sweeps are done). */
 pcol_status pcol_step(pcol_ctx *ctx, pcol_particles *p, const pcol_box *box, double dt, double e,
                       int32_t *partner, double *tcoll, pcol_stats *stats);
 

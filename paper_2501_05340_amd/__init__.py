@@ -349,7 +349,8 @@ def pcol_step_batched(ctx: Context, p: Particles, box_off, Ls, dt: float, e: flo
     if nbox < 1 or len(Ls) != nbox:
         raise ValueError("box_off needs nbox + 1 entries and Ls nbox boxes")
     off_arr = (ctypes.c_int64 * (nbox + 1))(*off)
-    # the sides flat, one conversion for all boxes (one store per side took 0.6 ms for 512)
+    # the sides flat, one conversion for all boxes (one store per side: 383 us a call of 512
+    # boxes in the binding, so 225)
     sides = []
     for L in Ls:
         if isinstance(L, (int, float)):

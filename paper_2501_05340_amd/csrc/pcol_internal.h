@@ -598,9 +598,9 @@ struct Particles {
 
 // Boxes that one workgroup bins (k_bin_small): fewer spheres than a plan needs to
 // split, and cells whose counts fit LDS.  And boxes that one workgroup sweeps
-// (k_sweeps_small): up to two spheres a thread; the queued kernels take the same
-// time up to 6,000 spheres, and both together a step of 93 us where this one
-// takes 78 at 2,000 spheres (phi 0.05), 94 at 3,000 and 111 at 4,000.
+// (k_sweeps_small): up to two spheres a thread.  A step of 500, 1,000, 2,000, 3,000
+// and 4,000 spheres (phi 0.05) takes 54, 60, 75, 91 and 106 us with it, and 74, 76,
+// 82, 88 and 89 with the queued kernels, which the launches bound.
 constexpr int SMALL_N = 4096;
 constexpr int SMALL_CELLS = 8192;
 constexpr int SMALL_TAIL = 2048;

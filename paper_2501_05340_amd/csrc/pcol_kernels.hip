@@ -440,7 +440,8 @@ __device__ void block_exclusive_scan(int v, int &excl) {
   __syncthreads();
 }
 
-// Exclusive scan of the cell counts into start (start[n] the total) in one pass:
+// Exclusive scan of the cell counts into start (start[n] the total) in one pass, by
+// the published decoupled look-back method (Merrill and Garland, 2016):
 // workgroups take tiles of SCAN_B cells in order, publish a tile's sum as soon
 // as they have it and its running total once they have added those before it,
 // looked up 64 tiles at a time by one wave.  A tile only waits for tiles taken
@@ -631,10 +632,10 @@ __device__ __forceinline__ void record_contact(const DetectArgs &A, int i, int g
 // pairs in the wave's LDS queue.  A survivor is rare (about one per home
 // sphere); deciding it at once would run the square root, the division and
 // two atomics for one live lane while the other 63 idle, so survivors are
-// queued and decided 64 at a time at the end of the home cell, where few
-// registers are live, or sooner when the queue has no room for another step's.
+// queued and decided 64 at a time, outside the filter loops, where few registers
+// are live, or sooner when the queue has no room for another step's.
 constexpr int QCAP = 256;    // binary32 filter: two homes appended per step
-constexpr int QCAP64 = 512;  // binary64 filter: four homes
+constexpr int QCAP64 = 512;  // binary64 filter: two homes against three chunks
 
 struct SurvivorQueue {
   int2 *q;              // cap entries in LDS, private to the wave
