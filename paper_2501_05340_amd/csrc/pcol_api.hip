@@ -690,7 +690,9 @@ pcol_status pcol_detect(pcol_ctx *ctx, const pcol_particles *p, const pcol_box *
   const int n = (int)p->n;
   if (n == 0) return PCOL_OK;
   if (!active) {
-    PCOL_HIP(hipMemsetAsync(ctx->ctr_d, 0, sizeof(SweepCounters), s));
+    // cleared by kernels: the call waits for nothing, so a caller may capture it, and
+    // memset nodes of a graph are not relied on
+    PCOL_HIP(launch_fill_u32(s, (unsigned int *)ctx->ctr_d, 0u, sizeof(SweepCounters) / 4));
     PCOL_HIP(launch_fill_i32(s, ctx->cnt, 0, n));
     if ((st = detect_all(ctx, dt, nullptr)) != PCOL_OK) return st;
     if (!ctx->plan.small && (st = overflow_search(ctx, dt, nullptr)) != PCOL_OK) return st;
